@@ -408,43 +408,54 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_dkdv_kernel(DkdvParams p) {
                 mfma_a(dkacc[1][db], dsp[1][c], bqt);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (t == 0) {
-                    // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  Index by index only
-                    // on row tiles that reach the diagonal, on padding steps and, with packed documents, on the
-                    // row tile in which some key's document ends.  A key whose document ends before the row
-                    // tile is seen by none of its rows: all 16 of its S' take one select on a per-lane flag
-                    // (a select, not arithmetic: S' of such a pair may be anything, a NaN included).  A wave
-                    // whose keys straddle a document boundary is in that state for every row tile of the later
-                    // document; masked index by index, it held the whole workgroup back on its longest walk.
-                    bool elementwise = cur_it <= it_mask_lo || step_no >= total;
-                    if (VARLEN && cur_it >= it_mask_hi) {  // rows at or past the end of the first key's document
+                    // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  The element of register r
+                    // is row q0 + 4*hi + c_r with c_r = 8*(r/4) + r%4 known at compile time, so "hidden" is one
+                    // compare of c_r with a per-lane limit and one select.  A step none of whose rows sees any of
+                    // the wave's keys (above the wave's diagonal while the rest of the workgroup is still on
+                    // theirs, and padding) is overwritten outright: a wave is in that state for up to six of the
+                    // eight steps of a tile's diagonal, and the whole workgroup waits for it at each barrier.
+                    // With packed documents, a key whose document ends before the row tile is seen by none of
+                    // its rows: all 16 of its S' take one select on a per-lane flag (a select, not arithmetic: S'
+                    // of such a pair may be anything, a NaN included); upper limits are compared element by
+                    // element only on the row tile in which some key's document (dense: the sequence) ends.
+                    if (cur_it <= it_mask_lo || step_no >= total) {
                         const int q0 = cur_it * BMQ;
-                        const bool dead0 = khi_l[0] <= q0, dead1 = khi_l[1] <= q0;
-                        elementwise = elementwise ||
-                                      __builtin_amdgcn_ballot_w64((khi_l[0] > q0 && khi_l[0] < q0 + BMQ) ||
-                                                                  (khi_l[1] > q0 && khi_l[1] < q0 + BMQ)) != 0;
-                        if (!elementwise && __builtin_amdgcn_ballot_w64(dead0 || dead1) != 0) {
+                        if (step_no >= total || q0 + BMQ - 1 + p.off < wkey0) {
                             asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
-                                sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
+                            for (int r = 0; r < 16; ++r) { sacc[0][r] = -__builtin_inff(); sacc[1][r] = -__builtin_inff(); }
+                        } else {
+                            asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
+#pragma unroll
+                            for (int kbk = 0; kbk < 2; ++kbk) {
+                                const int key = wkey0 + 32 * kbk + (int)(__lane_id() & 31);
+                                const int lim = key - p.off - q0 - 4 * (int)(__lane_id() >> 5);  // first row that sees the key
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) sacc[kbk][r] = 8 * (r / 4) + r % 4 >= lim ? sacc[kbk][r] : -__builtin_inff();
                             }
                         }
                     }
-                    if (!VARLEN && cur_it >= it_mask_hi) elementwise = true;  // rows past the end of the sequence
-                    if (elementwise) {  // rare
-                        asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
+                    if (cur_it >= it_mask_hi) {  // rows at or past the end of the first key's document or of the sequence
                         const int q0 = cur_it * BMQ;
-                        const bool real = step_no < total;
+                        const bool inside = !VARLEN || __builtin_amdgcn_ballot_w64((khi_l[0] > q0 && khi_l[0] < q0 + BMQ) ||
+                                                                                   (khi_l[1] > q0 && khi_l[1] < q0 + BMQ)) != 0;
+                        if (inside) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                        for (int kbk = 0; kbk < 2; ++kbk) {
-                            const int key = wkey0 + 32 * kbk + (int)(__lane_id() & 31);
-                            const int key_hi = VARLEN ? khi_l[kbk] : S;  // one past the last row that may see the key
+                            for (int kbk = 0; kbk < 2; ++kbk) {
+                                const int lim = (VARLEN ? khi_l[kbk] : S) - q0 - 4 * (int)(__lane_id() >> 5);
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const int row = q0 + 8 * (r / 4) + 4 * (int)(__lane_id() >> 5) + (r % 4);
-                                const bool vis = real && row + p.off >= key && row < key_hi;
-                                sacc[kbk][r] = vis ? sacc[kbk][r] : -__builtin_inff();
+                                for (int r = 0; r < 16; ++r) sacc[kbk][r] = 8 * (r / 4) + r % 4 < lim ? sacc[kbk][r] : -__builtin_inff();
+                            }
+                        } else {
+                            const bool dead0 = khi_l[0] <= q0, dead1 = khi_l[1] <= q0;
+                            if (__builtin_amdgcn_ballot_w64(dead0 || dead1) != 0) {
+                                asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) {
+                                    sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
+                                    sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
+                                }
                             }
                         }
                     }

@@ -211,8 +211,9 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_dq_kernel(DqParams p) {
     int step_no = 0;        // its number (the step count is padded to a multiple of NBUF: steps >= total are not real)
     // steps whose S' needs masking: from the first whose keys reach past the last key the wave's first row
     // may see (and every padding step), and, for packed documents, those before the wave's last row's
-    // document starts
+    // document starts; from dead_from on the wave sees no key at all
     const int mask_from = (last_key(wrow0) / BN - jt_begin) < total ? (last_key(wrow0) / BN - jt_begin) : total;
+    const int dead_from = (last_key(wrow0 + RPW - 1) / BN + 1 - jt_begin) < total ? (last_key(wrow0 + RPW - 1) / BN + 1 - jt_begin) : total;
     const int mask_until = VARLEN ? (wave_lo_max + BN - 1) / BN - jt_begin : 0;
     {
         static_for<0, PW>([&](auto K) { issue_load(K, NBUF - 1); });  // K rows of step 0 again, as the stand-in
@@ -345,43 +346,56 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_dq_kernel(DqParams p) {
                 else mfma_v_ab<-1>(pacc[1], av[kk], doreg[1][kk]);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (kk == 0) {
-                    // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  Index by index only
-                    // on steps that reach the diagonal (or are padding) and, with packed documents, on the
-                    // step in which some row's document starts.  A row whose document starts after the step's
-                    // keys sees none of them: all 16 of its S' take one select on a per-lane flag (a select, not
-                    // arithmetic: S' of such a pair may be anything, a NaN included).  A wave whose rows
-                    // straddle a document boundary is in that state for every step of the earlier document;
-                    // masked index by index, it held the whole workgroup back on its longest walk.
-                    bool elementwise = step_no >= mask_from;
-                    if (VARLEN && step_no < mask_until) {  // some row's document starts at or after this step's keys
-                        const int j0 = cur_jt * BN;
-                        const bool dead0 = rlo_l[0] >= j0 + BN, dead1 = rlo_l[1] >= j0 + BN;
-                        elementwise = elementwise ||
-                                      __builtin_amdgcn_ballot_w64((rlo_l[0] > j0 && rlo_l[0] < j0 + BN) ||
-                                                                  (rlo_l[1] > j0 && rlo_l[1] < j0 + BN)) != 0;
-                        if (!elementwise && __builtin_amdgcn_ballot_w64(dead0 || dead1) != 0) {
+                    // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  The element of register r
+                    // is key j0 + 4*hi + c_r with c_r = 8*(r/4) + r%4 known at compile time, so "hidden" is one
+                    // compare of c_r with a per-lane limit and one select.  A step none of whose keys the wave
+                    // sees (past its diagonal while the rest of the workgroup is still on theirs, and padding)
+                    // is overwritten outright: a wave is in that state for up to six of the eight steps of a
+                    // tile's diagonal, and every wave of the workgroup waits for it at each step's barrier
+                    // (diagonal block of 256 rows: 14.3 us with bounds compared index by index on all eight
+                    // steps, against 6.0 us for eight unmasked steps).
+                    // With packed documents, a row whose document starts after the step's keys sees none of
+                    // them: all 16 of its S' take one select on a per-lane flag (a select, not arithmetic: S' of
+                    // such a pair may be anything, a NaN included); lower limits are compared element by element
+                    // only on the step in which some row's document starts.
+                    if (step_no >= mask_from) {
+                        if (step_no >= dead_from) {
                             asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
-                                sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
+                            for (int r = 0; r < 16; ++r) { sacc[0][r] = -__builtin_inff(); sacc[1][r] = -__builtin_inff(); }
+                        } else {
+                            asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
+#pragma unroll
+                            for (int qb = 0; qb < 2; ++qb) {
+                                const int row = wrow0 + 32 * qb + (int)(__lane_id() & 31);
+                                const int rhi = row + p.off < p.Skv - 1 ? row + p.off : p.Skv - 1;  // last key it may see
+                                const int lim = rhi - cur_jt * BN - 4 * (int)(__lane_id() >> 5);
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) sacc[qb][r] = 8 * (r / 4) + r % 4 <= lim ? sacc[qb][r] : -__builtin_inff();
                             }
                         }
                     }
-                    if (elementwise) {  // rare
-                        asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
+                    if (VARLEN && step_no < mask_until) {  // some row's document starts at or after this step's keys
                         const int j0 = cur_jt * BN;
-                        const bool real = step_no < total;
+                        const bool inside = __builtin_amdgcn_ballot_w64((rlo_l[0] > j0 && rlo_l[0] < j0 + BN) ||
+                                                                        (rlo_l[1] > j0 && rlo_l[1] < j0 + BN)) != 0;
+                        if (inside) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                        for (int qb = 0; qb < 2; ++qb) {
-                            const int row = wrow0 + 32 * qb + (int)(__lane_id() & 31);
-                            const int rlo = VARLEN ? rlo_l[qb] : 0;  // first key the row may see
-                            const int rhi = row + p.off < p.Skv - 1 ? row + p.off : p.Skv - 1;  // and the last
+                            for (int qb = 0; qb < 2; ++qb) {
+                                const int lim = rlo_l[qb] - j0 - 4 * (int)(__lane_id() >> 5);
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const int key = j0 + 8 * (r / 4) + 4 * (int)(__lane_id() >> 5) + (r % 4);
-                                const bool vis = real && key <= rhi && key >= rlo;
-                                sacc[qb][r] = vis ? sacc[qb][r] : -__builtin_inff();
+                                for (int r = 0; r < 16; ++r) sacc[qb][r] = 8 * (r / 4) + r % 4 >= lim ? sacc[qb][r] : -__builtin_inff();
+                            }
+                        } else {
+                            const bool dead0 = rlo_l[0] >= j0 + BN, dead1 = rlo_l[1] >= j0 + BN;
+                            if (__builtin_amdgcn_ballot_w64(dead0 || dead1) != 0) {
+                                asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) {
+                                    sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
+                                    sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
+                                }
                             }
                         }
                     }

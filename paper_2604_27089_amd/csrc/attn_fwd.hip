@@ -224,14 +224,16 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(FwdParams p) {
         bool need_mask = j0 + BN - 1 > wave_hi_min;
         if (VARLEN) need_mask = need_mask || (j0 < wave_lo_max);
         if (need_mask) {
+            // register r of block nb is key j0 + 4*hi + c with c known at compile time: one compare with a
+            // per-lane limit and one select per bound
+            const int lim = qhi - j0 - 4 * hi, lim_lo = row_lo - j0 - 4 * hi;
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int key = j0 + 32 * nb + 8 * (r / 4) + 4 * hi + (r % 4);
-                    bool vis = key <= qhi;
-                    if (VARLEN) vis = vis && key >= row_lo;
-                    if (!vis) sacc[nb][r] = -INFINITY;
+                    const int c = 32 * nb + 8 * (r / 4) + r % 4;
+                    sacc[nb][r] = c <= lim ? sacc[nb][r] : -INFINITY;
+                    if (VARLEN) sacc[nb][r] = c >= lim_lo ? sacc[nb][r] : -INFINITY;
                 }
         }
         float mx = fmaxf(sacc[0][0], sacc[1][0]);
