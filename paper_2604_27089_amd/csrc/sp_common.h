@@ -86,6 +86,19 @@ inline dim3 tile_rank_grid(int32_t Hq, int32_t B, int32_t n_tiles) {
     return dim3((uint32_t)Hq * (uint32_t)B, (uint32_t)n_tiles < kRankY ? (uint32_t)n_tiles : kRankY,
                 ((uint32_t)n_tiles + kRankY - 1) / kRankY);
 }
+// How many key groups share a forward workgroup (attn_fwd.hip): its 8 waves cover 256 / KS rows, and every KS-th
+// key tile goes to the same group.  A compute unit holds one workgroup, and a workgroup walks its keys tile by
+// tile, so a launch of few 256-row tiles leaves most units idle while the longest tile is walked alone: KS groups
+// give KS times the workgroups, each with 1/KS of the walk, for KS times the K/V bytes staged per product.
+// Measured, 4 query heads of D = 128, KS = 1 / 2 / 4, us: 512 rows (8 tiles) 23 / 17 / 15, 4096 rows (64) 106 / 61 /
+// 49, 8192 rows (128) 196 / 116 / 114, 12288 rows (192) 310 / 192 / 247, 16384 rows (256) 405 / 292 / 379, 24576 rows
+// (384) 654 / 639 / 793, 32768 rows (512) 1000 / 1057 / 1365; 8 x 2048 rows (256) 64 / 52 / 73; 64 x 512 rows (512)
+// 49 / 66 / 86; D = 64: 8192 rows 164 / 90 / 64, 16384 rows 318 / 204 / 216.  A function of the extents only, so that
+// every layout and entry point of one problem gives the same bits.
+inline int fwd_key_groups(int64_t B, int64_t S, int32_t Hq) {
+    const int64_t tiles = (S + kOrderTile - 1) / kOrderTile * Hq * B;
+    return tiles <= 128 ? 4 : tiles <= 384 ? 2 : 1;
+}
 sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_dkdv(const AttnArgs& a, hipStream_t st);

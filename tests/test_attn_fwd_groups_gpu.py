@@ -1,0 +1,72 @@
+"""The forward's key groups: how many of them share a workgroup follows from the number of 256-row tiles in the
+call (four up to 128, two up to 384, else one), so the same sequence is run alone and inside larger batches to
+reach all three, each against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref_block as rb
+from oracle import ref_numpy as rn
+from paper_2604_27089_amd import binding as sp
+from paper_2604_27089_amd import synth
+from gpu_util import LSE_MAX_ABS, check_o, dev_bf16, host_f64
+
+pytestmark = pytest.mark.gpu
+
+# batch entries (or heads) that put one-tile and two-tile sequences into each class, edges of the classes among them
+BATCHES = {1: [1, 128, 129, 384, 385], 2: [1, 64, 65, 192, 193]}
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S", [1, 31, 33, 64, 65, 127, 129, 255, 256, 257, 300, 512])
+def test_batch_sizes_of_every_class(S, D):
+    qb, kb, vb, _ = synth.attn_inputs(S + D, S, 1, 1, D)
+    q, k, v = (dev_bf16(t) for t in (qb, kb, vb))
+    o_ref, lse_ref = rn.attn_fwd(*(rn.widen_bf16(t[0]) for t in (qb, kb, vb)))
+    for B in BATCHES[(S + 255) // 256]:
+        o, lse = sp.sp_attn_fwd(*(t.expand(B, -1, -1, -1).contiguous() for t in (q, k, v)))
+        assert torch.equal(o.view(torch.int16), o[:1].expand_as(o).contiguous().view(torch.int16))
+        assert torch.equal(lse, lse[:1].expand_as(lse))
+        check_o(host_f64(o[0]), o_ref, f"S={S} D={D} B={B}")
+        assert np.abs(host_f64(lse[0]) - lse_ref).max() <= LSE_MAX_ABS
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Sq,Skv,off", [(1, 1, 0), (1, 200, 199), (40, 130, 90), (300, 64, 7), (257, 500, 400), (130, 129, 5000)])
+def test_blocks_of_every_class(Sq, Skv, off, D):
+    qb, _, _, _ = synth.attn_inputs(Sq, Sq, 1, 1, D)
+    _, kb, vb, _ = synth.attn_inputs(Skv + 7, Skv, 1, 1, D)
+    q, k, v = (dev_bf16(t) for t in (qb, kb, vb))
+    o_ref, lse_ref = rb.block_attn_fwd(*(rn.widen_bf16(t[0]) for t in (qb, kb, vb)), 1.0 / np.sqrt(D), off)
+    for B in BATCHES[(Sq + 255) // 256]:
+        o, lse = sp.sp_attn_block_fwd(*(t.expand(B, -1, -1, -1).contiguous() for t in (q, k, v)), off)
+        check_o(host_f64(o[B - 1]), o_ref, f"Sq={Sq} Skv={Skv} off={off} D={D} B={B}")
+        assert np.abs(host_f64(lse[B - 1]) - lse_ref).max() <= LSE_MAX_ABS
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq", [4, 60, 140])
+def test_packed_documents_of_every_class(Hq, D):
+    lengths = [70, 0, 1, 300, 63, 129, 200]  # 763 rows: three tiles, the last one ragged
+    cu_h = synth.cu_seqlens_from_lengths(lengths)
+    qb, kb, vb, _ = synth.attn_inputs(Hq, sum(lengths), 2, 1, D)
+    q, k, v = (dev_bf16(t[0]) for t in (qb, kb, vb))
+    o_ref, lse_ref = rn.attn_varlen_fwd(*(rn.widen_bf16(t[0]) for t in (qb, kb, vb)), cu_h)
+    rep = Hq // 2
+    o, lse = sp.sp_attn_varlen_fwd(q.repeat(1, rep, 1), k.repeat(1, rep, 1), v.repeat(1, rep, 1), torch.from_numpy(cu_h).cuda())
+    for h0 in (0, Hq - 2):
+        check_o(host_f64(o[:, h0:h0 + 2]), o_ref, f"Hq={Hq} D={D} heads {h0}..")
+        assert np.abs(host_f64(lse[h0:h0 + 2]) - lse_ref).max() <= LSE_MAX_ABS
+
+
+@pytest.mark.parametrize("S", [2048, 12288, 24832])
+def test_longer_walks_of_every_class(S):
+    """Many tiles per group; the last rows, whose walks are the longest, against the oracle."""
+    qb, kb, vb, _ = synth.attn_inputs(S, S, 4, 1, 128)
+    q, k, v = (dev_bf16(t) for t in (qb, kb, vb))
+    o, lse = sp.sp_attn_fwd(q, k, v)
+    n = 70
+    kf, vf = (rn.widen_bf16(t[0]) for t in (kb, vb))
+    o_ref, lse_ref = rb.block_attn_fwd(rn.widen_bf16(qb[0, S - n:]), kf, vf, 1.0 / np.sqrt(128), S - n)
+    check_o(host_f64(o[0, S - n:]), o_ref, f"S={S}")
+    assert np.abs(host_f64(lse[0, :, S - n:]) - lse_ref).max() <= LSE_MAX_ABS
