@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libsp_hotpath.so")
 # The same sources with every hand-scheduled MFMA padded by full waits and wait states (-DSP_PADDED_MFMA):
 # slow, hazard-proof, bit-identical by construction; a GPU test compares the two builds.
 LIB_PADDED = os.path.join(HERE, "libsp_hotpath_padded.so")
-SOURCES = ["sp_api.hip", "relayout.hip", "doc_bounds.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_bwd_dkdv.hip", "attn_bwd_dq.hip", "attn_merge.hip", "pointwise.hip"]
+SOURCES = ["sp_api.hip", "relayout.hip", "doc_bounds.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_bwd_d128.hip", "attn_bwd_d64.hip", "attn_merge.hip", "pointwise.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Wall", "-Wextra",
          "-Wno-unused-command-line-argument", "-Wno-unused-parameter",
          # keep the compiler from forming packed-fp32 VALU instructions

@@ -6,8 +6,9 @@
 // Three stages, no atomics (bitwise reproducible):
 //   delta : Delta_i = dO_i . O_i and the per-row seeds -LSE_i/scale, -Delta_i
 //           (this file; HBM-bound, fp32 out)
-//   dkdv  : attn_bwd_dkdv.hip
-//   dq    : attn_bwd_dq.hip
+//   dkdv  : attn_bwd_dkdv.h, and the sum of its partial results here
+//   dq    : attn_bwd_dq.h
+// The last two are launched together (attn_bwd_matrix.h).
 // P is rebuilt from the saved LSE: P_ij = exp(scale*s_ij - LSE_i); S and dP
 // are evaluated in both matrix kernels.
 #include "attn_common.h"
@@ -57,7 +58,29 @@ __global__ __launch_bounds__(256) void delta_kernel(const __bf16* __restrict__ o
     }
 }
 
-template <int D, bool VARLEN>
+// dK = scale * sum of the chunks' partial sums, dV = sum of theirs; four elements per thread.  The
+// partial sums are dense [B, S, Hkv*D]; the outputs follow `map`.
+__global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restrict__ part, __bf16* __restrict__ dk,
+                                                         __bf16* __restrict__ dv, int64_t n_out, int32_t nsplit,
+                                                         float scale, RowMap map, int32_t S, int32_t HD) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n_out) return;  // n_out is a multiple of 4 (D is)
+    const int64_t br = i / HD;  // b*S + row
+    const int64_t bb = br / S;
+    const size_t o = (size_t)bb * S * HD + map.off((int32_t)(br - bb * S)) + (size_t)(i - br * HD);
+    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+    for (int32_t s = 0; s < nsplit; ++s) {
+        sk += *reinterpret_cast<const f32x4*>(part + (size_t)s * n_out + i);
+        sv += *reinterpret_cast<const f32x4*>(part + ((size_t)nsplit + s) * n_out + i);
+    }
+    u32x2 wk, wv;
+    wk[0] = pack_bf16(sk[0] * scale, sk[1] * scale); wk[1] = pack_bf16(sk[2] * scale, sk[3] * scale);
+    wv[0] = pack_bf16(sv[0], sv[1]); wv[1] = pack_bf16(sv[2], sv[3]);
+    *reinterpret_cast<u32x2*>(dk + o) = wk;
+    *reinterpret_cast<u32x2*>(dv + o) = wv;
+}
+
+template <int D>
 sp_status launch(const AttnArgs& a, hipStream_t st) {
     if (a.stages & SP_BWD_STAGE_DELTA) {
         const int64_t lanes = (int64_t)a.B * a.S_pad * a.Hq * (D / 8);
@@ -68,13 +91,16 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
                            1.0f / a.scale, a.qmap);
         if (hipGetLastError() != hipSuccess) return SP_ERR_LAUNCH;
     }
-    if (a.stages & SP_BWD_STAGE_DKDV) {
-        const sp_status r = launch_attn_bwd_dkdv(a, st);
+    if (a.stages & (SP_BWD_STAGE_DKDV | SP_BWD_STAGE_DQ)) {
+        const sp_status r = D == 64 ? launch_attn_bwd_matrix_d64(a, st) : launch_attn_bwd_matrix_d128(a, st);
         if (r != SP_OK) return r;
     }
-    if (a.stages & SP_BWD_STAGE_DQ) {
-        const sp_status r = launch_attn_bwd_dq(a, st);
-        if (r != SP_OK) return r;
+    if ((a.stages & SP_BWD_STAGE_DKDV) && a.dkdv_splits > 1) {
+        const int64_t n_out = (int64_t)a.B * a.Skv * a.Hkv * D;
+        const int64_t blocks = (n_out / 4 + 255) / 256;
+        hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a.dkdv_part, (__bf16*)a.dk,
+                           (__bf16*)a.dv, n_out, a.dkdv_splits, a.scale, a.kvmap, a.Skv, a.Hkv * D);
+        if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
     }
     return SP_OK;
 }
@@ -85,9 +111,8 @@ namespace sp {
 
 sp_status launch_attn_bwd(const AttnArgs& a, hipStream_t st) {
     if (a.Hq > 65535 || a.B > 65535) return SP_ERR_SHAPE;
-    const bool varlen = a.row_lo != nullptr;
-    if (a.D == 128) return varlen ? launch<128, true>(a, st) : launch<128, false>(a, st);
-    if (a.D == 64) return varlen ? launch<64, true>(a, st) : launch<64, false>(a, st);
+    if (a.D == 128) return launch<128>(a, st);
+    if (a.D == 64) return launch<64>(a, st);
     return SP_ERR_UNSUPPORTED;
 }
 

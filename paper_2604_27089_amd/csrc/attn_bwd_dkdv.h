@@ -32,12 +32,15 @@
 // asynchronous, issued two slots ahead with exact partial waits, the tile loads
 // of step u+2 are spread over the S phase, and the body is instantiated once per
 // ring position so that all LDS addresses are immediates.
+//
+// This file holds the workgroup's program; attn_bwd_matrix.h has the kernel that
+// runs it, beside the one of attn_bwd_dq.h.
+#pragma once
 #include "attn_common.h"
 #include "sp_common.h"
 
-namespace {
-
-using namespace sp;
+namespace sp {
+namespace dkdv {
 
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
@@ -54,7 +57,7 @@ struct DkdvParams {
     const int32_t* row_hi;
     const int32_t* order;  // packed documents: key tiles in the order workgroups take them (or null)
     RowMap qmap, kvmap;
-    int32_t B, batch_fastest;
+    int32_t B, several;  // several: more than one sequence
     int32_t S, Skv, off, S_pad, Hq, Hkv, G, n_ktiles, nsplit;  // S query rows, Skv keys; row i sees keys j <= i + off
     float scale, scale_log2;
 };
@@ -68,35 +71,43 @@ __device__ __forceinline__ void seeds_to_acc(f32x16& acc, const u32x4 (&s)[4]) {
     }
 }
 
+template <int D>
+struct Lds {
+    static constexpr int TILE_B = BMQ * D * 2;
+    static constexpr int QS = 0, DOS = NBUF * TILE_B, VS = 2 * NBUF * TILE_B, VW_B = KPW * D * 2;
+    static constexpr int AUX = VS + kWaves * VW_B, AUX_SLOT = 1024, AUX_W = NBUF * AUX_SLOT;
+    static constexpr int BYTES = AUX + kWaves * AUX_W;
+};
+
+// The work of workgroup `wg` of n_ktiles * nsplit * Hkv * B; smem holds Lds<D>::BYTES, 1 KB aligned.
 template <int D, bool VARLEN, bool SPLIT>
-__global__ __launch_bounds__(kThreads) void attn_bwd_dkdv_kernel(DkdvParams p) {
+__device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem) {
     constexpr int NS = D / 16;   // operand slots per phase (contraction steps over the head dim)
     constexpr int NDB = D / 32;  // 32-wide blocks of the head dim
-    constexpr int TILE_B = BMQ * D * 2;
     constexpr int HALF_B = 16 * D * 2;  // 16 rows of a tile
-    constexpr int QS = 0, DOS = NBUF * TILE_B, VS = 2 * NBUF * TILE_B, VW_B = KPW * D * 2;
-    constexpr int AUX = VS + kWaves * VW_B, AUX_SLOT = 1024, AUX_W = NBUF * AUX_SLOT;
-    constexpr int SMEM = AUX + kWaves * AUX_W;
+    using L = Lds<D>;
+    constexpr int TILE_B = L::TILE_B, QS = L::QS, DOS = L::DOS, VS = L::VS, VW_B = L::VW_B;
+    constexpr int AUX = L::AUX, AUX_SLOT = L::AUX_SLOT, AUX_W = L::AUX_W;
     static_assert(DOS + (NBUF - 1) * TILE_B + HALF_B < 65536, "immediate LDS offsets must fit 16 bits");
-    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // earliest key tiles (most rows to visit) first; the nsplit workgroups that share a key tile are neighbours
     const int nsplit = SPLIT ? p.nsplit : 1;
-    // Grid: (key tile x chunk, KV head, batch entry) for a single sequence; with several sequences the batch
-    // entry and KV head vary fastest instead, (KV head + Hkv * batch entry, key tile x chunk), so that every
-    // sequence's longest key tiles are dispatched before anybody's short ones (sequence by sequence, the last
-    // sequence's longest tile started when the grid was two thirds done: 16 x 4096 rows 710 -> 510 us).
-    const int chunk_id = p.batch_fastest ? blockIdx.y : blockIdx.x;
+    // Order: chunks of one head together for a single sequence (they share the head's Q/dO stream through L2); with
+    // several sequences the batch entry and KV head vary fastest instead, so that every sequence's longest key
+    // tiles are dispatched before anybody's short ones (sequence by sequence, the last sequence's longest tile
+    // started when the grid was two thirds done: 16 x 4096 rows 710 -> 510 us).
+    const uint32_t n_chunks = (uint32_t)p.n_ktiles * (uint32_t)nsplit, n_heads = (uint32_t)p.Hkv * (uint32_t)p.B;
+    const int chunk_id = (int)(p.several ? wg / n_heads : wg % n_chunks);
+    const int head_id = (int)(p.several ? wg % n_heads : wg / n_chunks);
     int jt = SPLIT ? chunk_id / nsplit : chunk_id;
     const int split = SPLIT ? chunk_id % nsplit : 0;
     if (VARLEN && p.order) {  // longest tile first; clamped so that a bad entry cannot become a wild address
         const int v = __builtin_amdgcn_readfirstlane(p.order[jt]);
         jt = v < 0 ? 0 : (v < p.n_ktiles ? v : p.n_ktiles - 1);
     }
-    const int g = p.batch_fastest ? blockIdx.x % p.Hkv : blockIdx.y;
-    const int b = p.batch_fastest ? blockIdx.x / p.Hkv : blockIdx.z;
+    const int g = head_id % p.Hkv, b = head_id / p.Hkv;
     const int S = p.S, Skv = p.Skv;
     const __bf16* kb = p.k + ((size_t)b * Skv * p.Hkv + g) * D;
     const __bf16* vb = p.v + ((size_t)b * Skv * p.Hkv + g) * D;
@@ -570,66 +581,5 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_dkdv_kernel(DkdvParams p) {
     }
 }
 
-// dK = scale * sum of the chunks' partial sums, dV = sum of theirs; four elements per thread.  The
-// partial sums are dense [B, S, Hkv*D]; the outputs follow `map`.
-__global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restrict__ part, __bf16* __restrict__ dk,
-                                                         __bf16* __restrict__ dv, int64_t n_out, int32_t nsplit,
-                                                         float scale, RowMap map, int32_t S, int32_t HD) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n_out) return;  // n_out is a multiple of 4 (D is)
-    const int64_t br = i / HD;  // b*S + row
-    const int64_t bb = br / S;
-    const size_t o = (size_t)bb * S * HD + map.off((int32_t)(br - bb * S)) + (size_t)(i - br * HD);
-    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    for (int32_t s = 0; s < nsplit; ++s) {
-        sk += *reinterpret_cast<const f32x4*>(part + (size_t)s * n_out + i);
-        sv += *reinterpret_cast<const f32x4*>(part + ((size_t)nsplit + s) * n_out + i);
-    }
-    u32x2 wk, wv;
-    wk[0] = pack_bf16(sk[0] * scale, sk[1] * scale); wk[1] = pack_bf16(sk[2] * scale, sk[3] * scale);
-    wv[0] = pack_bf16(sv[0], sv[1]); wv[1] = pack_bf16(sv[2], sv[3]);
-    *reinterpret_cast<u32x2*>(dk + o) = wk;
-    *reinterpret_cast<u32x2*>(dv + o) = wv;
-}
-
-template <int D, bool VARLEN>
-sp_status launch(const AttnArgs& a, hipStream_t st) {
-    DkdvParams p;
-    p.q = (const __bf16*)a.q; p.k = (const __bf16*)a.k; p.v = (const __bf16*)a.v; p.dO = (const __bf16*)a.dO;
-    p.aux = a.aux; p.dk = (__bf16*)a.dk; p.dv = (__bf16*)a.dv; p.row_hi = a.row_hi; p.order = a.order_k;
-    static_assert(BNK == kOrderTile, "the tile order is made for this tile size");
-    p.S = a.S; p.Skv = a.Skv; p.off = a.off; p.S_pad = a.S_pad; p.Hq = a.Hq; p.Hkv = a.Hkv; p.G = a.Hq / a.Hkv;
-    p.qmap = a.qmap; p.kvmap = a.kvmap;
-    p.n_ktiles = (a.Skv + BNK - 1) / BNK;
-    p.nsplit = a.dkdv_splits; p.part = a.dkdv_part;
-    p.scale = a.scale; p.scale_log2 = a.scale * kLog2e;
-    if (p.nsplit < 1 || (p.nsplit > 1 && !p.part)) return SP_ERR_WORKSPACE;
-    p.B = a.B;
-    p.batch_fastest = a.B > 1 && (int64_t)p.n_ktiles * p.nsplit <= 65535 && (int64_t)a.Hkv * a.B <= 0x7fffffff;
-    dim3 grid(p.n_ktiles * p.nsplit, a.Hkv, a.B);
-    if (p.batch_fastest) grid = dim3(a.Hkv * a.B, p.n_ktiles * p.nsplit, 1);
-    if (p.nsplit > 1) hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, VARLEN, true>), grid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, VARLEN, false>), grid, dim3(kThreads), 0, st, p);
-    if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
-    if (p.nsplit > 1) {
-        const int64_t n_out = (int64_t)a.B * a.Skv * a.Hkv * D;
-        const int64_t blocks = (n_out / 4 + 255) / 256;
-        hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p.part, p.dk, p.dv, n_out,
-                           p.nsplit, p.scale, a.kvmap, a.Skv, a.Hkv * D);
-    }
-    return launch_status();
-}
-
-}  // namespace
-
-namespace sp {
-
-sp_status launch_attn_bwd_dkdv(const AttnArgs& a, hipStream_t st) {
-    if (a.Hkv > 65535 || a.B > 65535) return SP_ERR_SHAPE;
-    const bool varlen = a.row_lo != nullptr;
-    if (a.D == 128) return varlen ? launch<128, true>(a, st) : launch<128, false>(a, st);
-    if (a.D == 64) return varlen ? launch<64, true>(a, st) : launch<64, false>(a, st);
-    return SP_ERR_UNSUPPORTED;
-}
-
+}  // namespace dkdv
 }  // namespace sp

@@ -32,12 +32,15 @@
 // ahead (across bodies) with one exact partial wait per pair of slots, and the
 // body is instantiated once per ring position so that LDS addresses are
 // immediates.
+//
+// This file holds the workgroup's program; attn_bwd_matrix.h has the kernel that
+// runs it, beside the one of attn_bwd_dkdv.h.
+#pragma once
 #include "attn_common.h"
 #include "sp_common.h"
 
-namespace {
-
-using namespace sp;
+namespace sp {
+namespace dq {
 
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
@@ -54,26 +57,31 @@ struct DqParams {
     const int32_t* row_lo;
     const int32_t* order;  // packed documents: query tiles in the order workgroups take them (or null)
     RowMap qmap, kvmap;
-    int32_t S, Skv, off, Hq, Hkv, G, n_qtiles;  // S query rows, Skv keys; row i sees keys j <= i + off
+    int32_t B, S, Skv, off, Hq, Hkv, G, n_qtiles;  // S query rows, Skv keys; row i sees keys j <= i + off
     float scale, scale_log2;
 };
 
+template <int D>
+struct Lds {
+    static constexpr int TILE_B = BN * D * 2;
+    static constexpr int KS = 0, VS = NBUF * TILE_B, BYTES = 2 * NBUF * TILE_B;
+};
+
+// The work of workgroup `wg` of n_qtiles * Hq * B; smem holds Lds<D>::BYTES, 1 KB aligned.
 template <int D, bool VARLEN>
-__global__ __launch_bounds__(kThreads) void attn_bwd_dq_kernel(DqParams p) {
+__device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) {
     constexpr int NS = D / 16;   // operand slots per phase (contraction steps over the head dim)
     constexpr int NDB = D / 32;  // 32-wide blocks of the head dim
-    constexpr int TILE_B = BN * D * 2;
+    constexpr int TILE_B = Lds<D>::TILE_B, KS = Lds<D>::KS, VS = Lds<D>::VS;
     constexpr int HALF_B = 16 * D * 2;  // 16 rows of a tile
-    constexpr int KS = 0, VS = NBUF * TILE_B, SMEM = 2 * NBUF * TILE_B;
     static_assert(KS + (NBUF - 1) * TILE_B + HALF_B < 65536, "immediate LDS offsets must fit 16 bits");
-    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // heads vary fastest (they share K/V tiles), query tiles from the last (longest) to the first
-    const int h = blockIdx.x % p.Hq, b = blockIdx.x / p.Hq;
-    const int rank = (int)(blockIdx.y + kRankY * blockIdx.z);
-    if (rank >= p.n_qtiles) return;  // the last z-slice of a grid of more than kRankY tiles may be ragged
+    // heads vary fastest (they share K/V tiles), then batch entries; query tiles from the last (longest) to the first
+    const uint32_t n_heads = (uint32_t)p.Hq * (uint32_t)p.B;
+    const int head_id = (int)(wg % n_heads), rank = (int)(wg / n_heads);
+    const int h = head_id % p.Hq, b = head_id / p.Hq;
     int qt = p.n_qtiles - 1 - rank;
     if (VARLEN && p.order) {  // longest tile first; clamped so that a bad entry cannot become a wild address
         const int v = __builtin_amdgcn_readfirstlane(p.order[rank]);
@@ -469,31 +477,5 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_dq_kernel(DqParams p) {
     }
 }
 
-template <int D, bool VARLEN>
-sp_status launch(const AttnArgs& a, hipStream_t st) {
-    DqParams p;
-    p.q = (const __bf16*)a.q; p.k = (const __bf16*)a.k; p.v = (const __bf16*)a.v; p.dO = (const __bf16*)a.dO;
-    p.lse = a.lse; p.delta = a.delta; p.dq = (__bf16*)a.dq; p.row_lo = a.row_lo; p.order = a.order_q;
-    static_assert(BM == kOrderTile, "the tile order is made for this tile size");
-    p.S = a.S; p.Skv = a.Skv; p.off = a.off; p.Hq = a.Hq; p.Hkv = a.Hkv; p.G = a.Hq / a.Hkv;
-    p.qmap = a.qmap; p.kvmap = a.kvmap;
-    p.n_qtiles = (a.S + BM - 1) / BM;
-    p.scale = a.scale; p.scale_log2 = a.scale * kLog2e;
-    const dim3 grid = tile_rank_grid(a.Hq, a.B, p.n_qtiles);
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, VARLEN>), grid, dim3(kThreads), 0, st, p);
-    return launch_status();
-}
-
-}  // namespace
-
-namespace sp {
-
-sp_status launch_attn_bwd_dq(const AttnArgs& a, hipStream_t st) {
-    if ((int64_t)a.B * a.Hq > 0x7fffffff) return SP_ERR_SHAPE;
-    const bool varlen = a.row_lo != nullptr;
-    if (a.D == 128) return varlen ? launch<128, true>(a, st) : launch<128, false>(a, st);
-    if (a.D == 64) return varlen ? launch<64, true>(a, st) : launch<64, false>(a, st);
-    return SP_ERR_UNSUPPORTED;
-}
-
+}  // namespace dq
 }  // namespace sp

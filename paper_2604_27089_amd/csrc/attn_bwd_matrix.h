@@ -1,0 +1,125 @@
+// The kernel of the backward's two matrix stages, and its launcher.
+//
+// dK/dV (attn_bwd_dkdv.h) and dQ (attn_bwd_dq.h) read the same inputs and write different outputs, so one launch
+// holds the workgroups of both.  Either stage alone ends with compute units idle (each unit holds one workgroup,
+// and the longest walk of a stage is twice the mean or more), and a short problem fills the chip with neither.
+// Whole backward, one launch against one per stage (with equal kernels, 4 query heads, D = 128): 512 rows 71 -> 35
+// us, 4096 rows 218 -> 124, 8192 398 -> 267, 16384 890 -> 753, 32768 2.80 -> 2.77 ms, 16 x 4096 rows 857 -> 815 us.
+// Both programs keep a wave's whole register file, so sharing a kernel costs neither of them occupancy.
+#pragma once
+#include "attn_bwd_dkdv.h"
+#include "attn_bwd_dq.h"
+
+namespace {
+
+using namespace sp;
+
+struct MatrixParams {
+    dkdv::DkdvParams kv;
+    dq::DqParams q;
+    uint32_t base;         // first workgroup of this launch
+    // Order of dispatch: n_lead workgroups of one stage, then the remaining mix_kv and mix_q of the two in even
+    // alternation, each stage longest first.
+    uint32_t n_lead, mix_kv, mix_q;
+    bool lead_is_q;
+};
+
+template <int D, bool VARLEN, bool SPLIT>
+__global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixParams p) {
+    static_assert(dkdv::kThreads == dq::kThreads, "one block size");
+    constexpr int kLds = dkdv::Lds<D>::BYTES > dq::Lds<D>::BYTES ? dkdv::Lds<D>::BYTES : dq::Lds<D>::BYTES;
+    __shared__ __attribute__((aligned(1024))) char smem[kLds];
+    const uint32_t i = p.base + blockIdx.x;
+    bool is_q = p.lead_is_q;
+    uint32_t wg = i;
+    if (i >= p.n_lead) {
+        const uint32_t r = i - p.n_lead;
+        uint32_t q_before = 0;  // dQ workgroups among the first r of the alternation
+        if (p.mix_kv == 0) { is_q = true; q_before = r; }
+        else if (p.mix_q == 0) is_q = false;
+        else {  // short launches only: the products fit 32 bits
+            q_before = r * p.mix_q / (p.mix_kv + p.mix_q);
+            is_q = (r + 1) * p.mix_q / (p.mix_kv + p.mix_q) > q_before;
+        }
+        wg = is_q ? q_before : r - q_before;
+        if (is_q == p.lead_is_q) wg += p.n_lead;
+    }
+    if (is_q) dq::run<D, VARLEN>(p.q, wg, smem);
+    else dkdv::run<D, VARLEN, SPLIT>(p.kv, wg, smem);
+}
+
+// In which order the workgroups of the two stages go out (speed only: every order gives the same bits).  Each stage
+// hands out its longest walks first; the longest of each, in us, is about 0.95 per 32-key step of dQ and 1.5 per
+// 32-row step of dK/dV beyond fixed costs.
+//   Up to three rounds of the chip (768 workgroups; five with packed documents, whose work is uneven): the two are
+// merged by expected length, i.e. the stage with the longer walks leads until its remaining ones are as long as
+// the other's, and from there they alternate.  Measured against dK/dV first / dQ first, us: 8192 rows of 5 heads,
+// full attention, 335 against 343 / 361, 16384 rows, 4 heads, 797 against 899 / 799, packed documents of 32768 rows
+// at D = 64 (longest 12877) 448 against 572 / 506.
+//   Beyond that whole stages follow each other: alternating mixes two access patterns that each share their stream
+// through L2 (131072 rows 47.0 ms against 41.9; 16384 rows of 8 heads 1572 us against 1490).  dQ first, since the
+// chunks of dK/dV are the finer ones to fill the end with, unless few long documents stand out so far that their
+// dK/dV walk would outlast all the rest (65536 rows in documents of 512, longest 4364: 497 us with dK/dV first, 625
+// with dQ first).
+inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixParams& p) {
+    const int64_t longest = a.longest > 0 && a.longest < a.S ? a.longest : a.S;
+    const double steps = (double)((longest + 31) / 32);
+    const double t_q = 0.95 * steps + 10., t_kv = 1.5 * steps * (a.Hq / a.Hkv) / a.dkdv_splits + 20.;
+    bool lead_q;
+    int64_t lead;
+    if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
+        lead_q = t_q >= t_kv;
+        lead = (int64_t)(lead_q ? n_q * (1. - t_kv / t_q) : n_kv * (1. - t_q / t_kv));
+    } else {
+        const int64_t mean = a.S / (a.n_docs > 0 ? a.n_docs : 1);
+        lead_q = n_kv * mean >= 256 * longest;
+        lead = lead_q ? n_q : n_kv;
+    }
+    p.lead_is_q = lead_q;
+    p.n_lead = (uint32_t)lead;
+    p.mix_q = (uint32_t)(lead_q ? n_q - lead : n_q);
+    p.mix_kv = (uint32_t)(lead_q ? n_kv : n_kv - lead);
+}
+
+template <int D, bool VARLEN>
+sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
+    MatrixParams p{};
+    const bool kv = (a.stages & SP_BWD_STAGE_DKDV) != 0, qs = (a.stages & SP_BWD_STAGE_DQ) != 0;
+    static_assert(dkdv::BNK == kOrderTile && dq::BM == kOrderTile, "the tile orders are made for this tile size");
+    {
+        dkdv::DkdvParams& k = p.kv;
+        k.q = (const __bf16*)a.q; k.k = (const __bf16*)a.k; k.v = (const __bf16*)a.v; k.dO = (const __bf16*)a.dO;
+        k.aux = a.aux; k.dk = (__bf16*)a.dk; k.dv = (__bf16*)a.dv; k.row_hi = a.row_hi; k.order = a.order_k;
+        k.S = a.S; k.Skv = a.Skv; k.off = a.off; k.S_pad = a.S_pad; k.Hq = a.Hq; k.Hkv = a.Hkv; k.G = a.Hq / a.Hkv;
+        k.qmap = a.qmap; k.kvmap = a.kvmap;
+        k.n_ktiles = (a.Skv + dkdv::BNK - 1) / dkdv::BNK;
+        k.nsplit = a.dkdv_splits; k.part = a.dkdv_part;
+        k.scale = a.scale; k.scale_log2 = a.scale * kLog2e;
+        k.B = a.B; k.several = a.B > 1;
+        if (kv && (k.nsplit < 1 || (k.nsplit > 1 && !k.part))) return SP_ERR_WORKSPACE;
+    }
+    {
+        dq::DqParams& q = p.q;
+        q.q = (const __bf16*)a.q; q.k = (const __bf16*)a.k; q.v = (const __bf16*)a.v; q.dO = (const __bf16*)a.dO;
+        q.lse = a.lse; q.delta = a.delta; q.dq = (__bf16*)a.dq; q.row_lo = a.row_lo; q.order = a.order_q;
+        q.B = a.B; q.S = a.S; q.Skv = a.Skv; q.off = a.off; q.Hq = a.Hq; q.Hkv = a.Hkv; q.G = a.Hq / a.Hkv;
+        q.qmap = a.qmap; q.kvmap = a.kvmap;
+        q.n_qtiles = (a.S + dq::BM - 1) / dq::BM;
+        q.scale = a.scale; q.scale_log2 = a.scale * kLog2e;
+    }
+    const int64_t n_kv = kv ? (int64_t)p.kv.n_ktiles * p.kv.nsplit * a.Hkv * a.B : 0;
+    const int64_t n_q = qs ? (int64_t)p.q.n_qtiles * a.Hq * a.B : 0;
+    if (n_kv + n_q > 0x7fffffff) return SP_ERR_SHAPE;
+    dispatch_order(a, n_kv, n_q, p);
+    constexpr int64_t kMaxGrid = 1 << 23;  // workgroups per launch (a grid holds fewer than 2^32 threads)
+    for (int64_t base = 0; base < n_kv + n_q; base += kMaxGrid) {
+        const int64_t n = n_kv + n_q - base < kMaxGrid ? n_kv + n_q - base : kMaxGrid;
+        p.base = (uint32_t)base;
+        if (p.kv.nsplit > 1) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, true>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p);
+        else hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, false>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p);
+        if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
+    }
+    return SP_OK;
+}
+
+}  // namespace

@@ -383,6 +383,7 @@ sp_status sp_attn_varlen_bwd(const void* q, const void* k, const void* v, const 
     attention_side_maps(a);
     a.scale = resolve_scale(softmax_scale, D);
     a.stages = SP_BWD_STAGE_ALL;
+    a.n_docs = n_docs; a.longest = max_seqlen;
     a.dkdv_splits = sp::dkdv_split_count(1, T, T, Hq, Hkv, max_seqlen);  // the hint only shapes the work split
     a.dkdv_part = a.dkdv_splits > 1 ? (float*)((char*)row_hi + bounds_bytes(T) + order_bytes(T)) : nullptr;
     return sp::launch_attn_bwd(a, s);

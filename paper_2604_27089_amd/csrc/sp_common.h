@@ -59,6 +59,8 @@ struct AttnArgs {
     RowMap qmap, kvmap;     // layout of q, o, dO, dq and of k, v, dk, dv
     float scale;            // softmax scale (already defaulted)
     int32_t stages;         // bwd: bit mask of SP_BWD_STAGE_*
+    int32_t n_docs;         // varlen: number of documents (else 0)
+    int32_t longest;        // bwd: upper bound of the longest document, when the caller knows one (else 0)
     int32_t dkdv_splits;    // bwd: workgroups that share one key tile of the dK/dV kernel (dkdv_split_count)
     float* dkdv_part;       // bwd workspace: their fp32 partial sums (null when dkdv_splits == 1)
 };
@@ -101,8 +103,8 @@ inline int fwd_key_groups(int64_t B, int64_t S, int32_t Hq) {
 }
 sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd(const AttnArgs& a, hipStream_t st);
-sp_status launch_attn_bwd_dkdv(const AttnArgs& a, hipStream_t st);
-sp_status launch_attn_bwd_dq(const AttnArgs& a, hipStream_t st);
+sp_status launch_attn_bwd_matrix_d64(const AttnArgs& a, hipStream_t st);
+sp_status launch_attn_bwd_matrix_d128(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_merge(float* o_acc, float* lse_acc, const void* o_blk, const float* lse_blk, void* o_out,
                             int64_t B, int64_t S, int32_t Hq, int32_t D, hipStream_t st);
 

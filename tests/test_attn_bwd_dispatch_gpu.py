@@ -1,0 +1,59 @@
+"""The backward's two matrix stages in one launch: whatever order the workgroups go out in, every one runs.  Heads are
+copies of each other, so a workgroup left out or run twice shows as a head that differs; one head is held to the
+oracle.  Sizes put the launch into every class of the order: alternation with either stage in front, dQ first and
+dK/dV first, and single stages."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref_numpy as rn
+from paper_2604_27089_amd import binding as sp
+from paper_2604_27089_amd import synth
+from gpu_util import GRAD_REL_L2, dev_bf16, grad_err, host_f64
+
+pytestmark = pytest.mark.gpu
+
+
+def same_heads(t):
+    return torch.equal(t.view(torch.int16), t[..., :1, :].expand_as(t).contiguous().view(torch.int16))
+
+
+# (rows, copies of one query and one key/value head): up to 768 workgroups alternate, above that dQ goes first
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,heads", [(40, 1), (300, 3), (300, 191), (300, 260), (1100, 90)])
+def test_full_attention(S, heads, D):
+    bits = synth.attn_inputs(S + heads, S, 1, 1, D)
+    q, k, v, do = (dev_bf16(t).expand(-1, -1, heads, -1).contiguous() for t in bits)
+    o, lse = sp.sp_attn_fwd(q, k, v)
+    ws = torch.empty(sp.sp_attn_bwd_workspace_bytes(1, S, heads, heads, D), dtype=torch.uint8, device="cuda")
+    dq, dk, dv = sp.sp_attn_bwd(q, k, v, o, lse, do, workspace=ws)
+    assert same_heads(dq) and same_heads(dk) and same_heads(dv)
+    refs = rn.attn_bwd(*(rn.widen_bf16(t[0]) for t in bits), 0.0)[:3]
+    for got, ref, name in zip((dq, dk, dv), refs, ("dq", "dk", "dv")):
+        assert grad_err(host_f64(got[0, :, :1]), ref, name) <= GRAD_REL_L2
+    # the stages one at a time give the same bits, and a stage writes its own outputs only
+    parts = [torch.full_like(t, 7.0) for t in (dq, dk, dv)]
+    for stage in (sp.SP_BWD_STAGE_DELTA, sp.SP_BWD_STAGE_DQ, sp.SP_BWD_STAGE_DKDV):
+        sp.sp_attn_bwd_stages(q, k, v, o, lse, do, *parts, ws, stage)
+        if stage != sp.SP_BWD_STAGE_DKDV:
+            assert bool((parts[1] == 7.0).all()) and bool((parts[2] == 7.0).all())
+            assert bool((parts[0] == 7.0).all()) == (stage == sp.SP_BWD_STAGE_DELTA)
+    for a, b in zip(parts, (dq, dk, dv)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+# packed documents: alternation up to 1280 workgroups; above, dK/dV first when one document stands out (a long
+# document among many short ones), else dQ first
+@pytest.mark.parametrize("lengths,heads", [([70, 1, 200], 4), ([763], 240), ([600] + [3] * 60, 240), ([90] * 8, 260)])
+def test_packed_documents(lengths, heads):
+    D, T = 64, sum(lengths)
+    cu_h = synth.cu_seqlens_from_lengths(lengths)
+    cu = torch.from_numpy(cu_h).cuda()
+    bits = synth.attn_inputs(T + heads, T, 1, 1, D)
+    q, k, v, do = (dev_bf16(t[0]).expand(-1, heads, -1).contiguous() for t in bits)
+    o, lse = sp.sp_attn_varlen_fwd(q, k, v, cu, max(lengths))
+    grads = sp.sp_attn_varlen_bwd(q, k, v, o, lse, do, cu, max(lengths))
+    assert all(same_heads(t) for t in grads)
+    refs = rn.attn_varlen_bwd(*(rn.widen_bf16(t[0]) for t in bits), cu_h)[:3]
+    for got, ref, name in zip(grads, refs, ("dq", "dk", "dv")):
+        assert grad_err(host_f64(got[:, :1]), ref, name) <= GRAD_REL_L2
