@@ -58,26 +58,49 @@ __global__ __launch_bounds__(256) void delta_kernel(const __bf16* __restrict__ o
     }
 }
 
-// dK = scale * sum of the chunks' partial sums, dV = sum of theirs; four elements per thread.  The
-// partial sums are dense [B, S, Hkv*D]; the outputs follow `map`.
+// dK = scale * sum of the chunks' partial sums, dV = sum of theirs.  The sums of one chunk, batch entry and KV head
+// are Skv * D floats in groups of four keys, [key / 4][column][key % 4] (the last group may hold fewer keys); the
+// outputs follow `map`.  A thread takes four keys of two columns.
+template <int D>
 __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restrict__ part, __bf16* __restrict__ dk,
-                                                         __bf16* __restrict__ dv, int64_t n_out, int32_t nsplit,
-                                                         float scale, RowMap map, int32_t S, int32_t HD) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n_out) return;  // n_out is a multiple of 4 (D is)
-    const int64_t br = i / HD;  // b*S + row
-    const int64_t bb = br / S;
-    const size_t o = (size_t)bb * S * HD + map.off((int32_t)(br - bb * S)) + (size_t)(i - br * HD);
-    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    for (int32_t s = 0; s < nsplit; ++s) {
-        sk += *reinterpret_cast<const f32x4*>(part + (size_t)s * n_out + i);
-        sv += *reinterpret_cast<const f32x4*>(part + ((size_t)nsplit + s) * n_out + i);
+                                                         __bf16* __restrict__ dv, int32_t groups, int64_t n_items,
+                                                         int32_t nsplit, float scale, RowMap map, int32_t Skv, int32_t Hkv) {
+    constexpr int CP = D / 2;  // column pairs
+    const int64_t item = (int64_t)blockIdx.x * (256 / CP) + threadIdx.x / CP;  // (b*Hkv + g) * groups + key group
+    if (item >= n_items) return;
+    const int c = (int)(threadIdx.x % CP) * 2;
+    const int64_t bg = item / groups, b = bg / Hkv;
+    const int g = (int)(bg - b * Hkv), k0 = (int)(item - bg * groups) * 4;
+    const size_t chunk = (size_t)(n_items / groups) * Skv * D;  // floats of one chunk of the whole call
+    const int n = Skv - k0 < 4 ? Skv - k0 : 4;
+    const float* src = part + (size_t)bg * Skv * D + (size_t)k0 * D + (size_t)n * c;
+    float sk[2][4] = {}, sv[2][4] = {};
+    if (n == 4) {
+        for (int32_t s = 0; s < nsplit; ++s) {
+            const f32x4 k0v = *reinterpret_cast<const f32x4*>(src + (size_t)s * chunk);
+            const f32x4 k1v = *reinterpret_cast<const f32x4*>(src + (size_t)s * chunk + 4);
+            const f32x4 v0v = *reinterpret_cast<const f32x4*>(src + ((size_t)nsplit + s) * chunk);
+            const f32x4 v1v = *reinterpret_cast<const f32x4*>(src + ((size_t)nsplit + s) * chunk + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { sk[0][e] += k0v[e]; sk[1][e] += k1v[e]; sv[0][e] += v0v[e]; sv[1][e] += v1v[e]; }
+        }
+    } else {
+        for (int32_t s = 0; s < nsplit; ++s)
+            for (int x = 0; x < 2; ++x)
+                for (int e = 0; e < 3; ++e)
+                    if (e < n) {
+                        sk[x][e] += src[(size_t)s * chunk + x * n + e];
+                        sv[x][e] += src[((size_t)nsplit + s) * chunk + x * n + e];
+                    }
     }
-    u32x2 wk, wv;
-    wk[0] = pack_bf16(sk[0] * scale, sk[1] * scale); wk[1] = pack_bf16(sk[2] * scale, sk[3] * scale);
-    wv[0] = pack_bf16(sv[0], sv[1]); wv[1] = pack_bf16(sv[2], sv[3]);
-    *reinterpret_cast<u32x2*>(dk + o) = wk;
-    *reinterpret_cast<u32x2*>(dv + o) = wv;
+    const size_t base = ((size_t)b * Skv * Hkv + g) * D + c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e < n) {
+            const size_t o = base + map.off(k0 + e);
+            *reinterpret_cast<uint32_t*>(dk + o) = pack_bf16(sk[0][e] * scale, sk[1][e] * scale);
+            *reinterpret_cast<uint32_t*>(dv + o) = pack_bf16(sv[0][e], sv[1][e]);
+        }
 }
 
 template <int D>
@@ -96,10 +119,12 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
         if (r != SP_OK) return r;
     }
     if ((a.stages & SP_BWD_STAGE_DKDV) && a.dkdv_splits > 1) {
-        const int64_t n_out = (int64_t)a.B * a.Skv * a.Hkv * D;
-        const int64_t blocks = (n_out / 4 + 255) / 256;
-        hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a.dkdv_part, (__bf16*)a.dk,
-                           (__bf16*)a.dv, n_out, a.dkdv_splits, a.scale, a.kvmap, a.Skv, a.Hkv * D);
+        const int32_t groups = (a.Skv + 3) / 4;
+        const int64_t items = (int64_t)a.B * a.Hkv * groups, per_block = 256 / (D / 2);
+        if ((items + per_block - 1) / per_block > 0x7fffffff) return SP_ERR_SHAPE;
+        hipLaunchKernelGGL((dkdv_reduce_kernel<D>), dim3((unsigned)((items + per_block - 1) / per_block)), dim3(256), 0, st,
+                           a.dkdv_part, (__bf16*)a.dk, (__bf16*)a.dv, groups, items, a.dkdv_splits, a.scale, a.kvmap,
+                           a.Skv, a.Hkv);
         if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
     }
     return SP_OK;
