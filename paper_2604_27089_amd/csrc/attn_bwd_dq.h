@@ -10,13 +10,14 @@
 // Section 4.1); the plain causal call is Skv = S, off = 0.
 //
 // One workgroup = 4 waves = 256 query rows of one query head, one wave per SIMD;
-// a wave owns 64 rows (two 32-row blocks): their Q and dO stay resident as MFMA
+// a wave owns 64 rows (NQ = two 32-row blocks; one in launches of few tiles, see
+// dq_row_blocks()): their Q and dO stay resident as MFMA
 // B operands (in accumulation registers), their dQ lives in accumulation
 // registers that only MFMAs touch, and -LSE/scale and -Delta of the lane's row
 // sit in register tiles that seed the S and dP accumulators through the MFMA C
 // operand.  K/V stream through rings of eight 32-key LDS tiles (direct
 // global->LDS loads issued six steps ahead, XOR-swizzled); every operand
-// fetched from LDS feeds two MFMAs, one per row block.  Per 32-key step u:
+// fetched from LDS feeds NQ MFMAs, one per row block.  Per 32-key step u:
 //   S'^T = K.Q^T - LSE/scale, dP'^T = V.dO^T - Delta   (keys on the register axis,
 //        one query per lane)
 //   P = exp2(S' * scale*log2e), dS = P * dP'            (fp32 vector ALU, then bf16)
@@ -25,10 +26,10 @@
 //
 // A lone wave issues in order, so the vector-ALU work is interleaved by hand
 // into the MFMA stream.  One loop body runs three phases of D/16 operand slots
-// (two MFMAs per slot):
+// (an MFMA per row block in each):
 //   S(u) + the loads of step u+6 | dP(u) + exponentials | dQ(u-1) + dS products
 // i.e. the dQ contraction of a step is deferred into the next body.  The body is
-// straight-line code: LDS operand reads are asynchronous, issued four slots
+// straight-line code: LDS operand reads are asynchronous, issued eight MFMAs
 // ahead (across bodies) with one exact partial wait per pair of slots, and the
 // body is instantiated once per ring position so that LDS addresses are
 // immediates.
@@ -44,8 +45,8 @@ namespace dq {
 
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
-constexpr int RPW = 64;           // query rows per wave
-constexpr int BM = RPW * kWaves;  // query rows per workgroup
+template <int NQ> constexpr int kRowsPerWave = 32 * NQ;      // NQ = 1 or 2 row blocks per wave
+template <int NQ> constexpr int kRows = 32 * NQ * kWaves;    // query rows per workgroup
 constexpr int BN = 32;            // keys per streamed tile = one step
 constexpr int NBUF = 8;           // ring of streamed tiles (K and V each)
 constexpr int LEAD = 6;           // a tile is loaded this many steps before its step
@@ -57,7 +58,7 @@ struct DqParams {
     const int32_t* row_lo;
     const int32_t* order;  // packed documents: query tiles in the order workgroups take them (or null)
     RowMap qmap, kvmap;
-    int32_t B, S, Skv, off, Hq, Hkv, G, n_qtiles;  // S query rows, Skv keys; row i sees keys j <= i + off
+    int32_t B, S, Skv, off, Hq, Hkv, G, n_qtiles, n_ranks;  // S query rows, Skv keys; row i sees keys j <= i + off
     float scale, scale_log2;
 };
 
@@ -67,9 +68,10 @@ struct Lds {
     static constexpr int KS = 0, VS = NBUF * TILE_B, BYTES = 2 * NBUF * TILE_B;
 };
 
-// The work of workgroup `wg` of n_qtiles * Hq * B; smem holds Lds<D>::BYTES, 1 KB aligned.
-template <int D, bool VARLEN>
+// The work of workgroup `wg` of n_ranks * Hq * B; smem holds Lds<D>::BYTES, 1 KB aligned.
+template <int D, bool VARLEN, int NQ>
 __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) {
+    constexpr int RPW = kRowsPerWave<NQ>, BM = kRows<NQ>;
     constexpr int NS = D / 16;   // operand slots per phase (contraction steps over the head dim)
     constexpr int NDB = D / 32;  // 32-wide blocks of the head dim
     constexpr int TILE_B = Lds<D>::TILE_B, KS = Lds<D>::KS, VS = Lds<D>::VS;
@@ -83,8 +85,12 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     const int head_id = (int)(wg % n_heads), rank = (int)(wg / n_heads);
     const int h = head_id % p.Hq, b = head_id / p.Hq;
     int qt = p.n_qtiles - 1 - rank;
-    if (VARLEN && p.order) {  // longest tile first; clamped so that a bad entry cannot become a wild address
-        const int v = __builtin_amdgcn_readfirstlane(p.order[rank]);
+    if (VARLEN && p.order) {
+        // longest 256-row tile first, its parts from the last; the value is clamped so that a bad entry cannot
+        // become a wild address (a part past the last row has nothing to do)
+        constexpr int SUB = kOrderTile / BM;
+        const int v = __builtin_amdgcn_readfirstlane(p.order[rank / SUB]) * SUB + (SUB - 1 - rank % SUB);
+        if (SUB > 1 && v >= p.n_qtiles) return;
         qt = v < 0 ? 0 : (v < p.n_qtiles ? v : p.n_qtiles - 1);
     }
     const int g = h / p.G;
@@ -96,10 +102,10 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     const int wrow0 = i0 + RPW * wave;  // first row of this wave
 
     // resident B operands (Q^T, dO^T columns of this lane's two rows) and accumulator seeds
-    bf16x8 qreg[2][NS], doreg[2][NS];
-    f32x16 seed_s[2], seed_p[2];
+    bf16x8 qreg[NQ][NS], doreg[NQ][NS];
+    f32x16 seed_s[NQ], seed_p[NQ];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
         const int row = wrow0 + 32 * qb + lo;
         const int rc = row < S ? row : S - 1;
 #pragma unroll
@@ -118,15 +124,16 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         wave_lo_max = __builtin_amdgcn_readfirstlane(p.row_lo[(wrow0 + RPW - 1 < S ? wrow0 + RPW - 1 : S - 1)]);
         wg_lo_min = __builtin_amdgcn_readfirstlane(p.row_lo[i0]);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < NQ; ++qb) {
             const int row = wrow0 + 32 * qb + lo;
             rlo_l[qb] = p.row_lo[row < S ? row : S - 1];
         }
+        if constexpr (NQ == 1) rlo_l[1] = rlo_l[0];
     }
 
-    f32x16 dqacc[2][NDB];
+    f32x16 dqacc[NQ][NDB];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -231,12 +238,12 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         });
     }
 
-    f32x16 sacc[2], pacc[2];
-    u32x4 dsp[2][2][2];  // bf16 B operands [parity of the step][row block][16-key half]
+    f32x16 sacc[NQ], pacc[NQ];
+    u32x4 dsp[2][NQ][2];  // bf16 B operands [parity of the step][row block][16-key half]
 #pragma unroll
     for (int par = 0; par < 2; ++par)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
             for (int c = 0; c < 2; ++c) dsp[par][qb][c] = u32x4{0, 0, 0, 0};
 
@@ -244,7 +251,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     // kAhead slots early (behind the first MFMA of the issuing slot), possibly from the previous body (slots
     // x >= 3*NS name slots of the next body).  Waits happen once per pair of slots, at the even one.
     constexpr int P3 = 3 * NS;
-    constexpr int kAhead = 4;
+    constexpr int kAhead = NQ == 2 ? 4 : 8;  // eight MFMAs
     auto nreads = [](int x) constexpr { return (x % P3) < 2 * NS ? 1 : 2; };
     // reads issued after those of slot s+1 by the time (even) slot s waits, which is before slot s issues
     // its own (none for the next body if `last`)
@@ -281,8 +288,8 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         constexpr int BUF = decltype(BUFC)::value, DBUF = (BUF + LEAD) % NBUF, PAR = BUF % 2;
         constexpr bool FIRST = decltype(FIRSTC)::value, LAST = decltype(LASTC)::value;
         using NextBuf = std::integral_constant<int, (BUF + 1) % NBUF>;
-        constexpr int EPM = 32 / (2 * NS);  // exponentials per MFMA in the dP phase
-        constexpr int PPM = 16 / (2 * NS);  // dS pairs per MFMA in the dQ phase
+        constexpr int EPM = 16 / NS;  // exponentials per MFMA in the dP phase (16 * NQ behind NS * NQ MFMAs)
+        constexpr int PPM = 8 / NS;   // dS pairs per MFMA in the dQ phase
 
         // exponentials of accumulator elements m*EPM .. of the step (element i = row block i/16, register
         // i%16); P stays in the S' registers
@@ -336,8 +343,10 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                 // its second MFMA, where the compiler would otherwise put a wait state)
                 if constexpr (s == GROUP) advance_load();
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (s == 0) mfma_vc_ab<-1>(sacc[1], ak[s], qreg[1][s], seed_s[1]);
-                else mfma_v_ab<-1>(sacc[1], ak[s], qreg[1][s]);
+                if constexpr (NQ == 2) {
+                    if constexpr (s == 0) mfma_vc_ab<-1>(sacc[1], ak[s], qreg[1][s], seed_s[1]);
+                    else mfma_v_ab<-1>(sacc[1], ak[s], qreg[1][s]);
+                }
             } else if constexpr (s < 2 * NS) {
                 // ---- dP(u), exponentials ----
                 // Exponential chunk m runs behind MFMA m+1 of the phase (the last one behind the first MFMA
@@ -348,12 +357,14 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                 else mfma_v_ab<W>(pacc[0], av[kk], doreg[0][kk]);
                 __builtin_amdgcn_sched_barrier(0);
                 issue_slot();
-                if constexpr (kk > 0) exp_chunk(std::integral_constant<int, 2 * kk - 1>{});
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (kk == 0) mfma_vc_ab<-1>(pacc[1], av[kk], doreg[1][kk], seed_p[1]);
-                else mfma_v_ab<-1>(pacc[1], av[kk], doreg[1][kk]);
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (kk == 0) {
+                if constexpr (NQ == 2) {
+                    if constexpr (kk > 0) exp_chunk(std::integral_constant<int, 2 * kk - 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (kk == 0) mfma_vc_ab<-1>(pacc[1], av[kk], doreg[1][kk], seed_p[1]);
+                    else mfma_v_ab<-1>(pacc[1], av[kk], doreg[1][kk]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (kk == 2 - NQ) {  // behind the second MFMA of the phase
                     // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  The element of register r
                     // is key j0 + 4*hi + c_r with c_r = 8*(r/4) + r%4 known at compile time, so "hidden" is one
                     // compare of c_r with a per-lane limit and one select.  A step none of whose keys the wave
@@ -370,11 +381,13 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                         if (step_no >= dead_from) {
                             asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) { sacc[0][r] = -__builtin_inff(); sacc[1][r] = -__builtin_inff(); }
+                            for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) sacc[qb][r] = -__builtin_inff();
                         } else {
                             asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
 #pragma unroll
-                            for (int qb = 0; qb < 2; ++qb) {
+                            for (int qb = 0; qb < NQ; ++qb) {
                                 const int row = wrow0 + 32 * qb + (int)(__lane_id() & 31);
                                 const int rhi = row + p.off < p.Skv - 1 ? row + p.off : p.Skv - 1;  // last key it may see
                                 const int lim = rhi - cur_jt * BN - 4 * (int)(__lane_id() >> 5);
@@ -390,7 +403,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                         if (inside) {
                             asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                            for (int qb = 0; qb < 2; ++qb) {
+                            for (int qb = 0; qb < NQ; ++qb) {
                                 const int lim = rlo_l[qb] - j0 - 4 * (int)(__lane_id() >> 5);
 #pragma unroll
                                 for (int r = 0; r < 16; ++r) sacc[qb][r] = 8 * (r / 4) + r % 4 >= lim ? sacc[qb][r] : -__builtin_inff();
@@ -402,13 +415,14 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
 #pragma unroll
                                 for (int r = 0; r < 16; ++r) {
                                     sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
-                                    sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
+                                    if constexpr (NQ == 2) sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
                                 }
                             }
                         }
                     }
                 }
-                exp_chunk(std::integral_constant<int, 2 * kk>{});
+                if constexpr (NQ == 2) exp_chunk(std::integral_constant<int, 2 * kk>{});
+                else if constexpr (kk > 0) exp_chunk(std::integral_constant<int, kk - 1>{});
             } else {
                 // ---- dQ(u-1), dS products of step u (pair chunk m behind MFMA m+1, as above) ----
                 constexpr int t = s - 2 * NS, c = t / NDB, db = t % NDB;
@@ -416,13 +430,16 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                 mfma_a_w<W>(dqacc[0][db], kt, dsp[1 - PAR][0][c]);
                 __builtin_amdgcn_sched_barrier(0);
                 issue_slot();
-                if constexpr (t == 0) exp_chunk(std::integral_constant<int, 2 * NS - 1>{});
-                else static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (2 * t - 1) * PPM + decltype(J)::value>{}); });
-                __builtin_amdgcn_sched_barrier(0);
-                mfma_a(dqacc[1][db], kt, dsp[1 - PAR][1][c]);
-                __builtin_amdgcn_sched_barrier(0);
-                static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (2 * t) * PPM + decltype(J)::value>{}); });
-                if constexpr (t == NS - 1) static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (2 * t + 1) * PPM + decltype(J)::value>{}); });
+                constexpr int m = NQ * t;  // this slot's first MFMA of the phase
+                if constexpr (t == 0) exp_chunk(std::integral_constant<int, NQ * NS - 1>{});
+                else static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (m - 1) * PPM + decltype(J)::value>{}); });
+                if constexpr (NQ == 2) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_a(dqacc[1][db], kt, dsp[1 - PAR][1][c]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, m * PPM + decltype(J)::value>{}); });
+                }
+                if constexpr (t == NS - 1) static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (NQ * NS - 1) * PPM + decltype(J)::value>{}); });
             }
         });
         __builtin_amdgcn_sched_barrier(0);
@@ -453,14 +470,14 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
             lds_wait<0>(h0, h1);
             const u32x4 kt = {h0[0], h0[1], h1[0], h1[1]};
             dqacc[0][db] = mfma32(as_bf16x8(kt), as_bf16x8(dsp[1][0][c]), dqacc[0][db]);
-            dqacc[1][db] = mfma32(as_bf16x8(kt), as_bf16x8(dsp[1][1][c]), dqacc[1][db]);
+            if constexpr (NQ == 2) dqacc[1][db] = mfma32(as_bf16x8(kt), as_bf16x8(dsp[1][1][c]), dqacc[1][db]);
         });
     }
     wait_vmem();  // no direct-to-LDS load may outlive the workgroup's LDS allocation
 
     // ---- write dQ (scaled): accumulator rows = d, column = this lane's query ----
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
         const int row = wrow0 + 32 * qb + lo;
         if (row < S) {
             __bf16* out = p.dq + ((size_t)b * S * p.Hq + h) * D + p.qmap.off(row);

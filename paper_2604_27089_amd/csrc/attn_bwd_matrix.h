@@ -24,7 +24,7 @@ struct MatrixParams {
     bool lead_is_q;
 };
 
-template <int D, bool VARLEN, bool SPLIT>
+template <int D, bool VARLEN, bool SPLIT, int NQ>
 __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixParams p) {
     static_assert(dkdv::kThreads == dq::kThreads, "one block size");
     constexpr int kLds = dkdv::Lds<D>::BYTES > dq::Lds<D>::BYTES ? dkdv::Lds<D>::BYTES : dq::Lds<D>::BYTES;
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
         wg = is_q ? q_before : r - q_before;
         if (is_q == p.lead_is_q) wg += p.n_lead;
     }
-    if (is_q) dq::run<D, VARLEN>(p.q, wg, smem);
+    if (is_q) dq::run<D, VARLEN, NQ>(p.q, wg, smem);
     else dkdv::run<D, VARLEN, SPLIT>(p.kv, wg, smem);
 }
 
@@ -84,8 +84,9 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
 template <int D, bool VARLEN>
 sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
     MatrixParams p{};
+    int nq;  // row blocks of a dQ wave
     const bool kv = (a.stages & SP_BWD_STAGE_DKDV) != 0, qs = (a.stages & SP_BWD_STAGE_DQ) != 0;
-    static_assert(dkdv::BNK == kOrderTile && dq::BM == kOrderTile, "the tile orders are made for this tile size");
+    static_assert(dkdv::BNK == kOrderTile && dq::kRows<2> == kOrderTile, "the tile orders are made for this tile size");
     {
         dkdv::DkdvParams& k = p.kv;
         k.q = (const __bf16*)a.q; k.k = (const __bf16*)a.k; k.v = (const __bf16*)a.v; k.dO = (const __bf16*)a.dO;
@@ -104,19 +105,24 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
         q.lse = a.lse; q.delta = a.delta; q.dq = (__bf16*)a.dq; q.row_lo = a.row_lo; q.order = a.order_q;
         q.B = a.B; q.S = a.S; q.Skv = a.Skv; q.off = a.off; q.Hq = a.Hq; q.Hkv = a.Hkv; q.G = a.Hq / a.Hkv;
         q.qmap = a.qmap; q.kvmap = a.kvmap;
-        q.n_qtiles = (a.S + dq::BM - 1) / dq::BM;
+        nq = dq_row_blocks(a.B, a.S, a.Hq);
+        const int rows = nq == 1 ? dq::kRows<1> : dq::kRows<2>;
+        q.n_qtiles = (a.S + rows - 1) / rows;
+        q.n_ranks = VARLEN && q.order ? order_tiles(a.S) * (kOrderTile / rows) : q.n_qtiles;
         q.scale = a.scale; q.scale_log2 = a.scale * kLog2e;
     }
     const int64_t n_kv = kv ? (int64_t)p.kv.n_ktiles * p.kv.nsplit * a.Hkv * a.B : 0;
-    const int64_t n_q = qs ? (int64_t)p.q.n_qtiles * a.Hq * a.B : 0;
+    const int64_t n_q = qs ? (int64_t)p.q.n_ranks * a.Hq * a.B : 0;
     if (n_kv + n_q > 0x7fffffff) return SP_ERR_SHAPE;
     dispatch_order(a, n_kv, n_q, p);
     constexpr int64_t kMaxGrid = 1 << 23;  // workgroups per launch (a grid holds fewer than 2^32 threads)
     for (int64_t base = 0; base < n_kv + n_q; base += kMaxGrid) {
         const int64_t n = n_kv + n_q - base < kMaxGrid ? n_kv + n_q - base : kMaxGrid;
         p.base = (uint32_t)base;
-        if (p.kv.nsplit > 1) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, true>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p);
-        else hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, false>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p);
+#define SP_MATRIX(SPLIT, NQ) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, SPLIT, NQ>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p)
+        if (p.kv.nsplit > 1) { if (nq == 1) SP_MATRIX(true, 1); else SP_MATRIX(true, 2); }
+        else { if (nq == 1) SP_MATRIX(false, 1); else SP_MATRIX(false, 2); }
+#undef SP_MATRIX
         if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
     }
     return SP_OK;

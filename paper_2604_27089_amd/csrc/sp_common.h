@@ -102,6 +102,15 @@ inline int fwd_key_groups(int64_t B, int64_t S, int32_t Hq) {
     return tiles <= 128 ? 4 : tiles <= 384 ? 2 : 1;
 }
 sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
+// Row blocks of 32 query rows per wave of the dQ stage: 2 (256 rows per workgroup) unless the launch has few tiles
+// and is bound by the walk of the longest one.  With one block a wave's step takes 0.4 us instead of 0.75 and there are
+// twice the workgroups, but every K/V operand read from LDS feeds one MFMA instead of two.  Same bits.  Backward
+// with 2 / 1 blocks, 4 heads of D = 128, us: 2048 rows (32 tiles of 256) 75 / 59, 4096 rows (64) 127 / 103, 8192 rows
+// (128) 280 / 246, 10007 rows of 3 heads (120) 330 / 277, 12288 rows (192) 483 / 509, 16384 rows (256) 835 / 855;
+// 8192 rows of 5 heads (160) 347 / 354; D = 64: 4096 rows 87 / 70, 8192 rows 173 / 150.
+inline int dq_row_blocks(int64_t B, int64_t S, int32_t Hq) {
+    return (S + kOrderTile - 1) / kOrderTile * Hq * B <= 128 ? 1 : 2;
+}
 sp_status launch_attn_bwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_matrix_d64(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_matrix_d128(const AttnArgs& a, hipStream_t st);
