@@ -11,8 +11,7 @@
 // The last two are launched together (attn_bwd_matrix.h).
 // P is rebuilt from the saved LSE: P_ij = exp(scale*s_ij - LSE_i); S and dP
 // are evaluated in both matrix kernels.
-#include "attn_common.h"
-#include "sp_common.h"
+#include "attn_bwd_dkdv.h"
 
 namespace {
 
@@ -58,46 +57,55 @@ __global__ __launch_bounds__(256) void delta_kernel(const __bf16* __restrict__ o
     }
 }
 
-// dK = scale * sum of the chunks' partial sums, dV = sum of theirs.  The sums of one chunk, batch entry and KV head
-// are Skv * D floats in groups of four keys, [key / 4][column][key % 4] (the last group may hold fewer keys); the
-// outputs follow `map`.  A thread takes four keys of two columns.
+// dK = scale * sum of the chunks' partial sums, dV = sum of theirs (layout: dkdv::part_offset); the outputs follow
+// `map`.  A block takes 16 (D = 128) or 32 keys of one tile, a thread four keys of two columns.
 template <int D>
 __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restrict__ part, __bf16* __restrict__ dk,
-                                                         __bf16* __restrict__ dv, int32_t groups, int64_t n_items,
-                                                         int32_t nsplit, float scale, RowMap map, int32_t Skv, int32_t Hkv) {
-    constexpr int CP = D / 2;  // column pairs
-    const int64_t item = (int64_t)blockIdx.x * (256 / CP) + threadIdx.x / CP;  // (b*Hkv + g) * groups + key group
-    if (item >= n_items) return;
+                                                         __bf16* __restrict__ dv, DkdvChunks chunks, int32_t n_tiles,
+                                                         float scale, RowMap map, int32_t S, int32_t Skv, int32_t off,
+                                                         int32_t G, int32_t Hkv, int64_t n_bg) {
+    constexpr int CP = D / 2;                            // column pairs
+    constexpr int BPT = kOrderTile / 4 / (256 / CP);     // blocks per tile
+    const int64_t tile = blockIdx.x / BPT, bg = tile / n_tiles, b = bg / Hkv;
+    const int jt = (int)(tile - bg * n_tiles), g = (int)(bg - b * Hkv);
+    int n_split = chunks.nsplit, first = jt * n_split;
+    if (chunks.len > 0) {  // uniform
+        int count, upto;
+        dkdv::scan_chunks(n_tiles, S, off, G, chunks.len, count, upto);
+        n_split = __builtin_amdgcn_readlane(count, jt);
+        first = __builtin_amdgcn_readlane(upto, jt) - n_split;
+    }
     const int c = (int)(threadIdx.x % CP) * 2;
-    const int64_t bg = item / groups, b = bg / Hkv;
-    const int g = (int)(bg - b * Hkv), k0 = (int)(item - bg * groups) * 4;
-    const size_t chunk = (size_t)(n_items / groups) * Skv * D;  // floats of one chunk of the whole call
-    const int n = Skv - k0 < 4 ? Skv - k0 : 4;
-    const float* src = part + (size_t)bg * Skv * D + (size_t)k0 * D + (size_t)n * c;
+    const int k0 = ((int)(blockIdx.x % BPT) * (256 / CP) + (int)(threadIdx.x / CP)) * 4;  // in the tile
+    const int keys = Skv - jt * kOrderTile < kOrderTile ? Skv - jt * kOrderTile : kOrderTile;
+    if (k0 >= keys) return;
+    const int n = keys - k0 < 4 ? keys - k0 : 4;
+    const size_t chunk = (size_t)keys * D;  // floats from one chunk of the tile to the next
+    const float* sk_ = part + dkdv::part_offset(bg, chunks.nsplit, Skv, first, 0, keys, D) + (size_t)k0 * D + (size_t)n * c;
+    const float* sv_ = sk_ + (size_t)n_bg * chunks.nsplit * Skv * D;
     float sk[2][4] = {}, sv[2][4] = {};
     if (n == 4) {
-        for (int32_t s = 0; s < nsplit; ++s) {
-            const f32x4 k0v = *reinterpret_cast<const f32x4*>(src + (size_t)s * chunk);
-            const f32x4 k1v = *reinterpret_cast<const f32x4*>(src + (size_t)s * chunk + 4);
-            const f32x4 v0v = *reinterpret_cast<const f32x4*>(src + ((size_t)nsplit + s) * chunk);
-            const f32x4 v1v = *reinterpret_cast<const f32x4*>(src + ((size_t)nsplit + s) * chunk + 4);
+#pragma unroll 4
+        for (int32_t s = 0; s < n_split; ++s) {
+            const f32x4 ka = *reinterpret_cast<const f32x4*>(sk_ + s * chunk), kb = *reinterpret_cast<const f32x4*>(sk_ + s * chunk + 4);
+            const f32x4 va = *reinterpret_cast<const f32x4*>(sv_ + s * chunk), vb = *reinterpret_cast<const f32x4*>(sv_ + s * chunk + 4);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { sk[0][e] += k0v[e]; sk[1][e] += k1v[e]; sv[0][e] += v0v[e]; sv[1][e] += v1v[e]; }
+            for (int e = 0; e < 4; ++e) { sk[0][e] += ka[e]; sk[1][e] += kb[e]; sv[0][e] += va[e]; sv[1][e] += vb[e]; }
         }
     } else {
-        for (int32_t s = 0; s < nsplit; ++s)
+        for (int32_t s = 0; s < n_split; ++s)
             for (int x = 0; x < 2; ++x)
                 for (int e = 0; e < 3; ++e)
                     if (e < n) {
-                        sk[x][e] += src[(size_t)s * chunk + x * n + e];
-                        sv[x][e] += src[((size_t)nsplit + s) * chunk + x * n + e];
+                        sk[x][e] += sk_[s * chunk + x * n + e];
+                        sv[x][e] += sv_[s * chunk + x * n + e];
                     }
     }
     const size_t base = ((size_t)b * Skv * Hkv + g) * D + c;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (e < n) {
-            const size_t o = base + map.off(k0 + e);
+            const size_t o = base + map.off(jt * kOrderTile + k0 + e);
             *reinterpret_cast<uint32_t*>(dk + o) = pack_bf16(sk[0][e] * scale, sk[1][e] * scale);
             *reinterpret_cast<uint32_t*>(dv + o) = pack_bf16(sv[0][e], sv[1][e]);
         }
@@ -118,13 +126,13 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
         const sp_status r = D == 64 ? launch_attn_bwd_matrix_d64(a, st) : launch_attn_bwd_matrix_d128(a, st);
         if (r != SP_OK) return r;
     }
-    if ((a.stages & SP_BWD_STAGE_DKDV) && a.dkdv_splits > 1) {
-        const int32_t groups = (a.Skv + 3) / 4;
-        const int64_t items = (int64_t)a.B * a.Hkv * groups, per_block = 256 / (D / 2);
-        if ((items + per_block - 1) / per_block > 0x7fffffff) return SP_ERR_SHAPE;
-        hipLaunchKernelGGL((dkdv_reduce_kernel<D>), dim3((unsigned)((items + per_block - 1) / per_block)), dim3(256), 0, st,
-                           a.dkdv_part, (__bf16*)a.dk, (__bf16*)a.dv, groups, items, a.dkdv_splits, a.scale, a.kvmap,
-                           a.Skv, a.Hkv);
+    if ((a.stages & SP_BWD_STAGE_DKDV) && a.chunks.nsplit > 1) {
+        const int32_t tiles = order_tiles(a.Skv);
+        const int64_t blocks = (int64_t)a.B * a.Hkv * tiles * (kOrderTile / 4 / (256 / (D / 2)));
+        if (blocks > 0x7fffffff) return SP_ERR_SHAPE;
+        hipLaunchKernelGGL((dkdv_reduce_kernel<D>), dim3((unsigned)blocks), dim3(256), 0, st, a.dkdv_part, (__bf16*)a.dk,
+                           (__bf16*)a.dv, a.chunks, tiles, a.scale, a.kvmap, a.S, a.Skv, a.off, a.Hq / a.Hkv, a.Hkv,
+                           (int64_t)a.B * a.Hkv);
         if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
     }
     return SP_OK;

@@ -53,14 +53,33 @@ struct DkdvParams {
     const __bf16* q; const __bf16* k; const __bf16* v; const __bf16* dO;
     const float* aux;  // per 32-row tile: 32 x -LSE/scale then 32 x -Delta; [B*Hq, S_pad/32, 2, 32]
     __bf16* dk; __bf16* dv;
-    float* part;  // nsplit > 1: fp32 partial sums, [2 (dK unscaled, dV)][nsplit][B, Skv, Hkv, D]
+    DkdvChunks chunks;
+    float* part;  // chunks.nsplit > 1: fp32 partial sums, dK (unscaled) then dV; see part_offset
     const int32_t* row_hi;
     const int32_t* order;  // packed documents: key tiles in the order workgroups take them (or null)
     RowMap qmap, kvmap;
     int32_t B, several;  // several: more than one sequence
-    int32_t S, Skv, off, S_pad, Hq, Hkv, G, n_ktiles, nsplit;  // S query rows, Skv keys; row i sees keys j <= i + off
+    int32_t S, Skv, off, S_pad, Hq, Hkv, G, n_ktiles;  // S query rows, Skv keys; row i sees keys j <= i + off
     float scale, scale_log2;
 };
+
+// Equal chunks: the chunk counts of all tiles, one tile per lane, and their running sum.
+__device__ __forceinline__ void scan_chunks(int n_tiles, int S, int off, int G, int len, int& count, int& upto) {
+    const int t = (int)__lane_id();
+    count = t < n_tiles ? (dkdv_tile_steps(t, S, off, G) + len - 1) / len : 0;
+    upto = count;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int below = __shfl_up(upto, d, 64);
+        if (t >= d) upto += below;
+    }
+}
+// Where the partial sums of a chunk start: every (batch entry, KV head) bg has room for nsplit * Skv keys; in it the
+// tiles follow each other, a tile's chunks follow each other (`first` chunks of whole tiles lie before them), and a
+// chunk's `keys` keys are in groups of four, [key / 4][column][key % 4] (the last group may hold fewer).
+__device__ __forceinline__ size_t part_offset(int64_t bg, int nsplit, int Skv, int first, int split, int keys, int D) {
+    return ((size_t)bg * nsplit * Skv + (size_t)first * kOrderTile + (size_t)split * keys) * D;
+}
 
 // 16 accumulator registers from the four 16-byte per-row reads of one lane
 __device__ __forceinline__ void seeds_to_acc(f32x16& acc, const u32x4 (&s)[4]) {
@@ -79,7 +98,7 @@ struct Lds {
     static constexpr int BYTES = AUX + kWaves * AUX_W;
 };
 
-// The work of workgroup `wg` of n_ktiles * nsplit * Hkv * B; smem holds Lds<D>::BYTES, 1 KB aligned.
+// The work of workgroup `wg` of n_chunks * Hkv * B; smem holds Lds<D>::BYTES, 1 KB aligned.
 template <int D, bool VARLEN, bool SPLIT>
 __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem) {
     constexpr int NS = D / 16;   // operand slots per phase (contraction steps over the head dim)
@@ -92,21 +111,38 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
 
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // earliest key tiles (most rows to visit) first; the nsplit workgroups that share a key tile are neighbours
-    const int nsplit = SPLIT ? p.nsplit : 1;
+    // earliest key tiles (most rows to visit) first; the workgroups that share a key tile are neighbours
     // Order: chunks of one head together for a single sequence (they share the head's Q/dO stream through L2); with
     // several sequences the batch entry and KV head vary fastest instead, so that every sequence's longest key
     // tiles are dispatched before anybody's short ones (sequence by sequence, the last sequence's longest tile
     // started when the grid was two thirds done: 16 x 4096 rows 710 -> 510 us).
-    const uint32_t n_chunks = (uint32_t)p.n_ktiles * (uint32_t)nsplit, n_heads = (uint32_t)p.Hkv * (uint32_t)p.B;
+    const uint32_t n_chunks = (uint32_t)p.chunks.n_chunks, n_heads = (uint32_t)p.Hkv * (uint32_t)p.B;
     const int chunk_id = (int)(p.several ? wg / n_heads : wg % n_chunks);
     const int head_id = (int)(p.several ? wg % n_heads : wg / n_chunks);
-    int jt = SPLIT ? chunk_id / nsplit : chunk_id;
-    const int split = SPLIT ? chunk_id % nsplit : 0;
-    if (VARLEN && p.order) {  // longest tile first; clamped so that a bad entry cannot become a wild address
+    int jt = chunk_id, split = 0;
+    int tile_chunks = 1, first_chunk = 0;  // chunks of this tile, and of the tiles before it
+    bool equal = false;
+    if constexpr (SPLIT) {
+        equal = p.chunks.len > 0;
+        if (equal) {
+            int count, upto;
+            scan_chunks(p.n_ktiles, p.S, p.off, p.G, p.chunks.len, count, upto);
+            jt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= chunk_id));
+            jt = jt < p.n_ktiles ? jt : p.n_ktiles - 1;
+            tile_chunks = __builtin_amdgcn_readlane(count, jt);
+            first_chunk = __builtin_amdgcn_readlane(upto, jt) - tile_chunks;
+            split = chunk_id - first_chunk;
+        } else {
+            tile_chunks = p.chunks.nsplit;
+            jt = chunk_id / tile_chunks;
+            split = chunk_id % tile_chunks;
+        }
+    }
+    if (VARLEN && p.order && !equal) {  // longest tile first; clamped so that a bad entry cannot become a wild address
         const int v = __builtin_amdgcn_readfirstlane(p.order[jt]);
         jt = v < 0 ? 0 : (v < p.n_ktiles ? v : p.n_ktiles - 1);
     }
+    if (SPLIT && !equal) first_chunk = jt * tile_chunks;
     const int g = head_id % p.Hkv, b = head_id / p.Hkv;
     const int S = p.S, Skv = p.Skv;
     const __bf16* kb = p.k + ((size_t)b * Skv * p.Hkv + g) * D;
@@ -167,10 +203,10 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     const int it_end = (wg_hi_max + BMQ - 1) / BMQ;  // exclusive
     const int n_it = it_end - it_begin;
     // Steps are (head in group, row tile) pairs, heads ascending, rows descending inside a head.  The
-    // key tile's step sequence is cut into nsplit contiguous chunks, one per workgroup; a chunk may be
+    // key tile's step sequence is cut into tile_chunks contiguous chunks, one per workgroup; a chunk may be
     // empty (its workgroup then contributes zeros).
     const int total_all = n_it * p.G;
-    const int per_split = (total_all + nsplit - 1) / nsplit;
+    const int per_split = (total_all + tile_chunks - 1) / tile_chunks;
     int s_begin = split * per_split < total_all ? split * per_split : total_all;
     const int s_end = s_begin + per_split < total_all ? s_begin + per_split : total_all;
     const int total = s_end - s_begin;
@@ -551,27 +587,28 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
         // lane holds four consecutive keys of one column in four registers, and the sums are laid out like that
         //, so a store is 16 bytes per lane and 512 contiguous bytes per half wave: 64 stores per wave
         // where key-major sums took 256 of 4 bytes per lane (5.5 us per workgroup).
-        float* pk = p.part + ((size_t)split * p.B + b) * p.Hkv * Skv * D + (size_t)g * Skv * D;
-        float* pv = pk + (size_t)nsplit * p.B * p.Hkv * Skv * D;
+        const int keys = Skv - j0 < BNK ? Skv - j0 : BNK;
+        float* pk = p.part + part_offset((int64_t)b * p.Hkv + g, p.chunks.nsplit, Skv, first_chunk, split, keys, D);
+        float* pv = pk + (size_t)p.B * p.Hkv * p.chunks.nsplit * Skv * D;
 #pragma unroll
         for (int kbk = 0; kbk < 2; ++kbk)
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
-                const int k0 = wkey0 + 32 * kbk + 8 * g4 + 4 * hi;  // first of the lane's four keys
-                if (k0 + 4 <= Skv) {
+                const int k0 = wkey0 - j0 + 32 * kbk + 8 * g4 + 4 * hi;  // first of the lane's four keys, in the tile
+                if (k0 + 4 <= keys) {
 #pragma unroll
                     for (int db = 0; db < NDB; ++db) {
                         const size_t at = (size_t)k0 * D + 4 * (32 * db + lo);
                         *reinterpret_cast<f32x4*>(pk + at) = f32x4{dkacc[kbk][db][4 * g4], dkacc[kbk][db][4 * g4 + 1], dkacc[kbk][db][4 * g4 + 2], dkacc[kbk][db][4 * g4 + 3]};
                         *reinterpret_cast<f32x4*>(pv + at) = f32x4{dvacc[kbk][db][4 * g4], dvacc[kbk][db][4 * g4 + 1], dvacc[kbk][db][4 * g4 + 2], dvacc[kbk][db][4 * g4 + 3]};
                     }
-                } else if (k0 < Skv) {  // the last one to three keys
+                } else if (k0 < keys) {  // the last one to three keys
 #pragma unroll
                     for (int db = 0; db < NDB; ++db)
 #pragma unroll
                         for (int e = 0; e < 3; ++e)
-                            if (k0 + e < Skv) {
-                                const size_t at = (size_t)k0 * D + (size_t)(Skv - k0) * (32 * db + lo) + e;
+                            if (k0 + e < keys) {
+                                const size_t at = (size_t)k0 * D + (size_t)(keys - k0) * (32 * db + lo) + e;
                                 pk[at] = dkacc[kbk][db][4 * g4 + e];
                                 pv[at] = dvacc[kbk][db][4 * g4 + e];
                             }

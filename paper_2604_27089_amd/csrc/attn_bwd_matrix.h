@@ -64,7 +64,7 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
 inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixParams& p) {
     const int64_t longest = a.longest > 0 && a.longest < a.S ? a.longest : a.S;
     const double steps = (double)((longest + 31) / 32);
-    const double t_q = 0.95 * steps + 10., t_kv = 1.5 * steps * (a.Hq / a.Hkv) / a.dkdv_splits + 20.;
+    const double t_q = 0.95 * steps + 10., t_kv = 1.5 * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + 20.;
     bool lead_q;
     int64_t lead;
     if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
@@ -94,10 +94,10 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
         k.S = a.S; k.Skv = a.Skv; k.off = a.off; k.S_pad = a.S_pad; k.Hq = a.Hq; k.Hkv = a.Hkv; k.G = a.Hq / a.Hkv;
         k.qmap = a.qmap; k.kvmap = a.kvmap;
         k.n_ktiles = (a.Skv + dkdv::BNK - 1) / dkdv::BNK;
-        k.nsplit = a.dkdv_splits; k.part = a.dkdv_part;
+        k.chunks = a.chunks; k.part = a.dkdv_part;
         k.scale = a.scale; k.scale_log2 = a.scale * kLog2e;
         k.B = a.B; k.several = a.B > 1;
-        if (kv && (k.nsplit < 1 || (k.nsplit > 1 && !k.part))) return SP_ERR_WORKSPACE;
+        if (kv && (k.chunks.nsplit < 1 || (k.chunks.nsplit > 1 && !k.part))) return SP_ERR_WORKSPACE;
     }
     {
         dq::DqParams& q = p.q;
@@ -111,7 +111,7 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
         q.n_ranks = VARLEN && q.order ? order_tiles(a.S) * (kOrderTile / rows) : q.n_qtiles;
         q.scale = a.scale; q.scale_log2 = a.scale * kLog2e;
     }
-    const int64_t n_kv = kv ? (int64_t)p.kv.n_ktiles * p.kv.nsplit * a.Hkv * a.B : 0;
+    const int64_t n_kv = kv ? (int64_t)p.kv.chunks.n_chunks * a.Hkv * a.B : 0;
     const int64_t n_q = qs ? (int64_t)p.q.n_ranks * a.Hq * a.B : 0;
     if (n_kv + n_q > 0x7fffffff) return SP_ERR_SHAPE;
     dispatch_order(a, n_kv, n_q, p);
@@ -120,7 +120,7 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
         const int64_t n = n_kv + n_q - base < kMaxGrid ? n_kv + n_q - base : kMaxGrid;
         p.base = (uint32_t)base;
 #define SP_MATRIX(SPLIT, NQ) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, SPLIT, NQ>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p)
-        if (p.kv.nsplit > 1) { if (nq == 1) SP_MATRIX(true, 1); else SP_MATRIX(true, 2); }
+        if (p.kv.chunks.nsplit > 1) { if (nq == 1) SP_MATRIX(true, 1); else SP_MATRIX(true, 2); }
         else { if (nq == 1) SP_MATRIX(false, 1); else SP_MATRIX(false, 2); }
 #undef SP_MATRIX
         if (launch_status() != SP_OK) return SP_ERR_LAUNCH;

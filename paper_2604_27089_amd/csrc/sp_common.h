@@ -36,6 +36,13 @@ struct RowMap {
     }
 };
 
+// How the dK/dV work of the key tiles of one sequence and KV head is cut into chunks, one workgroup each.
+struct DkdvChunks {
+    int32_t nsplit;    // chunks per key tile, and (times the keys) the room there is for partial sums
+    int32_t len;       // > 0: instead, every tile gets as many chunks of about this many steps as it needs
+    int32_t n_chunks;  // over all key tiles
+};
+
 // One attention problem as the kernels see it.  Dense calls are B independent
 // sequences of S rows; packed-document calls are B = 1, S = T rows with a
 // per-row visibility window taken from `row_lo` / `row_hi`.  In general the S
@@ -61,8 +68,8 @@ struct AttnArgs {
     int32_t stages;         // bwd: bit mask of SP_BWD_STAGE_*
     int32_t n_docs;         // varlen: number of documents (else 0)
     int32_t longest;        // bwd: upper bound of the longest document, when the caller knows one (else 0)
-    int32_t dkdv_splits;    // bwd: workgroups that share one key tile of the dK/dV kernel (dkdv_split_count)
-    float* dkdv_part;       // bwd workspace: their fp32 partial sums (null when dkdv_splits == 1)
+    DkdvChunks chunks;      // bwd: the work split of the dK/dV stage (dkdv_split_count, dkdv_chunks)
+    float* dkdv_part;       // bwd workspace: the chunks' fp32 partial sums (null when chunks.nsplit == 1)
 };
 
 sp_status launch_relayout(const void* in, void* out, int64_t B, int64_t S_l, int64_t H, int64_t D,
@@ -101,7 +108,6 @@ inline int fwd_key_groups(int64_t B, int64_t S, int32_t Hq) {
     const int64_t tiles = (S + kOrderTile - 1) / kOrderTile * Hq * B;
     return tiles <= 128 ? 4 : tiles <= 384 ? 2 : 1;
 }
-sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
 // Row blocks of 32 query rows per wave of the dQ stage: 2 (256 rows per workgroup) unless the launch has few tiles
 // and is bound by the walk of the longest one.  With one block a wave's step takes 0.4 us instead of 0.75 and there are
 // twice the workgroups, but every K/V operand read from LDS feeds one MFMA instead of two.  Same bits.  Backward
@@ -111,6 +117,7 @@ sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
 inline int dq_row_blocks(int64_t B, int64_t S, int32_t Hq) {
     return (S + kOrderTile - 1) / kOrderTile * Hq * B <= 128 ? 1 : 2;
 }
+sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_matrix_d64(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_matrix_d128(const AttnArgs& a, hipStream_t st);
@@ -146,6 +153,41 @@ inline int32_t dkdv_split_count(int64_t B, int64_t S, int64_t Skv, int32_t Hq, i
     const int64_t cap = (2048 + tiles - 1) / tiles;
     if (n > cap) n = cap;
     return n < 1 ? 1 : (int32_t)n;
+}
+// (head, row tile) steps of the 256 keys of tile jt when the whole sequence is one document
+__host__ __device__ inline int32_t dkdv_tile_steps(int32_t jt, int32_t S, int32_t off, int32_t G) {
+    const int32_t j0 = jt * kOrderTile;
+    return ((S + 31) / 32 - (j0 > off ? j0 - off : 0) / 32) * G;
+}
+// Equal chunks.  A causal key tile's steps fall linearly from the first tile to the last, so the same number of
+// chunks for every tile makes the first tile's twice as long as the mean.  A launch whose workgroups all run at once
+// (dK/dV and dQ together at most one per compute unit) ends with those, so there, if the work of each tile is known
+// on the host (`causal`: one document per sequence), tiles get chunks of one length instead, as short as the room
+// for partial sums allows (a tile's chunks times its keys, summed, at most nsplit * Skv).  A workgroup finds its
+// tile with one scan over the tiles' chunk counts, a tile per lane of a wave.  Launches of several rounds keep the
+// unequal chunks: the short ones fill the end.  Backward with unequal / equal chunks, us, 4 heads of D = 128: 2048
+// rows 59 / 53, 3000 rows 79 / 69, 4096 rows 100 / 89; two rounds, 8192 rows, 233 / 250; four, 16384 rows, 786 / 839.
+constexpr int32_t kMaxEqualTiles = 64;
+constexpr int64_t kComputeUnits = 256;
+inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t nsplit, bool causal) {
+    const int32_t n = order_tiles(Skv), G = Hq / Hkv, q_rows = 128 * dq_row_blocks(B, S, Hq);
+    const int64_t workgroups = (int64_t)n * nsplit * Hkv * B + ((int64_t)S + q_rows - 1) / q_rows * Hq * B;
+    DkdvChunks c{nsplit, 0, n * nsplit};
+    if (!causal || workgroups > kComputeUnits || nsplit < 2 || n < 2 || n > kMaxEqualTiles || (int64_t)S * G > (int64_t)1 << 30) return c;
+    int64_t total = 0;
+    for (int32_t t = 0; t < n; ++t) total += dkdv_tile_steps(t, S, off, G);
+    // steps are taken four at a time, so lengths are multiples of four; the smallest one (up to 1/16) that fits
+    for (int64_t len = (total / ((int64_t)n * nsplit) + 4) & ~(int64_t)3;; len += (len / 16 + 4) & ~(int64_t)3) {
+        int64_t rows = 0;
+        int32_t chunks = 0;
+        for (int32_t t = 0; t < n; ++t) {
+            const int32_t k = (int32_t)((dkdv_tile_steps(t, S, off, G) + len - 1) / len);
+            const int32_t keys = Skv - t * kOrderTile;
+            chunks += k;
+            rows += (int64_t)k * (keys < kOrderTile ? keys : kOrderTile);
+        }
+        if (rows <= (int64_t)nsplit * Skv) return DkdvChunks{nsplit, (int32_t)len, chunks};
+    }
 }
 inline size_t dkdv_part_bytes(int64_t B, int64_t Skv, int32_t Hkv, int32_t D, int32_t nsplit) {
     return nsplit > 1 ? (size_t)2 * nsplit * B * Skv * Hkv * D * sizeof(float) : 0;

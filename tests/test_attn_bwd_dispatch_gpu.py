@@ -6,10 +6,11 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import ref_block as rb
 from oracle import ref_numpy as rn
 from paper_2604_27089_amd import binding as sp
 from paper_2604_27089_amd import synth
-from gpu_util import GRAD_REL_L2, dev_bf16, grad_err, host_f64
+from gpu_util import GRAD_REL_L2, dev_bf16, grad_err, guarded, host_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +58,27 @@ def test_packed_documents(lengths, heads):
     refs = rn.attn_varlen_bwd(*(rn.widen_bf16(t[0]) for t in bits), cu_h)[:3]
     for got, ref, name in zip(grads, refs, ("dq", "dk", "dv")):
         assert grad_err(host_f64(got[:, :1]), ref, name) <= GRAD_REL_L2
+
+
+# one-round launches: chunks of equal length, as many per key tile as its steps need; ragged last tiles, offsets, and
+# shapes just past one round (unequal chunks).  The workspace has exactly the asked size, between canaries.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Sq,Skv,off,Hq,Hkv", [(257, 257, 0, 4, 1), (513, 513, 0, 1, 1), (1030, 1030, 0, 3, 1), (900, 900, 0, 8, 2),
+                                               (300, 1199, 900, 8, 1), (1500, 259, 0, 4, 1), (700, 800, 5000, 4, 2),
+                                               (2047, 2047, 0, 2, 1), (1025, 1025, 0, 16, 8), (2050, 2050, 0, 10, 5)])
+def test_equal_chunks(Sq, Skv, off, Hq, Hkv, D):
+    qb, _, _, dob = synth.attn_inputs(Sq, Sq, Hq, Hkv, D)
+    _, kb, vb, _ = synth.attn_inputs(Skv + 3, Skv, Hq, Hkv, D)
+    q, k, v, do = (dev_bf16(t) for t in (qb, kb, vb, dob))
+    o, lse = sp.sp_attn_block_fwd(q, k, v, off)
+    ws, check = guarded((sp.sp_attn_block_bwd_workspace_bytes(1, Sq, Skv, Hq, Hkv, D),), torch.uint8)
+    dq, dk, dv = sp.sp_attn_block_bwd(q, k, v, o, lse, do, off, workspace=ws)
+    check("workspace")
+    q64, k64, v64, do64 = (rn.widen_bf16(t[0]) for t in (qb, kb, vb, dob))
+    scale = 1.0 / np.sqrt(D)
+    o_ref, lse_ref = rb.block_attn_fwd(q64, k64, v64, scale, off)
+    refs = rb.block_attn_bwd(q64, k64, v64, lse_ref, np.einsum("shd,shd->hs", o_ref, do64), do64, scale, off)
+    for got, ref, name in zip((dq, dk, dv), refs, ("dq", "dk", "dv")):
+        assert grad_err(host_f64(got[0]), ref, name) <= GRAD_REL_L2, (name, Sq, Skv, off, Hq, Hkv, D)
+    again = sp.sp_attn_block_bwd(q, k, v, o, lse, do, off)
+    assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(again, (dq, dk, dv)))
