@@ -118,17 +118,20 @@ def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()  # the declared argument types make a pointer of it
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+# The raw handle of the current stream, without the Stream object that torch.cuda.current_stream() builds around it.
+_current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
+def _stream(stream) -> int:
+    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
 def _expect(t: torch.Tensor, shape, dtype, name: str):
     """The C ABI sees pointers only: extents and element types are checked here, before any launch."""
-    if tuple(t.shape) != tuple(int(x) for x in shape) or t.dtype != dtype:
+    if t.shape != shape or t.dtype != dtype:
         raise ValueError(f"{name}: expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
 
@@ -136,7 +139,7 @@ def _new(stream, shape, dtype, device) -> torch.Tensor:
     """A tensor allocated by a wrapper.  torch's allocator ties a block to the stream that was current when it
     was allocated; when the kernels go to another stream the block is marked as in use there, so that it is
     not handed out again while they are still queued."""
-    t = torch.empty(tuple(int(x) for x in shape), dtype=dtype, device=device)
+    t = torch.empty(shape, dtype=dtype, device=device)
     if stream is not None:
         t.record_stream(stream)
     return t
