@@ -495,14 +495,11 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
                                 for (int r = 0; r < 16; ++r) sacc[kbk][r] = 8 * (r / 4) + r % 4 < lim ? sacc[kbk][r] : -__builtin_inff();
                             }
                         } else {
-                            const bool dead0 = khi_l[0] <= q0, dead1 = khi_l[1] <= q0;
-                            if (__builtin_amdgcn_ballot_w64(dead0 || dead1) != 0) {
+                            const uint64_t dead0 = __builtin_amdgcn_ballot_w64(khi_l[0] <= q0), dead1 = __builtin_amdgcn_ballot_w64(khi_l[1] <= q0);
+                            if ((dead0 | dead1) != 0) {
                                 asm volatile("" ::: "memory");  // keeps this a branch
-#pragma unroll
-                                for (int r = 0; r < 16; ++r) {
-                                    sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
-                                    sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
-                                }
+                                hide_lanes(sacc[0], dead0);
+                                hide_lanes(sacc[1], dead1);
                             }
                         }
                     }

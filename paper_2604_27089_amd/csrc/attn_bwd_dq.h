@@ -409,14 +409,13 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                                 for (int r = 0; r < 16; ++r) sacc[qb][r] = 8 * (r / 4) + r % 4 >= lim ? sacc[qb][r] : -__builtin_inff();
                             }
                         } else {
-                            const bool dead0 = rlo_l[0] >= j0 + BN, dead1 = rlo_l[1] >= j0 + BN;
-                            if (__builtin_amdgcn_ballot_w64(dead0 || dead1) != 0) {
+                            uint64_t dead[NQ], any = 0;
+#pragma unroll
+                            for (int qb = 0; qb < NQ; ++qb) any |= dead[qb] = __builtin_amdgcn_ballot_w64(rlo_l[qb] >= j0 + BN);
+                            if (any != 0) {
                                 asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                                for (int r = 0; r < 16; ++r) {
-                                    sacc[0][r] = dead0 ? -__builtin_inff() : sacc[0][r];
-                                    if constexpr (NQ == 2) sacc[1][r] = dead1 ? -__builtin_inff() : sacc[1][r];
-                                }
+                                for (int qb = 0; qb < NQ; ++qb) hide_lanes(sacc[qb], dead[qb]);
                             }
                         }
                     }

@@ -81,6 +81,12 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     p.mix_kv = (uint32_t)(lead_q ? n_kv : n_kv - lead);
 }
 
+template <int D, bool VARLEN, int NQ>
+void launch_grid(const MatrixParams& p, unsigned n, hipStream_t st) {
+    if (p.kv.chunks.nsplit > 1) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, true, NQ>), dim3(n), dim3(dkdv::kThreads), 0, st, p);
+    else hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, false, NQ>), dim3(n), dim3(dkdv::kThreads), 0, st, p);
+}
+
 template <int D, bool VARLEN>
 sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
     MatrixParams p{};
@@ -119,10 +125,8 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
     for (int64_t base = 0; base < n_kv + n_q; base += kMaxGrid) {
         const int64_t n = n_kv + n_q - base < kMaxGrid ? n_kv + n_q - base : kMaxGrid;
         p.base = (uint32_t)base;
-#define SP_MATRIX(SPLIT, NQ) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, SPLIT, NQ>), dim3((unsigned)n), dim3(dkdv::kThreads), 0, st, p)
-        if (p.kv.chunks.nsplit > 1) { if (nq == 1) SP_MATRIX(true, 1); else SP_MATRIX(true, 2); }
-        else { if (nq == 1) SP_MATRIX(false, 1); else SP_MATRIX(false, 2); }
-#undef SP_MATRIX
+        if (nq == 1) launch_grid<D, VARLEN, 1>(p, (unsigned)n, st);
+        else launch_grid<D, VARLEN, 2>(p, (unsigned)n, st);
         if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
     }
     return SP_OK;

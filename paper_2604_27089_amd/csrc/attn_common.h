@@ -256,6 +256,20 @@ __device__ __forceinline__ void mfma_vc_ab(f32x16& acc, const u32x4& a, const bf
     if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%4)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c), "n"(W));
     else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c));
 }
+// x = the lane's bit of `lanes` ? -inf : x.  One select per register as assembly: written in C++, a run of selects on one
+// flag becomes a branch around moves, and its copies of whole accumulator tiles took the dQ stage with one row block
+// (packed documents) from 241 to 256 vector registers and moves between the register files.  The compiler does not see
+// that the first select reads a mask that a compare may just have written: two wait states.
+__device__ __forceinline__ void hide_lanes(f32x16& x, uint64_t lanes) {
+    const float hidden = -__builtin_inff();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float v = x[r];
+        if (r == 0) asm("s_nop 1\n\tv_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
+        else asm("v_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
+        x[r] = v;
+    }
+}
 // at most N of this wave's global loads (register and LDS destinations) are still in flight
 template <int N>
 __device__ __forceinline__ void vmem_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
