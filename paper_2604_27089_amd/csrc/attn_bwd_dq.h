@@ -472,24 +472,15 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
             if constexpr (NQ == 2) dqacc[1][db] = mfma32(as_bf16x8(kt), as_bf16x8(dsp[1][1][c]), dqacc[1][db]);
         });
     }
-    wait_vmem();  // no direct-to-LDS load may outlive the workgroup's LDS allocation
+    wait_vmem();  // no direct-to-LDS load may outlive the workgroup's LDS allocation, nor land in what is written next
+    __syncthreads();
 
-    // ---- write dQ (scaled): accumulator rows = d, column = this lane's query ----
+    // ---- write dQ (scaled), through LDS ----
+    __bf16* const out = p.dq + ((size_t)b * S * p.Hq + h) * D;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
-        const int row = wrow0 + 32 * qb + lo;
-        if (row < S) {
-            __bf16* out = p.dq + ((size_t)b * S * p.Hq + h) * D + p.qmap.off(row);
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    u32x2 w;
-                    w[0] = pack_bf16(dqacc[qb][db][4 * gq + 0] * p.scale, dqacc[qb][db][4 * gq + 1] * p.scale);
-                    w[1] = pack_bf16(dqacc[qb][db][4 * gq + 2] * p.scale, dqacc[qb][db][4 * gq + 3] * p.scale);
-                    *reinterpret_cast<u32x2*>(out + 32 * db + 8 * gq + 4 * hi) = w;
-                }
-        }
+        const int row0 = wrow0 + 32 * qb;
+        store_rows<D>(dqacc[qb], p.scale, smem + wave * (32 * D * 2), S - row0, [&](int row) __attribute__((always_inline)) { return out + p.qmap.off(row0 + row); });
     }
 }
 

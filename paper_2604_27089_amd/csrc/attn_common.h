@@ -337,4 +337,34 @@ __device__ __forceinline__ int tile_off_tr(int row0, int col0, int i16) {
     return row * (D * 2) + (((col >> 3) ^ swz<D>(row)) * 16) + (col & 7) * 2;
 }
 
+// Stores 32 result rows of D columns as bf16, from a transposed accumulator (lane = row lo, register r of block db =
+// column 32*db + 8*(r/4) + 4*hi + r%4), through `buf`: 32 * D * 2 bytes of LDS that no other wave touches.  Straight
+// from the registers a store instruction would write 16 bytes to each of 32 rows, an eighth of a cache line each; from
+// LDS it writes whole rows, 1 KB per instruction.  16-byte chunk c of row r sits at position c ^ (r or r/2) of its row,
+// which spreads both the 8-byte writes (32 rows, one chunk) and the 16-byte reads (whole rows) over the banks.
+// address(row) is where row `row` (0 .. 31) goes; rows from `rows` on are left out.
+template <int D, typename ADDR>
+__device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float scale, char* buf, int rows, ADDR&& address) {
+    constexpr int CH = D / 8, RPI = 64 / CH;  // chunks per row, rows per store instruction
+    const int lane = __lane_id(), lo = lane & 31, hi = lane >> 5;
+    auto at = [](int row, int chunk) __attribute__((always_inline)) { return row * (D * 2) + ((chunk ^ ((D == 128 ? row : row >> 1) & (CH - 1))) * 16); };
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            u32x2 w;
+            w[0] = pack_bf16(acc[db][4 * g + 0] * scale, acc[db][4 * g + 1] * scale);
+            w[1] = pack_bf16(acc[db][4 * g + 2] * scale, acc[db][4 * g + 3] * scale);
+            *reinterpret_cast<u32x2*>(buf + at(lo, 4 * db + g) + 8 * hi) = w;
+        }
+    asm volatile("" ::: "memory");  // LDS accesses of a wave execute in order: keeping the order is all it takes
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int row = RPI * i + lane / CH, chunk = lane % CH;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(buf + at(row, chunk));
+        if (row < rows) *reinterpret_cast<u32x4*>(address(row) + 8 * chunk) = v;
+    }
+    asm volatile("" ::: "memory");
+}
+
 }  // namespace sp

@@ -406,19 +406,12 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(FwdParams p) {
 
     // ---- epilogue: normalise, write O (bf16) and LSE (natural log) ----
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    if (qrow < S) {
-        __bf16* orow = p.o + ((size_t)b * S * p.Hq + h) * D + p.qmap.off(qrow);
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                u32x2 w;
-                w[0] = pack_bf16(oacc[db][4 * gq + 0] * inv, oacc[db][4 * gq + 1] * inv);
-                w[1] = pack_bf16(oacc[db][4 * gq + 2] * inv, oacc[db][4 * gq + 3] * inv);
-                *reinterpret_cast<u32x2*>(orow + 32 * db + 8 * gq + 4 * hi) = w;
-            }
-        if (hi == 0) p.lse[((size_t)b * p.Hq + h) * S + qrow] = (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2;
-    }
+    // (every wave is past its last read of the tiles, and each one takes LDS of its own: with key groups the slot whose
+    // partial result it has just merged)
+    char* const buf = reinterpret_cast<char*>(smem) + rb * (KS == 1 ? D * 64 : D * 128);
+    __bf16* const ob = p.o + ((size_t)b * S * p.Hq + h) * D;
+    store_rows<D>(oacc, inv, buf, S - wrow0, [&](int row) __attribute__((always_inline)) { return ob + p.qmap.off(wrow0 + row); });
+    if (qrow < S && hi == 0) p.lse[((size_t)b * p.Hq + h) * S + qrow] = (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2;
 }
 
 template <int D, bool VARLEN, int KS>
