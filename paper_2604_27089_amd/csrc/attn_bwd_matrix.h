@@ -67,7 +67,10 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     const double t_q = 0.95 * steps + 10., t_kv = 1.5 * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + 20.;
     bool lead_q;
     int64_t lead;
-    if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
+    if (a.off >= a.Skv) {  // every row sees every key: equal workgroups within a stage, the longer ones first
+        lead_q = full_dq_time(a.Skv, 128 * dq_row_blocks(a.B, a.S, a.Hq)) > full_dkdv_time(a.S, a.Hq / a.Hkv, a.chunks.nsplit);
+        lead = lead_q ? n_q : n_kv;
+    } else if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
         lead_q = t_q >= t_kv;
         lead = (int64_t)(lead_q ? n_q * (1. - t_kv / t_q) : n_kv * (1. - t_q / t_kv));
     } else {

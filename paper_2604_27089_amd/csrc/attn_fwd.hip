@@ -432,7 +432,7 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
 
 template <int D, bool VARLEN>
 sp_status launch_groups(const AttnArgs& a, hipStream_t st) {
-    switch (fwd_key_groups(a.B, a.S, a.Hq)) {
+    switch (fwd_key_groups(a.B, a.S, a.Skv, a.off, a.Hq)) {
         case 4: return launch<D, VARLEN, 4>(a, st);
         case 2: return launch<D, VARLEN, 2>(a, st);
         default: return launch<D, VARLEN, 1>(a, st);

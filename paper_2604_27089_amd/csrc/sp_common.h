@@ -79,6 +79,7 @@ sp_status launch_relayout(const void* in, void* out, int64_t B, int64_t S_l, int
 // worth its time and callers pass null orders.
 constexpr int32_t kOrderTile = 256;
 constexpr int32_t kMaxOrderTiles = 16384;
+constexpr int64_t kComputeUnits = 256;
 inline int32_t order_tiles(int64_t T) { return (int32_t)((T + kOrderTile - 1) / kOrderTile); }
 // Per-row document windows, and (if `work` is not null) the tile orders: `work` is scratch of
 // 2*order_tiles(T) int32, `order_q`, `order_k` receive order_tiles(T) int32 each.
@@ -98,15 +99,38 @@ inline dim3 tile_rank_grid(int32_t Hq, int32_t B, int32_t n_tiles) {
 // How many key groups share a forward workgroup (attn_fwd.hip): its 8 waves cover 256 / KS rows, and every KS-th
 // key tile goes to the same group.  A compute unit holds one workgroup, and a workgroup walks its keys tile by
 // tile, so a launch of few 256-row tiles leaves most units idle while the longest tile is walked alone: KS groups
-// give KS times the workgroups, each with 1/KS of the walk, for KS times the K/V bytes staged per product.
-// Measured, 4 query heads of D = 128, KS = 1 / 2 / 4, us: 512 rows (8 tiles) 23 / 17 / 15, 4096 rows (64) 106 / 61 /
-// 49, 8192 rows (128) 196 / 116 / 114, 12288 rows (192) 310 / 192 / 247, 16384 rows (256) 405 / 292 / 379, 24576 rows
-// (384) 654 / 639 / 793, 32768 rows (512) 1000 / 1057 / 1365; 8 x 2048 rows (256) 64 / 52 / 73; 64 x 512 rows (512)
-// 49 / 66 / 86; D = 64: 8192 rows 164 / 90 / 64, 16384 rows 318 / 204 / 216.  A function of the extents only, so that
-// every layout and entry point of one problem gives the same bits.
-inline int fwd_key_groups(int64_t B, int64_t S, int32_t Hq) {
-    const int64_t tiles = (S + kOrderTile - 1) / kOrderTile * Hq * B;
-    return tiles <= 128 ? 4 : tiles <= 384 ? 2 : 1;
+// give KS times the workgroups, each with 1/KS of the walk, for KS times the K/V bytes staged per product.  The
+// count is taken whose estimate is least: no launch ends before its longest workgroup, nor before the work shared
+// out evenly plus the units' idle time in a last round of (at least) the shortest workgroups, a fifth slower than
+// a workgroup alone (clock and shared paths); a workgroup takes 1.6 us per 64 keys of its walk, 8 and 38 % more
+// per key with 2 and 4 groups, and 9 to 10.5 us beyond.
+// Measured, 4 query heads of D = 128, KS = 1 / 2 / 4, us: 512 rows (8 tiles of 256) 23 / 17 / 15, 4096 rows (64) 106 /
+// 61 / 49, 8192 rows (128) 196 / 116 / 114, 12288 rows (192) 310 / 192 / 247, 16384 rows (256) 405 / 292 / 379, 24576
+// rows (384) 654 / 639 / 793, 32768 rows (512) 1000 / 1057 / 1365; 8 x 2048 rows (256) 64 / 52 / 73; 64 x 512 rows (512)
+// 49 / 66 / 86; D = 64: 8192 rows 164 / 90 / 64, 16384 rows 318 / 204 / 216; rows that see every key (a past block of a
+// ring): 2048 rows, 32 heads 72 / 76 / -, 700 rows, 24 heads 29 / 20 / 31.  A function of the extents only, so that every
+// layout and entry point of one problem gives the same bits; packed documents count as one sequence.
+inline int fwd_key_groups(int64_t B, int64_t S, int64_t Skv, int64_t off, int32_t Hq) {
+    const double heads = (double)Hq * (double)B, work[3] = {1., 1.08, 1.38}, fixed[3] = {9., 10., 10.5};
+    if (heads * (double)S > 1024. * kOrderTile) return 1;  // many rounds
+    int best = 1;
+    double best_time = 0.;
+    for (int i = 0; i < 3; ++i) {
+        const int64_t rows = kOrderTile >> i, ranks = (S + rows - 1) / rows;
+        const double per_key = 1.6 / 64. * work[i] / (1 << i);
+        const int64_t ramp_end = off < Skv ? (Skv - off) / rows : 0;  // tiles whose last row does not see every key yet
+        const double ramp = (double)(ramp_end < ranks ? ramp_end : ranks);
+        const double keys = ramp * (double)off + (double)rows * ramp * (ramp + 1.) / 2. + ((double)ranks - ramp) * (double)Skv;
+        const int64_t first = off + rows < Skv ? off + rows : Skv, last = off + S < Skv ? off + S : Skv;
+        const int64_t least = 32 << i;
+        const double t_first = per_key * (double)(first > least ? first : least) + fixed[i], t_last = per_key * (double)last + fixed[i];
+        const double rounds = heads * (double)ranks / (double)kComputeUnits;
+        const double shared = heads * (per_key * keys + fixed[i] * (double)ranks) / (double)kComputeUnits;
+        const double spread = 1.2 * (shared + t_first * ((double)(int64_t)(rounds + 0.999999) - rounds));
+        const double time = rounds > 1. && spread > t_last ? spread : t_last;
+        if (i == 0 || time < best_time) { best = 1 << i; best_time = time; }
+    }
+    return best;
 }
 // Row blocks of 32 query rows per wave of the dQ stage: 2 (256 rows per workgroup) unless the launch has few tiles
 // and is bound by the walk of the longest one.  With one block a wave's step takes 0.4 us instead of 0.75 and there are
@@ -173,7 +197,6 @@ __host__ __device__ inline int32_t dkdv_tile_steps(int32_t jt, int32_t S, int32_
 // unequal chunks: the short ones fill the end.  Backward with unequal / equal chunks, us, 4 heads of D = 128: 2048
 // rows 59 / 53, 3000 rows 79 / 69, 4096 rows 100 / 89; two rounds, 8192 rows, 233 / 250; four, 16384 rows, 786 / 839.
 constexpr int32_t kMaxEqualTiles = 64;
-constexpr int64_t kComputeUnits = 256;
 inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t nsplit, bool causal) {
     const int32_t n = order_tiles(Skv), G = Hq / Hkv, q_rows = 128 * dq_row_blocks(B, S, Hq);
     const int64_t workgroups = (int64_t)n * nsplit * Hkv * B + ((int64_t)S + q_rows - 1) / q_rows * Hq * B;

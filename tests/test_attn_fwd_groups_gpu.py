@@ -1,6 +1,6 @@
-"""The forward's key groups: how many of them share a workgroup follows from the number of 256-row tiles in the
-call (four up to 128, two up to 384, else one), so the same sequence is run alone and inside larger batches to
-reach all three, each against the oracle."""
+"""The forward's key groups: how many of them share a workgroup (one, two or four) follows from the extents of the call,
+fewer the more workgroups there are, so the same sequence is run alone and inside larger batches to reach all
+three, each against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ from gpu_util import LSE_MAX_ABS, check_o, dev_bf16, host_f64
 pytestmark = pytest.mark.gpu
 
 # batch entries (or heads) that put one-tile and two-tile sequences into each class, edges of the classes among them
-BATCHES = {1: [1, 128, 129, 384, 385], 2: [1, 64, 65, 192, 193]}
+BATCHES = {1: [1, 64, 65, 100, 128, 129, 385], 2: [1, 32, 33, 64, 65, 193]}
 
 
 @pytest.mark.parametrize("D", [64, 128])
