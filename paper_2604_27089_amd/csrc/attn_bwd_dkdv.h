@@ -58,7 +58,7 @@ struct DkdvParams {
     const int32_t* row_hi;
     const int32_t* order;  // packed documents: key tiles in the order workgroups take them (or null)
     RowMap qmap, kvmap;
-    int32_t B, several;  // several: more than one sequence
+    int32_t B, several;  // several: more than one sequence or KV head
     int32_t S, Skv, off, S_pad, Hq, Hkv, G, n_ktiles;  // S query rows, Skv keys; row i sees keys j <= i + off
     float scale, scale_log2;
 };
@@ -112,10 +112,10 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // earliest key tiles (most rows to visit) first; the workgroups that share a key tile are neighbours
-    // Order: chunks of one head together for a single sequence (they share the head's Q/dO stream through L2); with
-    // several sequences the batch entry and KV head vary fastest instead, so that every sequence's longest key
-    // tiles are dispatched before anybody's short ones (sequence by sequence, the last sequence's longest tile
-    // started when the grid was two thirds done: 16 x 4096 rows 710 -> 510 us).
+    // Order: with several sequences or KV heads those vary fastest, so that everybody's longest key tiles are
+    // dispatched before anybody's short ones (one after the other, the last one's longest tile started when the stage
+    // was two thirds done: 16 x 4096 rows 710 -> 510 us; 32768 rows of 8 heads, full attention, D = 64, whole backward
+    // 3944 -> 3246 us).
     const uint32_t n_chunks = (uint32_t)p.chunks.n_chunks, n_heads = (uint32_t)p.Hkv * (uint32_t)p.B;
     const int chunk_id = (int)(p.several ? wg / n_heads : wg % n_chunks);
     const int head_id = (int)(p.several ? wg % n_heads : wg / n_chunks);

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
 }
 
 // In which order the workgroups of the two stages go out (speed only: every order gives the same bits).  Each stage
-// hands out its longest walks first; the longest of each, in us, is about 0.95 per 32-key step of dQ and 1.5 per
+// hands out its longest walks first; the longest of each, in us, is about 0.95 per 32-key step of dQ (0.5 with one row block) and 1.5 per
 // 32-row step of dK/dV beyond fixed costs.
 //   Up to three rounds of the chip (768 workgroups; five with packed documents, whose work is uneven): the two are
 // merged by expected length, i.e. the stage with the longer walks leads until its remaining ones are as long as
@@ -58,24 +58,43 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
 // at D = 64 (longest 12877) 448 against 572 / 506.
 //   Beyond that whole stages follow each other: alternating mixes two access patterns that each share their stream
 // through L2 (131072 rows 47.0 ms against 41.9; 16384 rows of 8 heads 1572 us against 1490).  dQ first, since the
-// chunks of dK/dV are the finer ones to fill the end with, unless few long documents stand out so far that their
-// dK/dV walk would outlast all the rest (65536 rows in documents of 512, longest 4364: 497 us with dK/dV first, 625
-// with dQ first).
+// chunks of dK/dV are the finer ones to fill the end with (16 x 4096 rows 821 us against 838), unless a dK/dV walk
+// started last would outlast the rest (24576 rows, 8 query and 2 KV heads, dQ first 3434 us, dK/dV first 3238; 65536
+// rows in documents of 512, longest 4364, 625 and 497).
 inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixParams& p) {
     const int64_t longest = a.longest > 0 && a.longest < a.S ? a.longest : a.S;
     const double steps = (double)((longest + 31) / 32);
-    const double t_q = 0.95 * steps + 10., t_kv = 1.5 * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + 20.;
+    const int q_rows = 128 * dq_row_blocks(a.B, a.S, a.Hq);
+    const double q_step = q_rows == 128 ? 0.5 : 0.95;
+    const double t_q = q_step * steps + 10., t_kv = 1.5 * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + 20.;
     bool lead_q;
     int64_t lead;
     if (a.off >= a.Skv) {  // every row sees every key: equal workgroups within a stage, the longer ones first
-        lead_q = full_dq_time(a.Skv, 128 * dq_row_blocks(a.B, a.S, a.Hq)) > full_dkdv_time(a.S, a.Hq / a.Hkv, a.chunks.nsplit);
+        lead_q = full_dq_time(a.Skv, q_rows, a.D) > full_dkdv_time(a.S, a.Hq / a.Hkv, a.chunks.nsplit, a.D);
         lead = lead_q ? n_q : n_kv;
     } else if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
+        // walks fall evenly from the longest to the shortest (a short document's, or that of the first rows resp.
+        // the last keys)
+        double short_q = 10., short_kv = 20.;
+        if (!a.row_lo) {
+            short_q += q_step * (double)((a.off + q_rows < a.Skv ? a.off + q_rows : a.Skv) / 32);
+            short_kv = a.chunks.len > 0 ? t_kv : short_kv + 1.5 * dkdv_tile_steps(order_tiles(a.Skv) - 1, a.S, a.off, a.Hq / a.Hkv) / a.chunks.nsplit;
+        }
         lead_q = t_q >= t_kv;
-        lead = (int64_t)(lead_q ? n_q * (1. - t_kv / t_q) : n_kv * (1. - t_q / t_kv));
+        const double longer = lead_q ? t_q : t_kv, other = lead_q ? t_kv : t_q, least = lead_q ? short_q : short_kv;
+        const double share = longer > least ? (longer - other) / (longer - least) : 1.;
+        lead = (int64_t)((double)(lead_q ? n_q : n_kv) * (share < 1. ? share : 1.));
     } else {
-        const int64_t mean = a.S / (a.n_docs > 0 ? a.n_docs : 1);
-        lead_q = n_kv * mean >= 256 * longest;
+        // dQ first unless the longest dK/dV walk, started last, would outlast the rest of its stage
+        double kv_all;  // dK/dV work per compute unit; packed documents: as if all were of the mean length
+        if (a.row_lo) {
+            kv_all = t_kv * (double)n_kv * (double)(a.S / (a.n_docs > 0 ? a.n_docs : 1)) / (double)longest / (double)kComputeUnits;
+        } else {
+            const int32_t tiles = order_tiles(a.Skv), G = a.Hq / a.Hkv;
+            const double mean = ((double)dkdv_tile_steps(0, a.S, a.off, G) + (double)dkdv_tile_steps(tiles - 1, a.S, a.off, G)) / 2.;
+            kv_all = (1.5 * mean * tiles * (double)a.Hkv * a.B + 20. * (double)n_kv) / (double)kComputeUnits;
+        }
+        lead_q = t_kv <= kv_all;
         lead = lead_q ? n_q : n_kv;
     }
     p.lead_is_q = lead_q;
@@ -105,7 +124,7 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
         k.n_ktiles = (a.Skv + dkdv::BNK - 1) / dkdv::BNK;
         k.chunks = a.chunks; k.part = a.dkdv_part;
         k.scale = a.scale; k.scale_log2 = a.scale * kLog2e;
-        k.B = a.B; k.several = a.B > 1;
+        k.B = a.B; k.several = a.B > 1 || a.Hkv > 1;
         if (kv && (k.chunks.nsplit < 1 || (k.chunks.nsplit > 1 && !k.part))) return SP_ERR_WORKSPACE;
     }
     {

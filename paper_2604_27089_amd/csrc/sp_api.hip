@@ -112,8 +112,8 @@ sp_status run_dense_bwd(const BwdBuffers& t, int64_t B, int64_t Sq, int64_t Skv,
     a.scale = resolve_scale(softmax_scale, D);
     a.stages = stages;
     int32_t nsplit = sp::dkdv_split_count(B, Sq, Skv, Hq, Hkv);
-    if (off >= Skv) nsplit = sp::dkdv_full_splits(B, Sq, Skv, Hq, Hkv, nsplit);
-    a.chunks = sp::dkdv_chunks(B, a.S, a.Skv, a.off, Hq, Hkv, nsplit, off < Skv);
+    if (off >= Skv) nsplit = sp::dkdv_full_splits(B, Sq, Skv, Hq, Hkv, D, nsplit);
+    a.chunks = sp::dkdv_chunks(B, a.S, a.Skv, a.off, Hq, Hkv, D, nsplit, off < Skv);
     a.dkdv_part = a.chunks.nsplit > 1 ? (float*)((char*)a.aux + 2 * aux_bytes(B, Sq, Hq)) : nullptr;
     return sp::launch_attn_bwd(a, (hipStream_t)hip_stream);
 }
@@ -387,7 +387,7 @@ sp_status sp_attn_varlen_bwd(const void* q, const void* k, const void* v, const 
     a.stages = SP_BWD_STAGE_ALL;
     a.n_docs = n_docs; a.longest = max_seqlen;
     // the hint only shapes the work split; one document is one causal sequence
-    a.chunks = sp::dkdv_chunks(1, a.S, a.S, 0, Hq, Hkv, sp::dkdv_split_count(1, T, T, Hq, Hkv, max_seqlen), n_docs == 1);
+    a.chunks = sp::dkdv_chunks(1, a.S, a.S, 0, Hq, Hkv, D, sp::dkdv_split_count(1, T, T, Hq, Hkv, max_seqlen), n_docs == 1);
     a.dkdv_part = a.chunks.nsplit > 1 ? (float*)((char*)row_hi + bounds_bytes(T) + order_bytes(T)) : nullptr;
     return sp::launch_attn_bwd(a, s);
 }

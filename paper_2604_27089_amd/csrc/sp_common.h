@@ -188,6 +188,39 @@ __host__ __device__ inline int32_t dkdv_tile_steps(int32_t jt, int32_t S, int32_
     const int32_t j0 = jt * kOrderTile;
     return ((S + 31) / 32 - (j0 > off ? j0 - off : 0) / 32) * G;
 }
+// Where the work of every tile is known on the host (one document per sequence), there are several sequences or KV
+// heads and at most as many key tiles as compute units, the number of chunks follows from an estimate of when dK/dV and dQ, launched together, are done:
+// not before the longest workgroup of either, nor before all work shared out evenly, plus an eighth of the longest
+// dK/dV workgroup for the uneven end and the reduction of the partial sums (us per step: 1.5 for dK/dV, 0.95 or 0.5 for dQ with two or one row blocks, a third less at D = 64;
+// 20 and 10 us per workgroup; 12 TB/s of partial sums, which stay in the memory-side cache).  Of 1 .. `most`, the
+// count that the rule above gives and the workspace is sized for.  Backward, rule / estimate (with the order of
+// dispatch of attn_bwd_matrix.h), us: 16 x 1024 rows of 4 heads, full attention, 129 / 96; 32 x 2048 rows, 4 query heads
+// and one KV head, 499 / 461; 4096 rows, 32 and 8 heads, 566 / 436; 2500 rows, the same, 280 / 198.  For a single KV head
+// the estimate gives no more than the rule (16384 rows 765 / 765 us, D = 64 458 / 467; 65536 rows 10.8 / 11.0 ms).
+inline int32_t dkdv_causal_splits(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t D, int32_t most) {
+    const int32_t tiles = order_tiles(Skv), G = Hq / Hkv, q_rows = 128 * dq_row_blocks(B, S, Hq);
+    const double head_b = (double)Hkv * (double)B, scale = D == 64 ? 2. / 3. : 1.;
+    double steps = 0.;
+    for (int32_t t = 0; t < tiles; ++t) steps += dkdv_tile_steps(t, S, off, G);
+    const double longest = dkdv_tile_steps(0, S, off, G);
+    const double ranks = (double)(((int64_t)S + q_rows - 1) / q_rows), n_q = ranks * Hq * (double)B;
+    const double q_step = scale * (q_rows == 128 ? 0.5 : 0.95), q_last = (double)((Skv + 31) / 32), q_first = (double)((off < Skv ? off : Skv) / 32);
+    const double t_q = q_step * q_last + 10., work_q = n_q * (q_step * (q_first + q_last) / 2. + 10.);
+    int32_t best = 1;
+    double best_time = 0.;
+    for (int32_t n = 1; n <= most; ++n) {
+        const double jobs = (double)tiles * n * head_b;
+        double t_kv = scale * 1.5 * longest / n + 20.;
+        if (n > 1 && jobs + n_q <= (double)kComputeUnits) t_kv = scale * 1.5 * 1.1 * steps * head_b / jobs + 20.;  // equal chunks
+        const double shared = (scale * 1.5 * steps * head_b + 20. * jobs + work_q) / (double)kComputeUnits + 10.;
+        double time = t_kv > t_q ? t_kv : t_q;
+        if (shared > time) time = shared;
+        time += t_kv / 8.;
+        if (n > 1) time += 4. + (double)n * (double)B * Skv * Hkv * D * 16. / 12e6;
+        if (n == 1 || time < best_time) { best = n; best_time = time; }
+    }
+    return best;
+}
 // Equal chunks.  A causal key tile's steps fall linearly from the first tile to the last, so the same number of
 // chunks for every tile makes the first tile's twice as long as the mean.  A launch whose workgroups all run at once
 // (dK/dV and dQ together at most one per compute unit) ends with those, so there, if the work of each tile is known
@@ -197,9 +230,11 @@ __host__ __device__ inline int32_t dkdv_tile_steps(int32_t jt, int32_t S, int32_
 // unequal chunks: the short ones fill the end.  Backward with unequal / equal chunks, us, 4 heads of D = 128: 2048
 // rows 59 / 53, 3000 rows 79 / 69, 4096 rows 100 / 89; two rounds, 8192 rows, 233 / 250; four, 16384 rows, 786 / 839.
 constexpr int32_t kMaxEqualTiles = 64;
-inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t nsplit, bool causal) {
+inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t D, int32_t nsplit, bool causal) {
     const int32_t n = order_tiles(Skv), G = Hq / Hkv, q_rows = 128 * dq_row_blocks(B, S, Hq);
-    const int64_t workgroups = (int64_t)n * nsplit * Hkv * B + ((int64_t)S + q_rows - 1) / q_rows * Hq * B;
+    const int64_t n_q = ((int64_t)S + q_rows - 1) / q_rows * Hq * B;
+    if (causal && (int64_t)Hkv * B > 1 && (int64_t)n * Hkv * B <= kComputeUnits) nsplit = dkdv_causal_splits(B, S, Skv, off, Hq, Hkv, D, nsplit);
+    const int64_t workgroups = (int64_t)n * nsplit * Hkv * B + n_q;
     DkdvChunks c{nsplit, 0, n * nsplit};
     if (!causal || workgroups > kComputeUnits || nsplit < 2 || n < 2 || n > kMaxEqualTiles || (int64_t)S * G > (int64_t)1 << 30) return c;
     int64_t total = 0;
@@ -216,6 +251,46 @@ inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, in
         }
         if (rows <= (int64_t)nsplit * Skv) return DkdvChunks{nsplit, (int32_t)len, chunks};
     }
+}
+// When the chip is done with n1 workgroups of t1 us followed by n2 of t2 us, one per compute unit at a time.
+inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
+    // after the first stage `late` units are free one of its workgroups later than the others
+    const int64_t late = n1 % kComputeUnits, early = kComputeUnits - late;
+    const double free_early = t1 * (double)(n1 / kComputeUnits), free_late = late ? free_early + t1 : free_early;
+    if (n2 == 0) return free_late;
+    const double fluid = ((double)n2 * t2 + (double)early * free_early + (double)late * free_late) / (double)kComputeUnits;
+    double end = 0.;
+    for (int side = 0; side < 2; ++side) {  // the end is a whole number of workgroups after one of the two
+        const double from = side ? free_late : free_early;
+        int64_t k = fluid > from ? (int64_t)((fluid - from) / t2) : 0;
+        double t = 0.;
+        for (;; ++k) {
+            t = from + (double)k * t2 + 1e-6;
+            const int64_t done = early * (int64_t)((t - free_early) / t2) + (t > free_late ? late * (int64_t)((t - free_late) / t2) : 0);
+            if (t >= free_late && done >= n2) break;
+        }
+        if (side == 0 || t < end) end = t;
+    }
+    return end;
+}
+// What a workgroup of the two matrix stages takes where every row sees every key, in us.
+inline double full_dq_time(int64_t Skv, int64_t q_rows, int32_t D) { return (D == 64 ? 2. / 3. : 1.) * 0.95 * (double)((Skv + 31) / 32) * (double)q_rows / 256. + 10.; }
+inline double full_dkdv_time(int64_t S, int32_t G, int32_t nsplit, int32_t D) { return (D == 64 ? 2. / 3. : 1.) * 1.5 * (double)((S + 31) / 32 * G) / nsplit + 20.; }
+// Work split where every row sees every key (a block from the past in a ring schedule): all workgroups of a stage are
+// equally long, so a round that is not full wastes a part of a whole workgroup.  Of 1 .. `most` chunks per tile (what
+// the workspace has room for) the one is taken with which the two stages, the longer workgroups first, end soonest.
+inline int32_t dkdv_full_splits(int64_t B, int64_t S, int64_t Skv, int32_t Hq, int32_t Hkv, int32_t D, int32_t most) {
+    const int64_t tiles = (Skv + 255) / 256 * Hkv * B, q_rows = 128 * dq_row_blocks(B, S, Hq);
+    const int64_t n_q = (S + q_rows - 1) / q_rows * Hq * B;
+    const double t_q = full_dq_time(Skv, q_rows, D);
+    int32_t best = 1;
+    double best_end = 0.;
+    for (int32_t n = 1; n <= most; ++n) {
+        const double t = full_dkdv_time(S, Hq / Hkv, n, D);
+        const double end = t >= t_q ? two_stage_end(tiles * n, t, n_q, t_q) : two_stage_end(n_q, t_q, tiles * n, t);
+        if (n == 1 || end < best_end) { best = n; best_end = end; }
+    }
+    return best;
 }
 inline size_t dkdv_part_bytes(int64_t B, int64_t Skv, int32_t Hkv, int32_t D, int32_t nsplit) {
     return nsplit > 1 ? (size_t)2 * nsplit * B * Skv * Hkv * D * sizeof(float) : 0;

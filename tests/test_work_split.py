@@ -1,0 +1,81 @@
+"""The host-side rules that cut the attention work into workgroups, compiled for the CPU and checked over many extents:
+the partial sums of the dK/dV chunks fit the room the workspace query leaves for them, every step of every key tile
+belongs to exactly one chunk, and the counts stay inside what the kernels are built for."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SRC = r'''
+#define __HIP_PLATFORM_AMD__ 1
+#include "sp_common.h"
+#include <cstdio>
+#include <cstdlib>
+using namespace sp;
+static uint64_t seed = 12345;
+static int64_t pick(int64_t lo, int64_t hi) { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return lo + (int64_t)((seed >> 33) % (uint64_t)(hi - lo + 1)); }
+#define CHECK(c) do { if (!(c)) { printf("failed: %s (B %ld S %ld Skv %ld off %ld Hq %d Hkv %d D %d)\n", #c, (long)B, (long)S, (long)Skv, (long)off, Hq, Hkv, D); return 1; } } while (0)
+int main() {
+    long equal = 0, full = 0, cut = 0;
+    for (int it = 0; it < 200000; ++it) {
+        const int64_t B = it % 3 ? 1 : pick(1, 40);
+        int64_t S = it % 5 ? pick(1, 3000) : pick(1, 140000), Skv = S, off = 0;
+        const int kind = it % 7;
+        if (kind == 1) off = pick(0, S);
+        if (kind == 2) { Skv = pick(1, 2 * S); off = Skv > S ? Skv - S + pick(0, 50) : pick(0, Skv); }
+        if (kind == 3) { Skv = pick(1, 2 * S); off = Skv; }
+        if (off > Skv) off = Skv;
+        if (Skv > S + off) continue;
+        const int32_t Hkv = (int32_t)pick(1, 8), G = (int32_t)pick(1, 8), Hq = Hkv * G, D = it & 1 ? 64 : 128;
+        const int32_t rule = dkdv_split_count(B, S, Skv, Hq, Hkv);
+        CHECK(rule >= 1 && rule <= 8);
+        int32_t nsplit = rule;
+        if (off >= Skv) { nsplit = dkdv_full_splits(B, S, Skv, Hq, Hkv, D, rule); ++full; }
+        CHECK(nsplit >= 1 && nsplit <= rule);
+        const DkdvChunks c = dkdv_chunks(B, (int32_t)S, (int32_t)Skv, (int32_t)off, Hq, Hkv, D, nsplit, off < Skv);
+        CHECK(c.nsplit >= 1 && c.nsplit <= nsplit);
+        if (c.nsplit < rule) ++cut;
+        const int32_t tiles = order_tiles(Skv);
+        if (c.len == 0) CHECK(c.n_chunks == tiles * c.nsplit);
+        else {
+            ++equal;
+            CHECK(c.nsplit > 1 && tiles <= kMaxEqualTiles && c.len % 4 == 0);
+            int64_t rows = 0, n = 0;
+            for (int32_t t = 0; t < tiles; ++t) {
+                const int32_t steps = dkdv_tile_steps(t, (int32_t)S, (int32_t)off, G), k = (steps + c.len - 1) / c.len;
+                CHECK(steps >= 1 && k >= 1);
+                const int64_t keys = Skv - (int64_t)t * kOrderTile;
+                n += k; rows += k * (keys < kOrderTile ? keys : kOrderTile);
+            }
+            CHECK(n == c.n_chunks && rows <= (int64_t)c.nsplit * Skv);
+        }
+        CHECK(dkdv_part_bytes(B, Skv, Hkv, D, c.nsplit) <= dkdv_part_bytes(B, Skv, Hkv, D, rule));
+        const int ks = fwd_key_groups(B, S, Skv, off, Hq);
+        CHECK(ks == 1 || ks == 2 || ks == 4);
+        CHECK(dq_row_blocks(B, S, Hq) == 1 || dq_row_blocks(B, S, Hq) == 2);
+    }
+    // the most extreme extents end quickly and do not overflow into nonsense
+    const int64_t B = 65535, S = 32767, Skv = S, off = S; const int32_t Hq = 65535, Hkv = 1, D = 128;
+    CHECK(dkdv_full_splits(B, S, Skv, Hq, Hkv, D, 8) >= 1);
+    CHECK(fwd_key_groups(1, (int64_t)1 << 30, (int64_t)1 << 30, 0, 1) == 1);
+    // a round and a half of equal workgroups takes two; jobs that fit beside a late round cost nothing
+    if (two_stage_end(384, 10., 0, 1.) < 19.9 || two_stage_end(128, 10., 256, 5.) > 10.1) { printf("two_stage_end\n"); return 1; }
+    printf("ok %ld %ld %ld\n", equal, full, cut);
+    return equal > 100 && full > 100 && cut > 100 ? 0 : 2;
+}
+'''
+
+
+def test_chunks_fit_and_cover(tmp_path):
+    src, exe = tmp_path / "split.cpp", tmp_path / "split"
+    src.write_text(SRC)
+    inc = os.path.join(ROOT, "paper_2604_27089_amd", "csrc")
+    r = subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-I", inc, "-I", "/opt/rocm/include", str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    if r.returncode != 0 and "hip" in r.stderr and "No such file" in r.stderr:
+        pytest.skip("HIP headers are not installed")
+    assert r.returncode == 0, r.stderr[-3000:]
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
