@@ -3,7 +3,7 @@
 // dK/dV (attn_bwd_dkdv.h) and dQ (attn_bwd_dq.h) read the same inputs and write different outputs, so one launch
 // holds the workgroups of both.  Either stage alone ends with compute units idle (each unit holds one workgroup,
 // and the longest walk of a stage is twice the mean or more), and a short problem fills the chip with neither.
-// Whole backward, one launch against one per stage (with equal kernels, 4 query heads, D = 128): 512 rows 71 -> 35
+// Whole backward, one launch against one per stage (with equal programs, 4 query heads, D = 128): 512 rows 71 -> 35
 // us, 4096 rows 218 -> 124, 8192 398 -> 267, 16384 890 -> 753, 32768 2.80 -> 2.77 ms, 16 x 4096 rows 857 -> 815 us.
 // Both programs keep a wave's whole register file, so sharing a kernel costs neither of them occupancy.
 #pragma once
@@ -54,8 +54,8 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
 //   Up to three rounds of the chip (768 workgroups; five with packed documents, whose work is uneven): the two are
 // merged by expected length, i.e. the stage with the longer walks leads until its remaining ones are as long as
 // the other's, and from there they alternate.  Measured against dK/dV first / dQ first, us: 8192 rows of 5 heads,
-// full attention, 335 against 343 / 361, 16384 rows, 4 heads, 797 against 899 / 799, packed documents of 32768 rows
-// at D = 64 (longest 12877) 448 against 572 / 506.
+// full attention, 286 against 345 / 284, 16384 rows, 4 heads, 780 against 886 / 780, 64 x 512 rows 130 against 132 / 139,
+// packed documents of 32768 rows at D = 64 (longest 12877) 448 against 572 / 506.
 //   Beyond that whole stages follow each other: alternating mixes two access patterns that each share their stream
 // through L2 (131072 rows 47.0 ms against 41.9; 16384 rows of 8 heads 1572 us against 1490).  dQ first, since the
 // chunks of dK/dV are the finer ones to fill the end with (16 x 4096 rows 821 us against 838), unless a dK/dV walk

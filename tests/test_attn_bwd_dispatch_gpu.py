@@ -11,6 +11,8 @@ from oracle import ref_numpy as rn
 from paper_2604_27089_amd import binding as sp
 from paper_2604_27089_amd import synth
 from gpu_util import GRAD_REL_L2, dev_bf16, grad_err, guarded, host_f64
+from test_padded_build_gpu import run, same_bits
+from paper_2604_27089_amd import build as spbuild
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +84,22 @@ def test_equal_chunks(Sq, Skv, off, Hq, Hkv, D):
         assert grad_err(host_f64(got[0]), ref, name) <= GRAD_REL_L2, (name, Sq, Skv, off, Hq, Hkv, D)
     again = sp.sp_attn_block_bwd(q, k, v, o, lse, do, off)
     assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(again, (dq, dk, dv)))
+
+
+# the hand-scheduled dQ program with two row blocks per wave runs above 128 tiles of 256 rows: there, too, the build
+# with every wait spelled out must give the same bits
+@pytest.mark.parametrize("B,S,Hq,Hkv,D", [(1, 777, 36, 9, 128), (3, 513, 20, 5, 64), (1, 5000, 8, 1, 128)])
+def test_padded_build_two_row_blocks(B, S, Hq, Hkv, D):
+    fast, padded = sp.lib(), sp.open_library(spbuild.LIB_PADDED)
+    q, k, v, do = (dev_bf16(t) for t in synth.attn_inputs(S + D, S, Hq, Hkv, D, B))
+    same_bits(run(fast, q, k, v, do), run(padded, q, k, v, do), f"B={B} S={S} {Hq}q/{Hkv}kv D={D}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_padded_build_two_row_blocks_packed(D):
+    fast, padded = sp.lib(), sp.open_library(spbuild.LIB_PADDED)
+    lengths = [130, 0, 64, 1, 700, 63, 129, 2040, 8, 30, 2, 1500]
+    cu = synth.cu_seqlens_from_lengths(lengths)
+    q, k, v, do = (dev_bf16(t[0]) for t in synth.attn_inputs(78, int(cu[-1]), 9, 3, D))
+    cud = torch.from_numpy(cu).cuda()
+    same_bits(run(fast, q, k, v, do, cud), run(padded, q, k, v, do, cud), f"packed documents D={D}")
