@@ -31,7 +31,7 @@
 // sum and O, and the groups' results are merged through LDS at the end.  The
 // phases stay as they are: with KS = 2 group A and group B simply walk different
 // tiles.  4096 rows, 4 heads of D = 128: 106 us with one group, 49 with four
-// (350 TFLOP/s); fwd_key_groups() has the rule and more figures.
+// (350 TFLOP/s); fwd_key_groups() and packed_key_groups() have the rules and more figures.
 #include "attn_common.h"
 #include "sp_common.h"
 
@@ -432,7 +432,7 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
 
 template <int D, bool VARLEN>
 sp_status launch_groups(const AttnArgs& a, hipStream_t st) {
-    switch (fwd_key_groups(a.B, a.S, a.Skv, a.off, a.Hq)) {
+    switch (VARLEN ? packed_key_groups(a.S, a.n_docs, a.Hq) : fwd_key_groups(a.B, a.S, a.Skv, a.off, a.Hq)) {
         case 4: return launch<D, VARLEN, 4>(a, st);
         case 2: return launch<D, VARLEN, 2>(a, st);
         default: return launch<D, VARLEN, 1>(a, st);

@@ -258,7 +258,7 @@ sp_status run_varlen_fwd(const void* q, const void* k, const void* v, void* o, f
     if (st != SP_OK) return st;
     a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
     a.B = 1; a.S = (int32_t)T; a.Hq = Hq; a.Hkv = Hkv; a.D = D;
-    a.Skv = a.S; a.off = 0;
+    a.Skv = a.S; a.off = 0; a.n_docs = n_docs;
     attention_side_maps(a);
     a.scale = resolve_scale(softmax_scale, D);
     return sp::launch_attn_fwd(a, s);

@@ -68,9 +68,9 @@ int main() {
 '''
 
 
-def test_chunks_fit_and_cover(tmp_path):
+def run_on_host(tmp_path, text):
     src, exe = tmp_path / "split.cpp", tmp_path / "split"
-    src.write_text(SRC)
+    src.write_text(text)
     inc = os.path.join(ROOT, "paper_2604_27089_amd", "csrc")
     r = subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-I", inc, "-I", "/opt/rocm/include", str(src), "-o", str(exe)],
                        capture_output=True, text=True)
@@ -79,3 +79,39 @@ def test_chunks_fit_and_cover(tmp_path):
     assert r.returncode == 0, r.stderr[-3000:]
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_chunks_fit_and_cover(tmp_path):
+    run_on_host(tmp_path, SRC)
+
+
+PACKED = r'''
+#define __HIP_PLATFORM_AMD__ 1
+#include "sp_common.h"
+#include <cstdio>
+using namespace sp;
+int main() {
+    int bad = 0;
+    // packed rows, documents, query heads; measured with one group against two or four
+    const int one[][3] = {{14272, 56, 4}, {17615, 35, 4}, {5760, 23, 8}, {2482, 10, 20}, {9399, 10, 8}, {10304, 11, 8}, {22338, 44, 4}, {65536, 128, 4}};
+    const int more[][3] = {{4032, 13, 4}, {15168, 5, 1}, {6528, 7, 4}, {763, 7, 4}, {10007, 2, 3}};
+    for (const auto& x : one) if (packed_key_groups(x[0], x[1], x[2]) != 1) { printf("%d rows, %d documents, %d heads: too many groups\n", x[0], x[1], x[2]); ++bad; }
+    for (const auto& x : more) if (packed_key_groups(x[0], x[1], x[2]) < 2) { printf("%d rows, %d documents, %d heads: too few groups\n", x[0], x[1], x[2]); ++bad; }
+    uint64_t seed = 7;
+    for (int it = 0; it < 100000; ++it) {
+        seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+        const int64_t T = 1 + (int64_t)((seed >> 33) % 70000);
+        const int32_t Hq = 1 + (int32_t)((seed >> 20) % 40), n = 1 + (int32_t)((seed >> 40) % (it & 1 ? 64 : 100000));
+        const int ks = packed_key_groups(T, n, Hq), whole = fwd_key_groups(1, T, T, 0, Hq);
+        if (ks != 1 && ks != 2 && ks != 4) ++bad;
+        if (n == 1 && ks != whole) ++bad;                                        // one document is one sequence
+        if ((T + n - 1) / n < 64 && Hq * ((T + 255) / 256) > 512 && ks != 1) ++bad;  // short walks, more than two rounds
+    }
+    return bad ? 1 : 0;
+}
+'''
+
+
+def test_packed_documents_get_groups_for_their_own_length(tmp_path):
+    """Key groups of the forward follow the documents' walks, not the length of the whole batch."""
+    run_on_host(tmp_path, PACKED)
