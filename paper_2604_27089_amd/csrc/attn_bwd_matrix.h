@@ -51,6 +51,8 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
 // In which order the workgroups of the two stages go out (speed only: every order gives the same bits).  Each stage
 // hands out its longest walks first; the longest of each, in us, is about 0.95 per 32-key step of dQ (0.5 with one row block) and 1.5 per
 // 32-row step of dK/dV beyond fixed costs.
+//   Even walks beyond one round (even_walks()): the stage with the longer workgroups first, the other fills its last
+// round.
 //   Up to three rounds of the chip (768 workgroups; five with packed documents, whose work is uneven): the two are
 // merged by expected length, i.e. the stage with the longer walks leads until its remaining ones are as long as
 // the other's, and from there they alternate.  Measured against dK/dV first / dQ first, us: 8192 rows of 5 heads,
@@ -69,8 +71,8 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     const double t_q = q_step * steps + 10., t_kv = 1.5 * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + 20.;
     bool lead_q;
     int64_t lead;
-    if (a.off >= a.Skv) {  // every row sees every key: equal workgroups within a stage, the longer ones first
-        lead_q = full_dq_time(a.Skv, q_rows, a.D) > full_dkdv_time(a.S, a.Hq / a.Hkv, a.chunks.nsplit, a.D);
+    if (!a.row_lo && (a.off >= a.Skv || (even_walks(a.S, a.Skv, a.off) && n_kv + n_q > kComputeUnits))) {  // the longer workgroups first
+        lead_q = even_dq_time(a.S, a.Skv, a.off, q_rows, a.D) > even_dkdv_time(a.S, a.Skv, a.off, a.Hq / a.Hkv, a.chunks.nsplit, a.D);
         lead = lead_q ? n_q : n_kv;
     } else if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
         // walks fall evenly from the longest to the shortest (a short document's, or that of the first rows resp.

@@ -111,9 +111,7 @@ sp_status run_dense_bwd(const BwdBuffers& t, int64_t B, int64_t Sq, int64_t Skv,
     a.qmap = qmap; a.kvmap = kvmap;
     a.scale = resolve_scale(softmax_scale, D);
     a.stages = stages;
-    int32_t nsplit = sp::dkdv_split_count(B, Sq, Skv, Hq, Hkv);
-    if (off >= Skv) nsplit = sp::dkdv_full_splits(B, Sq, Skv, Hq, Hkv, D, nsplit);
-    a.chunks = sp::dkdv_chunks(B, a.S, a.Skv, a.off, Hq, Hkv, D, nsplit, off < Skv);
+    a.chunks = sp::dense_chunks(B, a.S, a.Skv, a.off, Hq, Hkv, D);
     a.dkdv_part = a.chunks.nsplit > 1 ? (float*)((char*)a.aux + 2 * aux_bytes(B, Sq, Hq)) : nullptr;
     return sp::launch_attn_bwd(a, (hipStream_t)hip_stream);
 }

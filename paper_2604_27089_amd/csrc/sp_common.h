@@ -212,6 +212,11 @@ inline int32_t dkdv_split_count(int64_t B, int64_t S, int64_t Skv, int32_t Hq, i
     if (n > cap) n = cap;
     return n < 1 ? 1 : (int32_t)n;
 }
+// What the kernel that adds the chunks' partial sums takes, in us: written once and read once at 12 TB/s (they stay in the
+// memory-side cache), and a launch.
+inline double dkdv_reduce_time(int64_t B, int64_t Skv, int32_t Hkv, int32_t D, int32_t nsplit) {
+    return 4. + (double)nsplit * (double)B * (double)Skv * Hkv * D * 16. / 12e6;
+}
 // (head, row tile) steps of the 256 keys of tile jt when the whole sequence is one document
 __host__ __device__ inline int32_t dkdv_tile_steps(int32_t jt, int32_t S, int32_t off, int32_t G) {
     const int32_t j0 = jt * kOrderTile;
@@ -245,7 +250,7 @@ inline int32_t dkdv_causal_splits(int64_t B, int32_t S, int32_t Skv, int32_t off
         double time = t_kv > t_q ? t_kv : t_q;
         if (shared > time) time = shared;
         time += t_kv / 8.;
-        if (n > 1) time += 4. + (double)n * (double)B * Skv * Hkv * D * 16. / 12e6;
+        if (n > 1) time += dkdv_reduce_time(B, Skv, Hkv, D, n);
         if (n == 1 || time < best_time) { best = n; best_time = time; }
     }
     return best;
@@ -281,13 +286,15 @@ inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, in
         if (rows <= (int64_t)nsplit * Skv) return DkdvChunks{nsplit, (int32_t)len, chunks};
     }
 }
-// When the chip is done with n1 workgroups of t1 us followed by n2 of t2 us, one per compute unit at a time.
-inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
+// When a part of the chip with kEngineUnits units is done with n1 workgroups of t1 us followed by n2 of t2 us, one per unit
+// at a time.
+constexpr int64_t kEngines = 32, kEngineUnits = kComputeUnits / kEngines;  // shader engines
+inline double engine_end(int64_t n1, double t1, int64_t n2, double t2) {
     // after the first stage `late` units are free one of its workgroups later than the others
-    const int64_t late = n1 % kComputeUnits, early = kComputeUnits - late;
-    const double free_early = t1 * (double)(n1 / kComputeUnits), free_late = late ? free_early + t1 : free_early;
+    const int64_t late = n1 % kEngineUnits, early = kEngineUnits - late;
+    const double free_early = t1 * (double)(n1 / kEngineUnits), free_late = late ? free_early + t1 : free_early;
     if (n2 == 0) return free_late;
-    const double fluid = ((double)n2 * t2 + (double)early * free_early + (double)late * free_late) / (double)kComputeUnits;
+    const double fluid = ((double)n2 * t2 + (double)early * free_early + (double)late * free_late) / (double)kEngineUnits;
     double end = 0.;
     for (int side = 0; side < 2; ++side) {  // the end is a whole number of workgroups after one of the two
         const double from = side ? free_late : free_early;
@@ -302,24 +309,65 @@ inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
     }
     return end;
 }
-// What a workgroup of the two matrix stages takes where every row sees every key, in us.
-inline double full_dq_time(int64_t Skv, int64_t q_rows, int32_t D) { return (D == 64 ? 2. / 3. : 1.) * 0.95 * (double)((Skv + 31) / 32) * (double)q_rows / 256. + 10.; }
-inline double full_dkdv_time(int64_t S, int32_t G, int32_t nsplit, int32_t D) { return (D == 64 ? 2. / 3. : 1.) * 1.5 * (double)((S + 31) / 32 * G) / nsplit + 20.; }
-// Work split where every row sees every key (a block from the past in a ring schedule): all workgroups of a stage are
-// equally long, so a round that is not full wastes a part of a whole workgroup.  Of 1 .. `most` chunks per tile (what
-// the workspace has room for) the one is taken with which the two stages, the longer workgroups first, end soonest.
-inline int32_t dkdv_full_splits(int64_t B, int64_t S, int64_t Skv, int32_t Hq, int32_t Hkv, int32_t D, int32_t most) {
+// The same for the whole chip.  Workgroups are dealt to the engines in turn and stay there, so a stage that would just fit
+// beside the other over the whole chip does not if one engine is a unit short: 224 workgroups of dQ (two rounds on the 116
+// units that 140 of dK/dV leave) took a third round, 553 us of dK/dV alone, 688 together.
+inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
+    const int64_t n = n1 + n2, kinds[4] = {0, (n1 + kEngines - 1) % kEngines, n1 % kEngines, (n + kEngines - 1) % kEngines};  // engines of every kind
+    double end = 0.;
+    for (const int64_t e : kinds) {
+        const int64_t first = n1 > e ? (n1 - e + kEngines - 1) / kEngines : 0, both = n > e ? (n - e + kEngines - 1) / kEngines : 0;
+        const double t = engine_end(first, t1, both - first, t2);
+        if (t > end) end = t;
+    }
+    return end;
+}
+// Even walks: the shortest walk of either stage is at least half the longest (a block from the past in a ring schedule, or
+// any causal offset from about the middle of the keys on).  Beyond one round of the chip such workgroups end in whole
+// rounds, like those of a block that hides nothing, and the estimates for a causal ramp do not see that: with them an
+// offset one below "hides nothing" got another chunk count and order, and times up to 17 % above those of one stage
+// after the other (backward, us, one stage after the other / causal estimate / this rule: 7039 rows of 16 and 4 heads,
+// D = 64, offset 7038, 685 / 805 / 678; 9224 rows, 20 and 5 heads, offset 9106, 1430 / 1602 / 1392).  1356 shapes with
+// offsets above half: 0.690 of the time of one stage after the other with the causal estimates, 17 of them more than 3 %
+// above it; with this rule 0.671 and 4 (5 % in one round of dK/dV beside one of dQ: 5860 rows of 8 heads 435 / 456).
+inline bool even_walks(int64_t S, int64_t Skv, int64_t off) { return 2 * off >= Skv && 2 * (Skv - off) <= S; }
+// The share of the (row, key) pairs that are visible there, and what a workgroup of either stage takes on average, in us.
+inline double even_share(int64_t S, int64_t Skv, int64_t off) {
+    const double hidden = off < Skv ? (double)(Skv - off) : 0.;
+    return 1. - hidden * hidden / (2. * (double)S * (double)Skv);
+}
+inline double even_dq_time(int64_t S, int64_t Skv, int64_t off, int64_t q_rows, int32_t D) {
+    return (D == 64 ? 2. / 3. : 1.) * 0.95 * (double)((Skv + 31) / 32) * even_share(S, Skv, off) * (double)q_rows / 256. + 10.;
+}
+inline double even_dkdv_time(int64_t S, int64_t Skv, int64_t off, int32_t G, int32_t nsplit, int32_t D) {
+    return (D == 64 ? 2. / 3. : 1.) * 1.5 * (double)((S + 31) / 32 * G) * even_share(S, Skv, off) / nsplit + 20.;
+}
+// Work split for even walks: of 1 .. `most` chunks per tile (what the workspace has room for) the one is taken with which
+// the two stages, the longer workgroups first, and the reduction of the partial sums end soonest.
+inline int32_t dkdv_full_splits(int64_t B, int64_t S, int64_t Skv, int32_t Hq, int32_t Hkv, int32_t D, int32_t most, int64_t off = INT32_MAX) {
     const int64_t tiles = (Skv + 255) / 256 * Hkv * B, q_rows = 128 * dq_row_blocks(B, S, Hq);
     const int64_t n_q = (S + q_rows - 1) / q_rows * Hq * B;
-    const double t_q = full_dq_time(Skv, q_rows, D);
+    const double t_q = even_dq_time(S, Skv, off, q_rows, D);
     int32_t best = 1;
     double best_end = 0.;
     for (int32_t n = 1; n <= most; ++n) {
-        const double t = full_dkdv_time(S, Hq / Hkv, n, D);
-        const double end = t >= t_q ? two_stage_end(tiles * n, t, n_q, t_q) : two_stage_end(n_q, t_q, tiles * n, t);
+        const double t = even_dkdv_time(S, Skv, off, Hq / Hkv, n, D);
+        double end = t >= t_q ? two_stage_end(tiles * n, t, n_q, t_q) : two_stage_end(n_q, t_q, tiles * n, t);
+        if (n > 1) end += dkdv_reduce_time(B, Skv, Hkv, D, n);
         if (n == 1 || end < best_end) { best = n; best_end = end; }
     }
     return best;
+}
+// The work split of a dense call.
+inline DkdvChunks dense_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t D) {
+    const int32_t most = dkdv_split_count(B, S, Skv, Hq, Hkv);
+    if (off < Skv) {
+        const DkdvChunks c = dkdv_chunks(B, S, Skv, off, Hq, Hkv, D, most, true);
+        const int64_t q_rows = 128 * dq_row_blocks(B, S, Hq), n_q = (S + q_rows - 1) / q_rows * Hq * B;
+        if (!even_walks(S, Skv, off) || (int64_t)c.n_chunks * Hkv * B + n_q <= kComputeUnits) return c;
+    }
+    const int32_t n = dkdv_full_splits(B, S, Skv, Hq, Hkv, D, most, off);
+    return DkdvChunks{n, 0, n * order_tiles(Skv)};
 }
 inline size_t dkdv_part_bytes(int64_t B, int64_t Skv, int32_t Hkv, int32_t D, int32_t nsplit) {
     return nsplit > 1 ? (size_t)2 * nsplit * B * Skv * Hkv * D * sizeof(float) : 0;

@@ -115,3 +115,68 @@ int main() {
 def test_packed_documents_get_groups_for_their_own_length(tmp_path):
     """Key groups of the forward follow the documents' walks, not the length of the whole batch."""
     run_on_host(tmp_path, PACKED)
+
+
+EVEN = r'''
+#define __HIP_PLATFORM_AMD__ 1
+#include "sp_common.h"
+#include <cmath>
+#include <cstdio>
+#include <queue>
+#include <vector>
+using namespace sp;
+static uint64_t seed = 99;
+static double uniform() { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return (double)(seed >> 11) / 9007199254740992.; }
+// Both stages' workgroups in the order of dispatch, dealt to 32 engines of 8 units, each with its own walk.
+static double simulate(int64_t B, int S, int Skv, int off, int Hq, int Hkv, int D, int n, bool q_first) {
+    const int G = Hq / Hkv, q_rows = 128 * dq_row_blocks(B, S, Hq), ranks = (S + q_rows - 1) / q_rows;
+    const double sc = D == 64 ? 2. / 3. : 1.;
+    std::vector<double> kv, q, all;
+    for (int t = 0; t < order_tiles(Skv); ++t)
+        for (int c = 0; c < n; ++c) kv.insert(kv.end(), Hkv * B, sc * 1.5 * dkdv_tile_steps(t, S, off, G) / n + 20.);
+    for (int r = ranks - 1; r >= 0; --r) {
+        const int last = std::min(S - 1, (r + 1) * q_rows - 1) + off, keys = last < Skv - 1 ? last + 1 : Skv;
+        q.insert(q.end(), Hq * B, sc * 0.95 * q_rows / 256. * ((keys + 31) / 32) + 10.);
+    }
+    const auto& a = q_first ? q : kv; const auto& b = q_first ? kv : q;
+    all = a; all.insert(all.end(), b.begin(), b.end());
+    double end = 0.;
+    for (int e = 0; e < 32; ++e) {
+        std::priority_queue<double, std::vector<double>, std::greater<double>> unit;
+        for (int i = 0; i < 8; ++i) unit.push(0.);
+        for (size_t i = e; i < all.size(); i += 32) { const double t = unit.top() + all[i]; unit.pop(); unit.push(t); end = std::max(end, t); }
+    }
+    return end + (n > 1 ? 4. + n * (double)B * Skv * Hkv * D * 16. / 12e6 : 0.);
+}
+int main() {
+    const int kv_heads[] = {1, 1, 1, 2, 4, 5, 8}, groups[] = {1, 2, 3, 4, 4, 8}, batch[] = {1, 1, 1, 2, 4, 8};
+    int seen = 0, worse = 0, jumps = 0;
+    double log_sum = 0.;
+    while (seen < 1500) {
+        const int Hkv = kv_heads[(int)(uniform() * 7)], G = groups[(int)(uniform() * 6)], Hq = Hkv * G, D = uniform() < .5 ? 64 : 128;
+        const int64_t B = batch[(int)(uniform() * 6)];
+        const int S = (int)exp(log(1000.) + uniform() * log(20.)), off = S - (int)(S / 2 * uniform() * uniform());
+        const int most = dkdv_split_count(B, S, S, Hq, Hkv);
+        if ((double)B * S * S * Hq > 6e9 || most < 2) continue;
+        const int q_rows = 128 * dq_row_blocks(B, S, Hq);
+        const DkdvChunks c = dense_chunks(B, S, S, off, Hq, Hkv, D);
+        if (c.len > 0 || (int64_t)c.n_chunks * Hkv * B + (S + q_rows - 1) / q_rows * Hq * B <= kComputeUnits) continue;
+        ++seen;
+        const bool q_first = even_dq_time(S, S, off, q_rows, D) > even_dkdv_time(S, S, off, G, c.nsplit, D);
+        const double now = simulate(B, S, S, off, Hq, Hkv, D, c.nsplit, q_first), plain = simulate(B, S, S, off, Hq, Hkv, D, most, false);
+        log_sum += log(now / plain);
+        if (now > 1.08 * plain) ++worse;
+        // an offset that hides one key of one row is no other problem than one that hides none
+        if (dense_chunks(B, S, S, S - 1, Hq, Hkv, D).nsplit != dense_chunks(B, S, S, S, Hq, Hkv, D).nsplit) ++jumps;
+    }
+    printf("of %d: %d worse than every chunk the rule allows, %d jumps, mean %.3f\n", seen, worse, jumps, exp(log_sum / seen));
+    return worse <= 3 && jumps <= 3 && log_sum < 0. ? 0 : 1;
+}
+'''
+
+
+def test_even_walks_are_split_by_whole_rounds(tmp_path):
+    """Blocks that hide little or nothing: the chunk count holds up in a simulation of the dispatch with every workgroup's
+    own walk, against the full count with one stage after the other, and does not jump where the offset reaches the
+    end of the keys."""
+    run_on_host(tmp_path, EVEN)
