@@ -143,17 +143,20 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const void* p) {
 // a full wait for outstanding LDS reads plus the two wait states a vector-ALU
 // write needs before an MFMA reads it, and followed by the wait states after
 // which any instruction may read its result; every partial LDS wait becomes a
-// full one.  The arithmetic and its order are unchanged, so the padded build
+// full one.  Every select on a lane mask is preceded by the wait states a
+// mask needs between the compare that writes it and its use.  The arithmetic and its order are unchanged, so the padded build
 // must give the regular build's bits: a test compares the two, which checks the
 // hand-counted waits and instruction spacing of the regular build.
 // ---------------------------------------------------------------------------
 #ifdef SP_PADDED_MFMA
 #define SP_MFMA_PRE "s_waitcnt lgkmcnt(0)\n\ts_nop 1\n\t"
 #define SP_MFMA_POST "\n\ts_nop 15\n\ts_nop 7"
+#define SP_MASK_PRE "s_nop 1\n\t"
 #define SP_LGKM(N) 0
 #else
 #define SP_MFMA_PRE ""
 #define SP_MFMA_POST ""
+#define SP_MASK_PRE ""
 #define SP_LGKM(N) (N)
 #endif
 
@@ -259,14 +262,15 @@ __device__ __forceinline__ void mfma_vc_ab(f32x16& acc, const u32x4& a, const bf
 // x = the lane's bit of `lanes` ? -inf : x.  One select per register as assembly: written in C++, a run of selects on one
 // flag becomes a branch around moves, and its copies of whole accumulator tiles took the dQ stage with one row block
 // (packed documents) from 241 to 256 vector registers and moves between the register files.  The compiler does not see
-// that the first select reads a mask that a compare may just have written: two wait states.
+// that the selects read a mask that a compare may just have written: two wait states, in a statement that hands the mask
+// on, so that no select can be placed before it.
 __device__ __forceinline__ void hide_lanes(f32x16& x, uint64_t lanes) {
     const float hidden = -__builtin_inff();
+    asm("s_nop 1" : "+s"(lanes));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         float v = x[r];
-        if (r == 0) asm("s_nop 1\n\tv_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
-        else asm("v_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
+        asm(SP_MASK_PRE "v_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
         x[r] = v;
     }
 }
