@@ -121,8 +121,12 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()  # the declared argument types make a pointer of it
 
 
-# The raw handle of the current stream, without the Stream object that torch.cuda.current_stream() builds around it.
-_current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# The raw handle of the current stream, without the Stream object that torch.cuda.current_stream() builds around it; through
+# that object where torch does not have the lookup (a build without a GPU backend, which can still import this module).
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+if _current_raw_stream is None or _current_device is None:
+    _current_device, _current_raw_stream = (lambda: None), (lambda device: torch.cuda.current_stream().cuda_stream)
 
 
 def _stream(stream) -> int:

@@ -4,6 +4,8 @@ status codes before any launch."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -196,3 +198,20 @@ def test_binding_rejects_wrong_dtypes_and_shapes_before_any_launch():
         sp.sp_rope(torch.zeros(4, 2, 64, dtype=bf), torch.zeros(4, 64), torch.zeros(4, 32))
     with pytest.raises(ValueError, match="u: expected"):
         sp.sp_swiglu_fwd(torch.zeros(16, dtype=bf), torch.zeros(8, dtype=bf))
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_import_without_the_raw_stream_lookup(missing):
+    """The binding imports, and its host functions run, on a torch that lacks the lookup of the raw stream handle; the
+    current stream then comes from the public call."""
+    code = f"""
+import torch
+if hasattr(torch._C, "{missing}"): delattr(torch._C, "{missing}")
+import paper_2604_27089_amd.binding as sp
+assert sp.sp_attn_bwd_workspace_bytes(1, 1024, 4, 1, 128) > 0
+class Stream: cuda_stream = 77
+torch.cuda.current_stream = lambda: Stream
+assert sp._stream(None) == 77 and sp._stream(Stream) == 77
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
