@@ -58,8 +58,7 @@ struct DkdvParams {
     const int32_t* row_hi;
     const int32_t* order;  // packed documents: key tiles in the order workgroups take them (or null)
     RowMap qmap, kvmap;
-    int32_t B, several;  // several: more than one sequence or KV head
-    int32_t S, Skv, off, S_pad, Hq, Hkv, G, n_ktiles;  // S query rows, Skv keys; row i sees keys j <= i + off
+    int32_t B, S, Skv, off, S_pad, Hq, Hkv, G, n_ktiles;  // S query rows, Skv keys; row i sees keys j <= i + off
     float scale, scale_log2;
 };
 
@@ -111,14 +110,12 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
 
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // earliest key tiles (most rows to visit) first; the workgroups that share a key tile are neighbours
-    // Order: with several sequences or KV heads those vary fastest, so that everybody's longest key tiles are
-    // dispatched before anybody's short ones (one after the other, the last one's longest tile started when the stage
-    // was two thirds done: 16 x 4096 rows 710 -> 510 us; 32768 rows of 8 heads, full attention, D = 64, whole backward
-    // 3944 -> 3246 us).
-    const uint32_t n_chunks = (uint32_t)p.chunks.n_chunks, n_heads = (uint32_t)p.Hkv * (uint32_t)p.B;
-    const int chunk_id = (int)(p.several ? wg / n_heads : wg % n_chunks);
-    const int head_id = (int)(p.several ? wg % n_heads : wg / n_chunks);
+    // Earliest key tiles (most rows to visit) first, the chunks of a tile behind each other; KV heads and batch entries vary
+    // fastest, so that everybody's longest key tiles are dispatched before anybody's short ones (one after the other, the
+    // last one's longest tile started when the stage was two thirds done: 16 x 4096 rows 710 -> 510 us; 32768 rows of 8
+    // heads, full attention, D = 64, whole backward 3944 -> 3246 us).
+    const uint32_t n_heads = (uint32_t)p.Hkv * (uint32_t)p.B;
+    const int chunk_id = (int)(wg / n_heads), head_id = (int)(wg % n_heads);
     int jt = chunk_id, split = 0;
     int tile_chunks = 1, first_chunk = 0;  // chunks of this tile, and of the tiles before it
     bool equal = false;
@@ -581,9 +578,9 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     // ---- write dK and dV: accumulator rows = keys, column = d ----
     if constexpr (SPLIT) {
         // fp32 partial sums of this chunk (dK unscaled); the reduction kernel adds the chunks in a fixed order.  A
-        // lane holds four consecutive keys of one column in four registers, and the sums are laid out like that
-        //, so a store is 16 bytes per lane and 512 contiguous bytes per half wave: 64 stores per wave
-        // where key-major sums took 256 of 4 bytes per lane (5.5 us per workgroup).
+        // lane holds four consecutive keys of one column in four registers, and the sums are laid out like that, so a
+        // store is 16 bytes per lane and 512 contiguous bytes per half wave: 64 stores per wave where key-major sums
+        // took 256 of 4 bytes per lane (5.5 us per workgroup).
         const int keys = Skv - j0 < BNK ? Skv - j0 : BNK;
         float* pk = p.part + part_offset((int64_t)b * p.Hkv + g, p.chunks.nsplit, Skv, first_chunk, split, keys, D);
         float* pv = pk + (size_t)p.B * p.Hkv * p.chunks.nsplit * Skv * D;

@@ -126,7 +126,7 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
         k.n_ktiles = (a.Skv + dkdv::BNK - 1) / dkdv::BNK;
         k.chunks = a.chunks; k.part = a.dkdv_part;
         k.scale = a.scale; k.scale_log2 = a.scale * kLog2e;
-        k.B = a.B; k.several = a.B > 1 || a.Hkv > 1;
+        k.B = a.B;
         if (kv && (k.chunks.nsplit < 1 || (k.chunks.nsplit > 1 && !k.part))) return SP_ERR_WORKSPACE;
     }
     {
