@@ -1,6 +1,7 @@
 """The host-side rules that cut the attention work into workgroups, compiled for the CPU and checked over many extents:
-the partial sums of the dK/dV chunks fit the room the workspace query leaves for them, every step of every key tile
-belongs to exactly one chunk, and the counts stay inside what the kernels are built for."""
+the counts stay inside what the kernels are built for, every step of every key tile belongs to exactly one chunk (the
+chunk's tile, its first and its last step, derived from its number as the kernel does), and the partial sums of the
+chunks lie side by side in the room the workspace query leaves for them."""
 import os
 import subprocess
 
@@ -13,6 +14,7 @@ SRC = r'''
 #include "sp_common.h"
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 using namespace sp;
 static uint64_t seed = 12345;
 static int64_t pick(int64_t lo, int64_t hi) { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return lo + (int64_t)((seed >> 33) % (uint64_t)(hi - lo + 1)); }
@@ -52,6 +54,34 @@ int main() {
             CHECK(n == c.n_chunks && rows <= (int64_t)c.nsplit * Skv);
         }
         CHECK(dkdv_part_bytes(B, Skv, Hkv, D, c.nsplit) <= dkdv_part_bytes(B, Skv, Hkv, D, rule));
+        if ((int64_t)c.n_chunks > 20000) continue;
+        // as the kernel derives them: a chunk's tile and number in it, its steps, the place of its partial sums (keys)
+        std::vector<int64_t> done(tiles, 0);  // steps of a tile that the chunks so far have taken, in order
+        int64_t place = 0;                    // end of the last chunk's partial sums
+        for (int32_t id = 0; id < c.n_chunks; ++id) {
+            int32_t jt = 0, split = 0, tile_chunks = c.nsplit, first = 0;
+            if (c.len > 0) {
+                for (int32_t upto = 0; jt < tiles; ++jt) {
+                    tile_chunks = (dkdv_tile_steps(jt, (int32_t)S, (int32_t)off, G) + c.len - 1) / c.len;
+                    first = upto; upto += tile_chunks;
+                    if (upto > id) break;
+                }
+                split = id - first;
+            } else { jt = id / c.nsplit; split = id % c.nsplit; first = jt * c.nsplit; }
+            CHECK(jt < tiles && split >= 0 && split < tile_chunks);
+            const int32_t j0 = jt * kOrderTile, n_it = (int32_t)((S + 31) / 32) - (int32_t)(j0 > off ? j0 - off : 0) / 32;
+            const int64_t total = (int64_t)n_it * G, per = (total + tile_chunks - 1) / tile_chunks;
+            const int64_t s0 = split * per < total ? split * per : total, s1 = s0 + per < total ? s0 + per : total;
+            CHECK(s0 == done[jt] && s1 >= s0);
+            done[jt] = s1;
+            if (split == tile_chunks - 1) CHECK(s1 == total);
+            if (c.nsplit > 1) {
+                const int64_t keys = Skv - j0 < kOrderTile ? Skv - j0 : kOrderTile, at = (int64_t)first * kOrderTile + split * keys;
+                CHECK(at >= place && at + keys <= (int64_t)c.nsplit * Skv);
+                place = at + keys;
+            }
+        }
+        for (int32_t t = 0; t < tiles; ++t) CHECK(done[t] == (int64_t)dkdv_tile_steps(t, (int32_t)S, (int32_t)off, G));
         const int ks = fwd_key_groups(B, S, Skv, off, Hq);
         CHECK(ks == 1 || ks == 2 || ks == 4);
         CHECK(dq_row_blocks(B, S, Hq) == 1 || dq_row_blocks(B, S, Hq) == 2);
