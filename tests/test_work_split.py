@@ -210,3 +210,18 @@ def test_even_walks_are_split_by_whole_rounds(tmp_path):
     own walk, against the full count with one stage after the other, and does not jump where the offset reaches the
     end of the keys."""
     run_on_host(tmp_path, EVEN)
+
+
+def test_the_group_counts_that_the_gpu_tests_are_there_for(tmp_path):
+    """The tables of test_attn_fwd_groups_gpu.py against the rule that picks the kernel."""
+    import test_attn_fwd_groups_gpu as groups
+    checks = [(f"fwd_key_groups({B}, {S}, {S}, 0, 1)", ks) for S, row in groups.BATCHES.items() for B, ks in row.items()]
+    checks += [(f"fwd_key_groups({B}, {Sq}, {Skv}, {min(off, Skv)}, 1)", ks)
+               for (Sq, Skv, off), row in groups.BLOCKS.items() for B, ks in row.items()]
+    checks += [(f"packed_key_groups({sum(lengths)}, {len(lengths)}, {Hq})", ks) for lengths, row in groups.PACKED.items() for Hq, ks in row.items()]
+    checks += [(f"fwd_key_groups(1, {S}, {S}, 0, 4)", ks) for S, ks in groups.WALKS.items()]
+    lines = "\n".join(f'    if ({call} != {ks}) {{ printf("{call} is not {ks}\\n"); ++bad; }}' for call, ks in checks)
+    run_on_host(tmp_path, "#define __HIP_PLATFORM_AMD__ 1\n#include \"sp_common.h\"\n#include <cstdio>\nusing namespace sp;\n"
+                          "int main() {\n    int bad = 0;\n" + lines + "\n    return bad ? 1 : 0;\n}\n")
+    for table in (groups.BATCHES, groups.BLOCKS, {"short": groups.PACKED[groups.SHORT]}, {"walks": groups.WALKS}):
+        assert {ks for row in table.values() for ks in row.values()} == {1, 2, 4}
