@@ -62,13 +62,7 @@ def test_packed_documents(lengths, heads):
         assert grad_err(host_f64(got[:, :1]), ref, name) <= GRAD_REL_L2
 
 
-# one-round launches: chunks of equal length, as many per key tile as its steps need; ragged last tiles, offsets, and
-# shapes just past one round (unequal chunks).  The workspace has exactly the asked size, between canaries.
-@pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("Sq,Skv,off,Hq,Hkv", [(257, 257, 0, 4, 1), (513, 513, 0, 1, 1), (1030, 1030, 0, 3, 1), (900, 900, 0, 8, 2),
-                                               (300, 1199, 900, 8, 1), (1500, 259, 0, 4, 1), (700, 800, 5000, 4, 2),
-                                               (2047, 2047, 0, 2, 1), (1025, 1025, 0, 16, 8), (2050, 2050, 0, 10, 5)])
-def test_equal_chunks(Sq, Skv, off, Hq, Hkv, D):
+def check_block(Sq, Skv, off, Hq, Hkv, D):
     qb, _, _, dob = synth.attn_inputs(Sq, Sq, Hq, Hkv, D)
     _, kb, vb, _ = synth.attn_inputs(Skv + 3, Skv, Hq, Hkv, D)
     q, k, v, do = (dev_bf16(t) for t in (qb, kb, vb, dob))
@@ -84,6 +78,23 @@ def test_equal_chunks(Sq, Skv, off, Hq, Hkv, D):
         assert grad_err(host_f64(got[0]), ref, name) <= GRAD_REL_L2, (name, Sq, Skv, off, Hq, Hkv, D)
     again = sp.sp_attn_block_bwd(q, k, v, o, lse, do, off)
     assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(again, (dq, dk, dv)))
+
+
+# one-round launches: chunks of equal length, as many per key tile as its steps need; ragged last tiles, offsets, and
+# shapes just past one round (unequal chunks).  The workspace has exactly the asked size, between canaries.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Sq,Skv,off,Hq,Hkv", [(257, 257, 0, 4, 1), (513, 513, 0, 1, 1), (1030, 1030, 0, 3, 1), (900, 900, 0, 8, 2),
+                                               (300, 1199, 900, 8, 1), (1500, 259, 0, 4, 1), (700, 800, 5000, 4, 2),
+                                               (2047, 2047, 0, 2, 1), (1025, 1025, 0, 16, 8), (2050, 2050, 0, 10, 5)])
+def test_equal_chunks(Sq, Skv, off, Hq, Hkv, D):
+    check_block(Sq, Skv, off, Hq, Hkv, D)
+
+
+# blocks that hide little, beyond one round of the chip: whole rounds of the longer stage, then the other
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Sq,Skv,off,Hq,Hkv", [(900, 900, 880, 32, 8), (700, 700, 699, 36, 9), (1025, 1025, 520, 40, 8), (1290, 1400, 1300, 24, 8)])
+def test_even_walks(Sq, Skv, off, Hq, Hkv, D):
+    check_block(Sq, Skv, off, Hq, Hkv, D)
 
 
 # the hand-scheduled dQ program with two row blocks per wave runs above 128 tiles of 256 rows: there, too, the build
