@@ -322,15 +322,17 @@ inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
     }
     return end;
 }
-// Even walks: the shortest walk of either stage is at least half the longest (a block from the past in a ring schedule, or
-// any causal offset from about the middle of the keys on).  Beyond one round of the chip such workgroups end in whole
+// Even walks: the shortest walk of either stage is at least a third of the longest (a block from the past in a ring
+// schedule, or any causal offset from a third of the keys on).  Beyond one round of the chip such workgroups end in whole
 // rounds, like those of a block that hides nothing, and the estimates for a causal ramp do not see that: with them an
 // offset one below "hides nothing" got another chunk count and order, and times up to 17 % above those of one stage
 // after the other (backward, us, one stage after the other / causal estimate / this rule: 7039 rows of 16 and 4 heads,
 // D = 64, offset 7038, 685 / 805 / 678; 9224 rows, 20 and 5 heads, offset 9106, 1430 / 1602 / 1392).  1356 shapes with
 // offsets above half: 0.690 of the time of one stage after the other with the causal estimates, 17 of them more than 3 %
 // above it; with this rule 0.671 and 4 (5 % in one round of dK/dV beside one of dQ: 5860 rows of 8 heads 435 / 456).
-inline bool even_walks(int64_t S, int64_t Skv, int64_t off) { return 2 * off >= Skv && 2 * (Skv - off) <= S; }
+// Offsets of 0.35 to 0.5 of the keys, 80 shapes beyond 300 us: 0.90 and 0.87; below a third the gain is a hundredth and
+// some lose.
+inline bool even_walks(int64_t S, int64_t Skv, int64_t off) { return 3 * off >= Skv && 3 * (Skv - off) <= 2 * S; }
 // The share of the (row, key) pairs that are visible there, and what a workgroup of either stage takes on average, in us.
 inline double even_share(int64_t S, int64_t Skv, int64_t off) {
     const double hidden = off < Skv ? (double)(Skv - off) : 0.;

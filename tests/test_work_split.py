@@ -185,7 +185,7 @@ int main() {
     while (seen < 1500) {
         const int Hkv = kv_heads[(int)(uniform() * 7)], G = groups[(int)(uniform() * 6)], Hq = Hkv * G, D = uniform() < .5 ? 64 : 128;
         const int64_t B = batch[(int)(uniform() * 6)];
-        const int S = (int)exp(log(1000.) + uniform() * log(20.)), off = S - (int)(S / 2 * uniform() * uniform());
+        const int S = (int)exp(log(1000.) + uniform() * log(20.)), off = S - (int)(S * 2 / 3 * uniform() * uniform());
         const int most = dkdv_split_count(B, S, S, Hq, Hkv);
         if ((double)B * S * S * Hq > 6e9 || most < 2) continue;
         const int q_rows = 128 * dq_row_blocks(B, S, Hq);
