@@ -243,6 +243,7 @@ sp_status sp_attn_block_bwd(const void* q, const void* k, const void* v, const v
  *               never changes a result beyond rounding order: the backward uses
  *               it to decide over how many workgroups a key tile's work is
  *               spread (short documents want fewer).
+ *               The forward's split follows from T, Hq and n_docs.
  *   workspace : >= the matching *_workspace_bytes query.  It receives the
  *               per-row document windows and the order in which workgroups
  *               take the 256-row tiles (longest first: with documents of

@@ -49,15 +49,16 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
 }
 
 // In which order the workgroups of the two stages go out (speed only: every order gives the same bits).  Each stage
-// hands out its longest walks first; the longest of each, in us, is about 0.95 per 32-key step of dQ (0.5 with one row block) and 1.5 per
-// 32-row step of dK/dV beyond fixed costs.
+// hands out its longest walks first; what they take is estimated with the costs of sp_common.h (at D = 64 both are a third
+// shorter, and it is their ratio that counts).
 //   Even walks beyond one round (even_walks()): the stage with the longer workgroups first, the other fills its last
 // round.
 //   Up to three rounds of the chip (768 workgroups; five with packed documents, whose work is uneven): the two are
-// merged by expected length, i.e. the stage with the longer walks leads until its remaining ones are as long as
-// the other's, and from there they alternate.  Measured against dK/dV first / dQ first, us: 8192 rows of 5 heads,
-// full attention, 286 against 345 / 284, 16384 rows, 4 heads, 780 against 886 / 780, 64 x 512 rows 130 against 132 / 139,
-// packed documents of 32768 rows at D = 64 (longest 12877) 448 against 572 / 506.
+// merged by expected length, i.e. the stage with the longer walks leads until its remaining ones are as long as the
+// other's, and from there they alternate.  Measured against dK/dV first / dQ first, us: 64 x 512 rows 130 against 132 /
+// 139, packed documents of 32768 rows at D = 64 (longest 12877) 448 against 572 / 506; where dQ's walks are the longer
+// ones the merged order is as good as dQ first: 8192 rows of 5 heads, full attention, 286 against 345 / 284, 16384 rows,
+// 4 heads, 780 against 886 / 780.
 //   Beyond that whole stages follow each other: alternating mixes two access patterns that each share their stream
 // through L2 (131072 rows 47.0 ms against 41.9; 16384 rows of 8 heads 1572 us against 1490).  dQ first, since the
 // chunks of dK/dV are the finer ones to fill the end with (16 x 4096 rows 821 us against 838), unless a dK/dV walk
@@ -67,8 +68,8 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     const int64_t longest = a.longest > 0 && a.longest < a.S ? a.longest : a.S;
     const double steps = (double)((longest + 31) / 32);
     const int q_rows = 128 * dq_row_blocks(a.B, a.S, a.Hq);
-    const double q_step = q_rows == 128 ? 0.5 : 0.95;
-    const double t_q = q_step * steps + 10., t_kv = 1.5 * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + 20.;
+    const double q_step = dq_step(q_rows), t_q = q_step * steps + kDqFixed;
+    const double t_kv = kDkdvStep * (a.chunks.len > 0 ? a.chunks.len : steps * (a.Hq / a.Hkv) / a.chunks.nsplit) + kDkdvFixed;
     bool lead_q;
     int64_t lead;
     if (!a.row_lo && (a.off >= a.Skv || (even_walks(a.S, a.Skv, a.off) && n_kv + n_q > kComputeUnits))) {  // the longer workgroups first
@@ -77,10 +78,10 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     } else if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
         // walks fall evenly from the longest to the shortest (a short document's, or that of the first rows resp.
         // the last keys)
-        double short_q = 10., short_kv = 20.;
+        double short_q = kDqFixed, short_kv = kDkdvFixed;
         if (!a.row_lo) {
             short_q += q_step * (double)((a.off + q_rows < a.Skv ? a.off + q_rows : a.Skv) / 32);
-            short_kv = a.chunks.len > 0 ? t_kv : short_kv + 1.5 * dkdv_tile_steps(order_tiles(a.Skv) - 1, a.S, a.off, a.Hq / a.Hkv) / a.chunks.nsplit;
+            short_kv = a.chunks.len > 0 ? t_kv : short_kv + kDkdvStep * dkdv_tile_steps(order_tiles(a.Skv) - 1, a.S, a.off, a.Hq / a.Hkv) / a.chunks.nsplit;
         }
         lead_q = t_q >= t_kv;
         const double longer = lead_q ? t_q : t_kv, other = lead_q ? t_kv : t_q, least = lead_q ? short_q : short_kv;
@@ -94,7 +95,7 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
         } else {
             const int32_t tiles = order_tiles(a.Skv), G = a.Hq / a.Hkv;
             const double mean = ((double)dkdv_tile_steps(0, a.S, a.off, G) + (double)dkdv_tile_steps(tiles - 1, a.S, a.off, G)) / 2.;
-            kv_all = (1.5 * mean * tiles * (double)a.Hkv * a.B + 20. * (double)n_kv) / (double)kComputeUnits;
+            kv_all = (kDkdvStep * mean * tiles * (double)a.Hkv * a.B + kDkdvFixed * (double)n_kv) / (double)kComputeUnits;
         }
         lead_q = t_kv <= kv_all;
         lead = lead_q ? n_q : n_kv;

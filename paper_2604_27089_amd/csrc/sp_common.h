@@ -184,14 +184,15 @@ sp_status launch_attn_merge(float* o_acc, float* lse_acc, const void* o_blk, con
 // (head, row tile) steps of a key tile are therefore cut into this many contiguous chunks, one workgroup
 // each, whose fp32 partial sums a second kernel adds in a fixed order (measured: 4.36 -> 1.65 ms at 32K
 // rows, 10.1 -> 6.3 ms at 64K, 25.3 -> 24.7 ms at 128K).
-// A workgroup of this kernel costs about 45 us beyond its steps (loading its keys and values, the pipeline
-// prologue, writing 256 KB of partial sums), a step about 1.5 us, and one compute unit holds one workgroup:
-// n chunks per tile cost (tiles * n / 256) * 45 us of overhead and leave a longest chunk of steps_first / n
-// steps, a fraction of which is exposed at the end.  The sum is smallest near n = sqrt(2.1 * steps_first /
-// tiles) (the constant fitted to sequences of 1K to 128K rows, dense and packed); at most 8 chunks, and no
-// more than about 2048 workgroups.  `longest` = the longest sequence in the call when the caller knows it
-// (packed documents: the max_seqlen hint), else S.  The count depends on these extents only, so packed
-// documents and dense calls of equal extents agree bitwise.
+// n chunks per tile cost (tiles * n / 256) times what a workgroup takes beyond its steps, and leave a longest chunk of
+// steps_first / n steps, a fraction of which is exposed at the end.  The sum is smallest near n = sqrt(2.1 * steps_first /
+// tiles); at most 8 chunks, and no more than about 2048 workgroups.  (The constant was fitted to sequences of 1K to 128K
+// rows, dense and packed, when a workgroup stored its sums 4 bytes per lane and took 27 us beyond its steps; it is 20 now,
+// and the count is still within a few percent of the best: 16384 rows, 4 heads, 5 chunks instead of 8 are 4 % faster at
+// D = 128 and slower at D = 64, 32768 rows 4 instead of 8 1 %.)  It is also the room for partial sums: the rules below
+// take at most as many.  `longest` = the longest sequence in the call when the caller knows it (packed documents: the
+// max_seqlen hint), else S.  The counts depend on extents only, so one packed document and a dense call of equal extents
+// agree bitwise.
 inline int32_t dkdv_split_count(int64_t B, int64_t S, int64_t Skv, int32_t Hq, int32_t Hkv, int64_t longest = 0) {
     if (B <= 0 || S <= 0 || Skv <= 0 || Hkv <= 0) return 1;
     if (longest <= 0 || longest > S) longest = S;
@@ -212,6 +213,12 @@ inline int32_t dkdv_split_count(int64_t B, int64_t S, int64_t Skv, int32_t Hq, i
     if (n > cap) n = cap;
     return n < 1 ? 1 : (int32_t)n;
 }
+// What the estimates take a workgroup of the two matrix stages to cost in a full chip, in us: per 32-row step of dK/dV, per
+// 32-key step of dQ with one or two row blocks (D = 128; D = 64 takes two thirds), and beyond the steps (resident operands
+// and first tiles, the pipeline's fill, the results).
+constexpr double kDkdvStep = 1.5, kDkdvFixed = 20., kDqFixed = 10.;
+inline double dq_step(int64_t q_rows) { return q_rows == 128 ? 0.5 : 0.95; }
+inline double step_share(int32_t D) { return D == 64 ? 2. / 3. : 1.; }
 // What the kernel that adds the chunks' partial sums takes, in us: written once and read once at 12 TB/s (they stay in the
 // memory-side cache), and a launch.
 inline double dkdv_reduce_time(int64_t B, int64_t Skv, int32_t Hkv, int32_t D, int32_t nsplit) {
@@ -223,30 +230,29 @@ __host__ __device__ inline int32_t dkdv_tile_steps(int32_t jt, int32_t S, int32_
     return ((S + 31) / 32 - (j0 > off ? j0 - off : 0) / 32) * G;
 }
 // Where the work of every tile is known on the host (one document per sequence), there are several sequences or KV
-// heads and at most as many key tiles as compute units, the number of chunks follows from an estimate of when dK/dV and dQ, launched together, are done:
-// not before the longest workgroup of either, nor before all work shared out evenly, plus an eighth of the longest
-// dK/dV workgroup for the uneven end and the reduction of the partial sums (us per step: 1.5 for dK/dV, 0.95 or 0.5 for dQ with two or one row blocks, a third less at D = 64;
-// 20 and 10 us per workgroup; 12 TB/s of partial sums, which stay in the memory-side cache).  Of 1 .. `most`, the
-// count that the rule above gives and the workspace is sized for.  Backward, rule / estimate (with the order of
-// dispatch of attn_bwd_matrix.h), us: 16 x 1024 rows of 4 heads, full attention, 129 / 96; 32 x 2048 rows, 4 query heads
-// and one KV head, 499 / 461; 4096 rows, 32 and 8 heads, 566 / 436; 2500 rows, the same, 280 / 198.  For a single KV head
-// the estimate gives no more than the rule (16384 rows 765 / 765 us, D = 64 458 / 467; 65536 rows 10.8 / 11.0 ms).
+// heads and at most as many key tiles as compute units, the number of chunks follows from an estimate of when dK/dV and
+// dQ, launched together, are done: not before the longest workgroup of either, nor before all work shared out evenly,
+// plus an eighth of the longest dK/dV workgroup for the uneven end and the reduction of the partial sums.  Of 1 ..
+// `most`, the count that the rule above gives and the workspace is sized for.  Backward, rule / estimate (with the order
+// of dispatch of attn_bwd_matrix.h), us: 16 x 1024 rows of 4 heads, full attention, 129 / 96; 32 x 2048 rows, 4 query
+// heads and one KV head, 499 / 461; 4096 rows, 32 and 8 heads, 566 / 436; 2500 rows, the same, 280 / 198.  For a single
+// KV head the estimate gives no more than the rule (16384 rows 765 / 765 us, D = 64 458 / 467; 65536 rows 10.8 / 11.0 ms).
 inline int32_t dkdv_causal_splits(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t D, int32_t most) {
     const int32_t tiles = order_tiles(Skv), G = Hq / Hkv, q_rows = 128 * dq_row_blocks(B, S, Hq);
-    const double head_b = (double)Hkv * (double)B, scale = D == 64 ? 2. / 3. : 1.;
+    const double head_b = (double)Hkv * (double)B, scale = step_share(D), kv_step = scale * kDkdvStep, q_step = scale * dq_step(q_rows);
     double steps = 0.;
     for (int32_t t = 0; t < tiles; ++t) steps += dkdv_tile_steps(t, S, off, G);
     const double longest = dkdv_tile_steps(0, S, off, G);
     const double ranks = (double)(((int64_t)S + q_rows - 1) / q_rows), n_q = ranks * Hq * (double)B;
-    const double q_step = scale * (q_rows == 128 ? 0.5 : 0.95), q_last = (double)((Skv + 31) / 32), q_first = (double)((off < Skv ? off : Skv) / 32);
-    const double t_q = q_step * q_last + 10., work_q = n_q * (q_step * (q_first + q_last) / 2. + 10.);
+    const double q_last = (double)((Skv + 31) / 32), q_first = (double)((off < Skv ? off : Skv) / 32);
+    const double t_q = q_step * q_last + kDqFixed, work_q = n_q * (q_step * (q_first + q_last) / 2. + kDqFixed);
     int32_t best = 1;
     double best_time = 0.;
     for (int32_t n = 1; n <= most; ++n) {
         const double jobs = (double)tiles * n * head_b;
-        double t_kv = scale * 1.5 * longest / n + 20.;
-        if (n > 1 && jobs + n_q <= (double)kComputeUnits) t_kv = scale * 1.5 * 1.1 * steps * head_b / jobs + 20.;  // equal chunks
-        const double shared = (scale * 1.5 * steps * head_b + 20. * jobs + work_q) / (double)kComputeUnits + 10.;
+        double t_kv = kv_step * longest / n + kDkdvFixed;
+        if (n > 1 && jobs + n_q <= (double)kComputeUnits) t_kv = kv_step * 1.1 * steps * head_b / jobs + kDkdvFixed;  // equal chunks
+        const double shared = (kv_step * steps * head_b + kDkdvFixed * jobs + work_q) / (double)kComputeUnits + 10.;
         double time = t_kv > t_q ? t_kv : t_q;
         if (shared > time) time = shared;
         time += t_kv / 8.;
@@ -339,10 +345,10 @@ inline double even_share(int64_t S, int64_t Skv, int64_t off) {
     return 1. - hidden * hidden / (2. * (double)S * (double)Skv);
 }
 inline double even_dq_time(int64_t S, int64_t Skv, int64_t off, int64_t q_rows, int32_t D) {
-    return (D == 64 ? 2. / 3. : 1.) * 0.95 * (double)((Skv + 31) / 32) * even_share(S, Skv, off) * (double)q_rows / 256. + 10.;
+    return step_share(D) * dq_step(q_rows) * (double)((Skv + 31) / 32) * even_share(S, Skv, off) + kDqFixed;
 }
 inline double even_dkdv_time(int64_t S, int64_t Skv, int64_t off, int32_t G, int32_t nsplit, int32_t D) {
-    return (D == 64 ? 2. / 3. : 1.) * 1.5 * (double)((S + 31) / 32 * G) * even_share(S, Skv, off) / nsplit + 20.;
+    return step_share(D) * kDkdvStep * (double)((S + 31) / 32 * G) * even_share(S, Skv, off) / nsplit + kDkdvFixed;
 }
 // Work split for even walks: of 1 .. `most` chunks per tile (what the workspace has room for) the one is taken with which
 // the two stages, the longer workgroups first, and the reduction of the partial sums end soonest.
