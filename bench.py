@@ -4,7 +4,7 @@
 A step is one pass of the whole path for one layer on one GPU's shard, inputs
 resident in HBM:
   forward : pack Q, K, V (seq->head) -> attention forward -> unpack O (head->seq)
-  backward: pack dO -> attention backward (delta, dK/dV, dQ) -> unpack dQ, dK, dV
+  backward: pack dO -> attention backward (one call: delta, then dK/dV and dQ in one launch) -> unpack dQ, dK, dV
 The metric is causal attention fwd+bwd TFLOP/s: algorithmic flops
 14*D*Hq*S(S+1)/2 (exact unmasked pairs; forward 4, backward 10; recomputed
 contractions and masked halves not credited) divided by the whole step time,
@@ -209,9 +209,7 @@ def main():
         timed("attn_fwd", lambda: sp.sp_attn_fwd(q, k, v, o=o, lse=lse), record)
         timed("unpack", lambda: sp.sp_unpack_head_to_seq(o, P, out=o_l), record)
         timed("pack", lambda: sp.sp_pack_seq_to_head(do_l, P, out=do), record)
-        timed("attn_bwd_delta", lambda: sp.sp_attn_bwd_stages(q, k, v, o, lse, do, dq, dk, dv, ws, sp.SP_BWD_STAGE_DELTA), record)
-        timed("attn_bwd_dkdv", lambda: sp.sp_attn_bwd_stages(q, k, v, o, lse, do, dq, dk, dv, ws, sp.SP_BWD_STAGE_DKDV), record)
-        timed("attn_bwd_dq", lambda: sp.sp_attn_bwd_stages(q, k, v, o, lse, do, dq, dk, dv, ws, sp.SP_BWD_STAGE_DQ), record)
+        timed("attn_bwd", lambda: sp.sp_attn_bwd(q, k, v, o, lse, do, dq=dq, dk=dk, dv=dv, workspace=ws), record)
         timed("unpack", lambda: (sp.sp_unpack_head_to_seq(dq, P, out=dq_l), sp.sp_unpack_head_to_seq(dk, P, out=dk_l),
                                  sp.sp_unpack_head_to_seq(dv, P, out=dv_l)), record)
 
@@ -225,10 +223,19 @@ def main():
     wall = time.perf_counter() - t0
     ms_per_step = wall * 1e3 / args.steps
 
+    # The backward of a step is one call, whose dK/dV and dQ workgroups share a launch; for the figures of either stage
+    # the same backward once more stage by stage, behind the timed steps.
+    stage_steps = max(1, min(args.steps, 5))
+    for i in range(stage_steps + 1):
+        for name, stage in (("attn_bwd_delta", sp.SP_BWD_STAGE_DELTA), ("attn_bwd_dkdv", sp.SP_BWD_STAGE_DKDV), ("attn_bwd_dq", sp.SP_BWD_STAGE_DQ)):
+            timed(name, lambda: sp.sp_attn_bwd_stages(q, k, v, o, lse, do, dq, dk, dv, ws, stage), i > 0)
+    torch.cuda.synchronize()
+
     per = {}
     for name, a, b in marks:
         per.setdefault(name, []).append(a.elapsed_time(b))
-    kern_ms = {n: float(np.sum(v)) / args.steps for n, v in per.items()}  # ms per step, all launches of that stage
+    # ms per step, all launches of that region (the stages: per backward)
+    kern_ms = {n: float(np.sum(v)) / (stage_steps if n.startswith("attn_bwd_") else args.steps) for n, v in per.items()}
 
     # dominant kernel and its roofline.  Algorithmic credit: forward 4*D*Hq*N; dK/dV kernel 8*D*Hq*N
     # (S, dP, dV, dK); dQ kernel 2*D*Hq*N (its S and dP are recomputed, not credited).
@@ -243,11 +250,13 @@ def main():
     value = (fl_fwd + fl_bwd) / (ms_per_step * 1e-3) / 1e12
     detail = {
         "kernel_ms_per_step": {n: round(v, 4) for n, v in kern_ms.items()},
+        "kernel_ms_note": "attn_bwd: the step's backward, one call; attn_bwd_delta, _dkdv, _dq: the same backward stage by stage, "
+                          f"{stage_steps} times behind the timed steps",
         # per timed region (median, minimum over the timed steps); pack and unpack have two regions per step each
         "kernel_ms_median": {n: round(float(np.median(v)), 4) for n, v in per.items()},
         "kernel_ms_min": {n: round(float(np.min(v)), 4) for n, v in per.items()},
         "attn_fwd_tflops": fl_fwd / (kern_ms["attn_fwd"] * 1e-3) / 1e12,
-        "attn_bwd_tflops": fl_bwd / ((kern_ms["attn_bwd_delta"] + kern_ms["attn_bwd_dkdv"] + kern_ms["attn_bwd_dq"]) * 1e-3) / 1e12,
+        "attn_bwd_tflops": fl_bwd / (kern_ms["attn_bwd"] * 1e-3) / 1e12,
         "pct_of_bf16_mfma_peak": 100.0 * value / MFMA_BF16_PEAK_TFLOPS,
     }
     # Every attention kernel against the matrix peak, both ways of counting: "credited" = the algorithmic
