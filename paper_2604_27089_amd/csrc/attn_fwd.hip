@@ -30,8 +30,8 @@
 // the tiles g, g + KS, ... through LDS buffers of its own, with its own maximum,
 // sum and O, and the groups' results are merged through LDS at the end.  The
 // phases stay as they are: with KS = 2 group A and group B simply walk different
-// tiles.  4096 rows, 4 heads of D = 128: 106 us with one group, 49 with four
-// (350 TFLOP/s); fwd_key_groups() and packed_key_groups() have the rules and more figures.
+// tiles.  4096 rows, 4 heads of D = 128: 102 us with one group, 45 with four
+// (380 TFLOP/s); fwd_key_groups() and packed_key_groups() have the rules and more figures.
 #include "attn_common.h"
 #include "sp_common.h"
 
