@@ -301,10 +301,11 @@ inline double engine_end(int64_t n1, double t1, int64_t n2, double t2) {
     const double free_early = t1 * (double)(n1 / kEngineUnits), free_late = late ? free_early + t1 : free_early;
     if (n2 == 0) return free_late;
     const double fluid = ((double)n2 * t2 + (double)early * free_early + (double)late * free_late) / (double)kEngineUnits;
+    const double least = fluid > free_late ? fluid : free_late;
     double end = 0.;
     for (int side = 0; side < 2; ++side) {  // the end is a whole number of workgroups after one of the two
         const double from = side ? free_late : free_early;
-        int64_t k = fluid > from ? (int64_t)((fluid - from) / t2) : 0;
+        int64_t k = (int64_t)((least - from) / t2);
         double t = 0.;
         for (;; ++k) {
             t = from + (double)k * t2 + 1e-6;
