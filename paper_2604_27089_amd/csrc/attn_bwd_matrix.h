@@ -73,7 +73,7 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     bool lead_q;
     int64_t lead;
     if (!a.row_lo && (a.off >= a.Skv || (even_walks(a.S, a.Skv, a.off) && n_kv + n_q > kComputeUnits))) {  // the longer workgroups first
-        lead_q = even_dq_time(a.S, a.Skv, a.off, q_rows, a.D) > even_dkdv_time(a.S, a.Skv, a.off, a.Hq / a.Hkv, a.chunks.nsplit, a.D);
+        lead_q = even_dq_first(a.S, a.Skv, a.off, a.Hq, a.Hkv, q_rows, a.chunks.nsplit, a.D);
         lead = lead_q ? n_q : n_kv;
     } else if (n_kv + n_q <= (a.row_lo ? 1280 : 768)) {
         // walks fall evenly from the longest to the shortest (a short document's, or that of the first rows resp.

@@ -292,40 +292,19 @@ inline DkdvChunks dkdv_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, in
         if (rows <= (int64_t)nsplit * Skv) return DkdvChunks{nsplit, (int32_t)len, chunks};
     }
 }
-// When a part of the chip with kEngineUnits units is done with n1 workgroups of t1 us followed by n2 of t2 us, one per unit
-// at a time.
-constexpr int64_t kEngines = 32, kEngineUnits = kComputeUnits / kEngines;  // shader engines
-inline double engine_end(int64_t n1, double t1, int64_t n2, double t2) {
-    // after the first stage `late` units are free one of its workgroups later than the others
-    const int64_t late = n1 % kEngineUnits, early = kEngineUnits - late;
-    const double free_early = t1 * (double)(n1 / kEngineUnits), free_late = late ? free_early + t1 : free_early;
-    if (n2 == 0) return free_late;
-    const double fluid = ((double)n2 * t2 + (double)early * free_early + (double)late * free_late) / (double)kEngineUnits;
-    const double least = fluid > free_late ? fluid : free_late;
-    double end = 0.;
-    for (int side = 0; side < 2; ++side) {  // the end is a whole number of workgroups after one of the two
-        const double from = side ? free_late : free_early;
-        int64_t k = (int64_t)((least - from) / t2);
-        double t = 0.;
-        for (;; ++k) {
-            t = from + (double)k * t2 + 1e-6;
-            const int64_t done = early * (int64_t)((t - free_early) / t2) + (t > free_late ? late * (int64_t)((t - free_late) / t2) : 0);
-            if (t >= free_late && done >= n2) break;
-        }
-        if (side == 0 || t < end) end = t;
-    }
-    return end;
-}
-// The same for the whole chip.  Workgroups are dealt to the engines in turn and stay there, so a stage that would just fit
-// beside the other over the whole chip does not if one engine is a unit short: 224 workgroups of dQ (two rounds on the 116
-// units that 140 of dK/dV leave) took a third round, 553 us of dK/dV alone, 688 together.
-inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
-    const int64_t n = n1 + n2, kinds[4] = {0, (n1 + kEngines - 1) % kEngines, n1 % kEngines, (n + kEngines - 1) % kEngines};  // engines of every kind
-    double end = 0.;
-    for (const int64_t e : kinds) {
-        const int64_t first = n1 > e ? (n1 - e + kEngines - 1) / kEngines : 0, both = n > e ? (n - e + kEngines - 1) / kEngines : 0;
-        const double t = engine_end(first, t1, both - first, t2);
-        if (t > end) end = t;
+// When the chip is done with n workgroups that take walk(0), walk(1), .. us in the order of dispatch.  Workgroups are dealt
+// to the shader engines in turn and stay there, on whichever unit of the engine comes free first; the first engine, which
+// has as many as any, stands for all.  (Counted over the whole chip, 224 workgroups of dQ just fit twice on the 116 units
+// that 140 of dK/dV leave; they took a third round, 553 us of dK/dV alone, 688 together.)
+constexpr int64_t kEngines = 32, kEngineUnits = kComputeUnits / kEngines;
+template <typename WALK>
+inline double dispatch_end(int64_t n, WALK&& walk) {
+    double unit[kEngineUnits] = {}, end = 0.;
+    for (int64_t i = 0; i < n; i += kEngines) {
+        int u = 0;
+        for (int j = 1; j < kEngineUnits; ++j) u = unit[j] < unit[u] ? j : u;
+        unit[u] += walk(i);
+        if (unit[u] > end) end = unit[u];
     }
     return end;
 }
@@ -337,8 +316,8 @@ inline double two_stage_end(int64_t n1, double t1, int64_t n2, double t2) {
 // D = 64, offset 7038, 685 / 805 / 678; 9224 rows, 20 and 5 heads, offset 9106, 1430 / 1602 / 1392).  1356 shapes with
 // offsets above half: 0.690 of the time of one stage after the other with the causal estimates, 17 of them more than 3 %
 // above it; with this rule 0.671 and 4 (5 % in one round of dK/dV beside one of dQ: 5860 rows of 8 heads 435 / 456).
-// Offsets of 0.35 to 0.5 of the keys, 80 shapes beyond 300 us: 0.90 and 0.87; below a third the gain is a hundredth and
-// some lose.
+// Offsets of a third to half of the keys, 182 shapes: 0.758 and 0.736.  Below a third the causal estimates stay: none of
+// 363 shapes was slower with them than one stage after the other.
 inline bool even_walks(int64_t S, int64_t Skv, int64_t off) { return 3 * off >= Skv && 3 * (Skv - off) <= 2 * S; }
 // The share of the (row, key) pairs that are visible there, and what a workgroup of either stage takes on average, in us.
 inline double even_share(int64_t S, int64_t Skv, int64_t off) {
@@ -351,17 +330,33 @@ inline double even_dq_time(int64_t S, int64_t Skv, int64_t off, int64_t q_rows, 
 inline double even_dkdv_time(int64_t S, int64_t Skv, int64_t off, int32_t G, int32_t nsplit, int32_t D) {
     return step_share(D) * kDkdvStep * (double)((S + 31) / 32 * G) * even_share(S, Skv, off) / nsplit + kDkdvFixed;
 }
+// The stage with the longer workgroups goes first, the other fills its last round.
+inline bool even_dq_first(int64_t S, int64_t Skv, int64_t off, int32_t Hq, int32_t Hkv, int64_t q_rows, int32_t nsplit, int32_t D) {
+    return even_dq_time(S, Skv, off, q_rows, D) > even_dkdv_time(S, Skv, off, Hq / Hkv, nsplit, D);
+}
 // Work split for even walks: of 1 .. `most` chunks per tile (what the workspace has room for) the one is taken with which
-// the two stages, the longer workgroups first, and the reduction of the partial sums end soonest.
+// both stages, every workgroup with its own walk, and the reduction of the partial sums end soonest.  (With the mean walk
+// for all, offsets below half the keys got too few chunks: 4 x 8695 rows of 4 heads, D = 64, offset 3007, one chunk
+// instead of two or three, 914 us instead of 819.)  A few microseconds of host time; beyond 2^20 workgroups it is not spent.
 inline int32_t dkdv_full_splits(int64_t B, int64_t S, int64_t Skv, int32_t Hq, int32_t Hkv, int32_t D, int32_t most, int64_t off = INT32_MAX) {
-    const int64_t tiles = (Skv + 255) / 256 * Hkv * B, q_rows = 128 * dq_row_blocks(B, S, Hq);
-    const int64_t n_q = (S + q_rows - 1) / q_rows * Hq * B;
-    const double t_q = even_dq_time(S, Skv, off, q_rows, D);
+    if (off > Skv) off = Skv;
+    const int32_t G = Hq / Hkv;
+    const int64_t heads_kv = Hkv * B, heads_q = Hq * B, q_rows = 128 * dq_row_blocks(B, S, Hq), ranks = (S + q_rows - 1) / q_rows, n_q = ranks * heads_q;
+    const int64_t tiles = (Skv + kOrderTile - 1) / kOrderTile * heads_kv;
+    if (most <= 1 || tiles * most + n_q > (int64_t)1 << 20) return most;
+    const double q_step = step_share(D) * dq_step(q_rows);
     int32_t best = 1;
     double best_end = 0.;
     for (int32_t n = 1; n <= most; ++n) {
-        const double t = even_dkdv_time(S, Skv, off, Hq / Hkv, n, D);
-        double end = t >= t_q ? two_stage_end(tiles * n, t, n_q, t_q) : two_stage_end(n_q, t_q, tiles * n, t);
+        const bool q_first = even_dq_first(S, Skv, off, Hq, Hkv, q_rows, n, D);
+        const double kv_step = step_share(D) * kDkdvStep / n;
+        const int64_t n_kv = tiles * n, first = q_first ? n_q : n_kv;
+        double end = dispatch_end(n_kv + n_q, [&](int64_t i) {
+            const int64_t wg = i < first ? i : i - first;
+            if ((i < first) != q_first) return kv_step * dkdv_tile_steps((int32_t)(wg / heads_kv / n), (int32_t)S, (int32_t)off, G) + kDkdvFixed;
+            const int64_t rows = (ranks - wg / heads_q) * q_rows, keys = (rows < S ? rows : S) + off;  // longest tile first
+            return q_step * (double)(((keys < Skv ? keys : Skv) + 31) / 32) + kDqFixed;
+        });
         if (n > 1) end += dkdv_reduce_time(B, Skv, Hkv, D, n);
         if (n == 1 || end < best_end) { best = n; best_end = end; }
     }

@@ -91,7 +91,7 @@ int main() {
     CHECK(dkdv_full_splits(B, S, Skv, Hq, Hkv, D, 8) >= 1);
     CHECK(fwd_key_groups(1, (int64_t)1 << 30, (int64_t)1 << 30, 0, 1) == 1);
     // a round and a half of equal workgroups takes two; jobs that fit beside a late round cost nothing
-    if (two_stage_end(384, 10., 0, 1.) < 19.9 || two_stage_end(128, 10., 256, 5.) > 10.1) { printf("two_stage_end\n"); return 1; }
+    if (dispatch_end(384, [](int64_t) { return 10.; }) < 19.9 || dispatch_end(384, [](int64_t i) { return i < 128 ? 10. : 5.; }) > 10.1) { printf("dispatch_end\n"); return 1; }
     printf("ok %ld %ld %ld\n", equal, full, cut);
     return equal > 100 && full > 100 && cut > 100 ? 0 : 2;
 }
@@ -192,7 +192,7 @@ int main() {
         const DkdvChunks c = dense_chunks(B, S, S, off, Hq, Hkv, D);
         if (c.len > 0 || (int64_t)c.n_chunks * Hkv * B + (S + q_rows - 1) / q_rows * Hq * B <= kComputeUnits) continue;
         ++seen;
-        const bool q_first = even_dq_time(S, S, off, q_rows, D) > even_dkdv_time(S, S, off, G, c.nsplit, D);
+        const bool q_first = even_dq_first(S, S, off, Hq, Hkv, q_rows, c.nsplit, D);
         const double now = simulate(B, S, S, off, Hq, Hkv, D, c.nsplit, q_first), plain = simulate(B, S, S, off, Hq, Hkv, D, most, false);
         log_sum += log(now / plain);
         if (now > 1.08 * plain) ++worse;
