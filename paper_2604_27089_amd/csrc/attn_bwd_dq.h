@@ -480,7 +480,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         const int row0 = wrow0 + 32 * qb;
-        store_rows<D>(dqacc[qb], p.scale, smem + wave * (32 * D * 2), S - row0, [&](int row) __attribute__((always_inline)) { return out + p.qmap.off(row0 + row); });
+        if (row0 < S) store_rows<D>(dqacc[qb], p.scale, smem + wave * (32 * D * 2), S - row0, [&](int row) __attribute__((always_inline)) { return out + p.qmap.off(row0 + row); });
     }
 }
 

@@ -410,7 +410,8 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_kernel(FwdParams p) {
     // partial result it has just merged)
     char* const buf = reinterpret_cast<char*>(smem) + rb * (KS == 1 ? D * 64 : D * 128);
     __bf16* const ob = p.o + ((size_t)b * S * p.Hq + h) * D;
-    store_rows<D>(oacc, inv, buf, S - wrow0, [&](int row) __attribute__((always_inline)) { return ob + p.qmap.off(wrow0 + row); });
+    if (wrow0 < S)  // a short sequence leaves waves without rows
+        store_rows<D>(oacc, inv, buf, S - wrow0, [&](int row) __attribute__((always_inline)) { return ob + p.qmap.off(wrow0 + row); });
     if (qrow < S && hi == 0) p.lse[((size_t)b * p.Hq + h) * S + qrow] = (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2;
 }
 
