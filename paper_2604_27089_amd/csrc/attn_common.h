@@ -27,6 +27,11 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// Branches of the hand-scheduled loops: the rare side goes out of line, so that the usual path takes no jump.
+#define SP_LIKELY(x) __builtin_expect(!!(x), 1)
+#define SP_UNLIKELY(x) __builtin_expect(!!(x), 0)
+template <int N> using Int = std::integral_constant<int, N>;
+
 // compile-time loop: f(std::integral_constant<int, I>{}) for I in [B, E)
 template <int B, int E, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -212,8 +217,8 @@ __device__ __forceinline__ void lds_wait(u32x2& x, u32x2& y) {
 //     before the MFMA (operands come from LDS reads, from earlier MFMAs, or from
 //     arithmetic done at least one operand slot earlier);
 //   - the vector ALU reads an MFMA's result only after enough later instructions
-//     have issued to cover the 8-pass MFMA's result latency (in the kernels: two
-//     independent MFMAs, or the vector-ALU chunk of an earlier step);
+//     have issued to cover the 4-pass MFMA's result latency (in the kernels: two
+//     independent MFMAs);
 //   - back-to-back MFMAs on the same accumulator are interlocked by hardware.
 // MFMAs ignore the EXEC mask: code that contains them must only be skipped by a
 // truly scalar branch, so every wave-uniform condition guarding such code has
@@ -221,54 +226,21 @@ __device__ __forceinline__ void lds_wait(u32x2& x, u32x2& y) {
 // Volatile assembly statements keep their order, which is what orders an MFMA
 // after the wait that covers its operands.  W >= 0: that wait rides in the same
 // statement.
-//   mfma_v  : accumulator in vector registers       mfma_vc : ... starting from another tile
-//   mfma_a  : accumulator in accumulation registers
-//   *_ab    : the B operand lives in accumulation registers (resident operands)
+//   mfma16_v : accumulator in vector registers       mfma16_vc : ... starting from another tile
+//   mfma16_a : accumulator in accumulation registers
+//   *_ab     : the B operand lives in accumulation registers (resident operands)
 // ---------------------------------------------------------------------------
-template <int W>
-__device__ __forceinline__ void mfma_v(f32x16& acc, const u32x4& a, const bf16x8& b) {
-    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b), "n"(W));
-    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b));
-}
-template <int W>
-__device__ __forceinline__ void mfma_v(f32x16& acc, const u32x4& a, const u32x4& b) {
-    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b), "n"(W));
-    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_vc(f32x16& acc, const u32x4& a, const bf16x8& b, const f32x16& c) {
-    asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "v"(b), "v"(c));
-}
-__device__ __forceinline__ void mfma_vc(f32x16& acc, const u32x4& a, const u32x4& b, const f32x16& c) {
-    asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "v"(b), "v"(c));
-}
-__device__ __forceinline__ void mfma_a(f32x16& acc, const u32x4& a, const u32x4& b) {
-    asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b));
-}
-template <int W>
-__device__ __forceinline__ void mfma_a_w(f32x16& acc, const u32x4& a, const u32x4& b) {
-    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b), "n"(W));
-    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b));
-}
-template <int W>
-__device__ __forceinline__ void mfma_v_ab(f32x16& acc, const u32x4& a, const bf16x8& b) {
-    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "a"(b), "n"(W));
-    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "a"(b));
-}
-template <int W>
-__device__ __forceinline__ void mfma_vc_ab(f32x16& acc, const u32x4& a, const bf16x8& b, const f32x16& c) {
-    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%4)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c), "n"(W));
-    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c));
-}
 // x = the lane's bit of `lanes` ? -inf : x.  One select per register as assembly: written in C++, a run of selects on one
 // flag becomes a branch around moves, and its copies of whole accumulator tiles took the dQ stage with one row block
 // (packed documents) from 241 to 256 vector registers and moves between the register files.  The compiler does not see
 // that the selects read a mask that a compare may just have written: two wait states, in a statement that hands the mask
 // on, so that no select can be placed before it.
-__device__ __forceinline__ void hide_lanes(f32x16& x, uint64_t lanes) {
+template <typename TILE>
+__device__ __forceinline__ void hide_lanes(TILE& x, uint64_t lanes) {
     const float hidden = -__builtin_inff();
     asm("s_nop 1" : "+s"(lanes));
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < (int)(sizeof(TILE) / 4); ++r) {
         float v = x[r];
         asm(SP_MASK_PRE "v_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
         x[r] = v;
@@ -277,15 +249,67 @@ __device__ __forceinline__ void hide_lanes(f32x16& x, uint64_t lanes) {
 // at most N of this wave's global loads (register and LDS destinations) are still in flight
 template <int N>
 __device__ __forceinline__ void vmem_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// Waits that tie the values they cover: used where the awaited registers are then combined into wider
-// operands (the combination must not be scheduled before the wait).
-template <int N>
-__device__ __forceinline__ void lds_wait4(u32x4& a, u32x4& b, u32x4& c, u32x4& d) {
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(SP_LGKM(N)));
+// ---------------------------------------------------------------------------
+// v_mfma_f32_16x16x32_bf16: C[16x16] += A[16x32] * B[32x16] per wave.  With lane l, lo = l % 16, g = l / 16:
+//   A operand: lane holds A[lo][8*g + e], e = 0..7;   B operand: lane holds B[8*g + e][lo]
+//   C/D      : lane holds C[4*g + r][lo] in register r = 0..3
+// Two C tiles (rows 0-15 and 16-31), rounded to bf16, are together an operand over a contraction index of 32 in the
+// order {4*g + e, 16 + 4*g + e}, e = 0..3; the other operand follows that order with two transposing reads.
+//
+// Why this shape: the long kernels run at the clock that the board's power leaves them (1.65 to 2.0 of 2.4 GHz), so what
+// counts is energy per product, and per product this shape moves half as many accumulator registers as 32x32x16.
+// Register-only loops on random data, every unit busy: 32x32x16 1.78-1.81 PFLOP/s at 1.77 GHz, 16x16x32 2.00-2.06
+// PFLOP/s at 2.07 GHz, 2.09 where each instruction keeps one operand of the one before (both shapes keep the matrix
+// pipe 93 to 97 % busy; on zeros, at the full clock, both reach 2.4).
+//
+// The assembly forms follow the rules above.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-template <int N>
-__device__ __forceinline__ void lds_wait4(u32x2& a, u32x2& b, u32x2& c, u32x2& d) {
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(SP_LGKM(N)));
+template <int W, typename B>
+__device__ __forceinline__ void mfma16_v(f32x4& acc, const u32x4& a, const B& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b));
+}
+template <int W, typename B>
+__device__ __forceinline__ void mfma16_vc(f32x4& acc, const u32x4& a, const B& b, const f32x4& c) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%4)\n\t" SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "v"(b), "v"(c), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "v"(b), "v"(c));
+}
+template <int W, typename B>
+__device__ __forceinline__ void mfma16_v_ab(f32x4& acc, const u32x4& a, const B& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "a"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "a"(b));
+}
+template <int W, typename B>
+__device__ __forceinline__ void mfma16_vc_ab(f32x4& acc, const u32x4& a, const B& b, const f32x4& c) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%4)\n\t" SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c));
+}
+template <int W>
+__device__ __forceinline__ void mfma16_a(f32x4& acc, const u32x4& a, const u32x4& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b));
+}
+
+// The swizzle of tiles read for these shapes: chunk c of row r at chunk position c ^ swz16<D>(r).  Free of bank
+// conflicts for row-major operand reads (16 consecutive rows, same chunk) and for transposing reads (8 consecutive rows
+// x 2 consecutive chunks per half-wave).  It depends on row % 16 only, so blocks of 16 rows are a constant apart.
+template <int D>
+__device__ __forceinline__ int swz16(int row) {
+    return D == 128 ? ((row & 7) << 1) | ((row >> 3) & 1) : ((row & 6)) | ((row >> 3) & 1);
+}
+// Byte offset of the 16-byte operand chunk (row, chunk) in such a tile.
+template <int D>
+__device__ __forceinline__ int tile16_off_b128(int row, int chunk) {
+    return row * (D * 2) + ((chunk ^ swz16<D>(row)) * 16);
+}
+// Byte offset that lane `lane` passes to the transposing read so that it receives rows 4*g .. 4*g+3 of column col0 + lo.
+template <int D>
+__device__ __forceinline__ int tile16_off_tr(int col0, int lane) {
+    const int row = 4 * (lane >> 4) + ((lane >> 2) & 3), col = col0 + 4 * (lane & 3);
+    return row * (D * 2) + (((col >> 3) ^ swz16<D>(row)) * 16) + (col & 7) * 2;
 }
 
 // Per-lane description of the DMA loads that fill one ROWS x D tile with NW waves.
@@ -293,7 +317,7 @@ __device__ __forceinline__ void lds_wait4(u32x2& a, u32x2& b, u32x2& c, u32x2& d
 // `wave` must be wave-uniform in the scalar sense (readfirstlane) so that LDS
 // destinations are scalar.  Global addresses are a scalar tile base plus a 32-bit
 // per-lane byte offset (rows of a tile span far less than 4 GiB).
-template <int D, int ROWS, int NW = 4>
+template <int D, int ROWS, int NW = 4, bool S16 = false>
 struct TileDma {
     static constexpr int CH = D / 8;
     static constexpr int RPI = 64 / CH;             // rows per instruction
@@ -309,7 +333,7 @@ struct TileDma {
         for (int k = 0; k < PER_WAVE; ++k) {
             const int i = wave + NW * k;
             row[k] = RPI * i + lane / CH;
-            chunk_b[k] = (uint32_t)(((lane % CH) ^ swz<D>(row[k])) * 16);
+            chunk_b[k] = (uint32_t)(((lane % CH) ^ (S16 ? swz16<D>(row[k]) : swz<D>(row[k]))) * 16);
         }
     }
     // The K-th of this wave's PER_WAVE loads for the tile whose first row is at `tile` (a scalar
@@ -360,6 +384,32 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float sc
             w[0] = pack_bf16(acc[db][4 * g + 0] * scale, acc[db][4 * g + 1] * scale);
             w[1] = pack_bf16(acc[db][4 * g + 2] * scale, acc[db][4 * g + 3] * scale);
             *reinterpret_cast<u32x2*>(buf + at(lo, 4 * db + g) + 8 * hi) = w;
+        }
+    asm volatile("" ::: "memory");  // LDS accesses of a wave execute in order: keeping the order is all it takes
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int row = RPI * i + lane / CH, chunk = lane % CH;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(buf + at(row, chunk));
+        if (row < rows) *reinterpret_cast<u32x4*>(address(row) + 8 * chunk) = v;
+    }
+    asm volatile("" ::: "memory");
+}
+
+// The same for accumulators of 16x16x32: acc[rb][db] holds rows 16*rb + lo, columns 16*db + 4*g + r.
+template <int D, typename ADDR>
+__device__ __forceinline__ void store_rows16(const f32x4 (&acc0)[D / 16], const f32x4 (&acc1)[D / 16], float scale, char* buf, int rows, ADDR&& address) {
+    constexpr int CH = D / 8, RPI = 64 / CH;  // chunks per row, rows per store instruction
+    const int lane = __lane_id(), lo = lane & 15, g = lane >> 4;
+    auto at = [](int row, int chunk) __attribute__((always_inline)) { return row * (D * 2) + ((chunk ^ ((D == 128 ? row : row >> 1) & (CH - 1))) * 16); };
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int db = 0; db < D / 16; ++db) {
+            const f32x4& a = rb == 0 ? acc0[db] : acc1[db];
+            u32x2 w;
+            w[0] = pack_bf16(a[0] * scale, a[1] * scale);
+            w[1] = pack_bf16(a[2] * scale, a[3] * scale);
+            *reinterpret_cast<u32x2*>(buf + at(16 * rb + lo, 2 * db + (g >> 1)) + 8 * (g & 1)) = w;
         }
     asm volatile("" ::: "memory");  // LDS accesses of a wave execute in order: keeping the order is all it takes
 #pragma unroll
