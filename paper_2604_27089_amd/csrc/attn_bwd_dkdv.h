@@ -274,6 +274,10 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     const int last_hidden = wkey0 + KPW - 2 - p.off;  // last row that does not see all the wave's keys
     const int it_mask_lo = last_hidden >= 0 ? last_hidden / BMQ : -1;
     const int it_mask_hi = (wave_hi_min - 31 + BMQ - 1) / BMQ;
+    // ... there, the keys (their lanes) that no row of the tiles end_it + 1 .. dead_it sees: kept from step to step until a tile
+    // in which some key's document ends, or the next head's last tile
+    uint64_t dead[KB] = {};
+    int end_it = -1, dead_it = -1;
     {
         if constexpr (!L::kVRegs) {
             TileDma<D, BNK, kWaves, true> vdma;
@@ -479,14 +483,22 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
                                 }
                             }
                         }
-                        if (SP_UNLIKELY(cur_it >= it_mask_hi)) {  // rows at or past the end of the first key's document or of the sequence
+                        if (VARLEN ? cur_it >= it_mask_hi : SP_UNLIKELY(cur_it >= it_mask_hi)) {  // rows at or past the end of the first key's document or of the sequence
                             const int q0 = cur_it * BMQ;
                             bool inside = !VARLEN;
-                            if (VARLEN) {
+                            if (VARLEN && (cur_it <= end_it || cur_it > dead_it)) {
+                                dead_it = cur_it;
                                 bool ends = false;
 #pragma unroll
                                 for (int k = 0; k < KB; ++k) ends = ends || (khi_l[k] > q0 && khi_l[k] < q0 + BMQ);
                                 inside = __builtin_amdgcn_ballot_w64(ends) != 0;
+                                // keys ascend, and so do their documents' ends: the next one, going down, is that of the last hidden key
+                                end_it = inside ? cur_it : -1;
+#pragma unroll
+                                for (int k = 0; k < KB; ++k) {
+                                    dead[k] = inside ? 0 : __builtin_amdgcn_ballot_w64(khi_l[k] <= q0);
+                                    if (dead[k] != 0) end_it = (__builtin_amdgcn_readlane(khi_l[k], 63 - __builtin_clzll(dead[k])) - 1) / BMQ;
+                                }
                             }
                             if (inside) {
                                 asm volatile("" ::: "memory");  // keeps this a branch
@@ -497,16 +509,13 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
                                     for (int i = 0; i < 8; ++i) sacc[i / 4][k][i % 4] = 16 * (i / 4) + i % 4 < lim ? sacc[i / 4][k][i % 4] : -__builtin_inff();
                                 }
                             } else {
-                                uint64_t dead[KB], any = 0;
+                                uint64_t any = 0;
 #pragma unroll
-                                for (int k = 0; k < KB; ++k) any |= dead[k] = __builtin_amdgcn_ballot_w64(khi_l[k] <= q0);
+                                for (int k = 0; k < KB; ++k) any |= dead[k];
                                 if (any != 0) {
                                     asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                                    for (int k = 0; k < KB; ++k) {
-                                        hide_lanes(sacc[0][k], dead[k]);
-                                        hide_lanes(sacc[1][k], dead[k]);
-                                    }
+                                    for (int k = 0; k < KB; ++k) hide_lanes(sacc[0][k], sacc[1][k], dead[k]);
                                 }
                             }
                         }

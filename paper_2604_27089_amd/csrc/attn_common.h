@@ -236,15 +236,25 @@ __device__ __forceinline__ void lds_wait(u32x2& x, u32x2& y) {
 // that the selects read a mask that a compare may just have written: two wait states, in a statement that hands the mask
 // on, so that no select can be placed before it.
 template <typename TILE>
-__device__ __forceinline__ void hide_lanes(TILE& x, uint64_t lanes) {
+__device__ __forceinline__ void select_hidden(TILE& x, uint64_t lanes) {
     const float hidden = -__builtin_inff();
-    asm("s_nop 1" : "+s"(lanes));
 #pragma unroll
     for (int r = 0; r < (int)(sizeof(TILE) / 4); ++r) {
         float v = x[r];
         asm(SP_MASK_PRE "v_cndmask_b32 %0, %0, %1, %2" : "+v"(v) : "v"(hidden), "s"(lanes));
         x[r] = v;
     }
+}
+template <typename TILE>
+__device__ __forceinline__ void hide_lanes(TILE& x, uint64_t lanes) {
+    asm("s_nop 1" : "+s"(lanes));
+    select_hidden(x, lanes);
+}
+template <typename TILE>
+__device__ __forceinline__ void hide_lanes(TILE& x, TILE& y, uint64_t lanes) {  // two tiles, one wait
+    asm("s_nop 1" : "+s"(lanes));
+    select_hidden(x, lanes);
+    select_hidden(y, lanes);
 }
 // at most N of this wave's global loads (register and LDS destinations) are still in flight
 template <int N>
