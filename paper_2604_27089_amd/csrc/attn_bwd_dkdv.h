@@ -242,7 +242,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     auto advance_load = [&]() __attribute__((always_inline)) {
         if (SP_LIKELY(dc.left > 0)) {  // past the last step the cursor stays (the padding steps re-read the last tile)
             --dc.left;
-            if (SP_UNLIKELY(dc.it == it_begin)) {  // first tile of a head -> last tile of the next
+            if (SP_RARE(VARLEN, dc.it == it_begin)) {  // first tile of a head -> last tile of the next
                 dc.it = it_end - 1; q_head_b += (size_t)D * 2; dc.aux += aux_jump_b;
             } else {
                 dc.it -= 1; dc.aux -= 256;
@@ -259,7 +259,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
         } else {
             constexpr int KK = (K - 1) % PW;
             uint32_t off = voff[KK];
-            if (SP_UNLIKELY(dc.it == it_tail)) off = lane_off(KK, S - 1 - dc.it * BMQ);  // rare
+            if (SP_RARE(VARLEN, dc.it == it_tail)) off = lane_off(KK, S - 1 - dc.it * BMQ);  // rare
             const char* src = K <= PW ? dc.q : dc.dO;
             char* dst = smem + (K <= PW ? QS : DOS) + buf * TILE_B + (wave + kWaves * KK) * 1024;
             dma16(src + off, dst);
@@ -464,7 +464,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
                         // its rows: all its S' take one select on a per-lane flag (a select, not arithmetic: S'
                         // of such a pair may be anything, a NaN included); upper limits are compared element by
                         // element only on the row tile in which some key's document (dense: the sequence) ends.
-                        if (SP_UNLIKELY(cur_it <= it_mask_lo || step_no >= total)) {
+                        if (SP_RARE(VARLEN, cur_it <= it_mask_lo || step_no >= total)) {
                             const int q0 = cur_it * BMQ;
                             if (step_no >= total || q0 + BMQ - 1 + p.off < wkey0) {
                                 asm volatile("" ::: "memory");  // keeps this a branch
@@ -483,7 +483,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
                                 }
                             }
                         }
-                        if (VARLEN ? cur_it >= it_mask_hi : SP_UNLIKELY(cur_it >= it_mask_hi)) {  // rows at or past the end of the first key's document or of the sequence
+                        if (SP_RARE(VARLEN, cur_it >= it_mask_hi)) {  // rows at or past the end of the first key's document or of the sequence
                             const int q0 = cur_it * BMQ;
                             bool inside = !VARLEN;
                             if (VARLEN && (cur_it <= end_it || cur_it > dead_it)) {

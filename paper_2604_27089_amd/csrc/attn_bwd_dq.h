@@ -191,7 +191,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     // The tail tile is the last one the cursor can reach, and the cursor stays on it: its clamped lane offsets
     // replace the regular ones for good.
     auto enter_tile = [&]() __attribute__((always_inline)) {
-        if (SP_UNLIKELY(dc.jt == jt_tail)) {  // rare
+        if (SP_RARE(VARLEN, dc.jt == jt_tail)) {  // rare
 #pragma unroll
             for (int K = 0; K < PW; ++K) voff[K] = lane_off(K, Skv - 1 - dc.jt * BN);
         }
@@ -208,7 +208,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         if (SP_LIKELY(dc.left > 0)) {  // past the last step the cursor stays (the padding steps re-read the last tile)
             --dc.left; dc.jt += 1;
             dc.k += tile_step_b; dc.v += tile_step_b;
-            if (SP_UNLIKELY((dc.jt & tiles_per_chunk_mask) == 0)) {  // rare: the first tile of the next peer's chunk
+            if (SP_RARE(VARLEN, (dc.jt & tiles_per_chunk_mask) == 0)) {  // rare: the first tile of the next peer's chunk
                 const size_t off = p.kvmap.off(dc.jt * BN) * 2;
                 dc.k = k_head + off; dc.v = v_head + off;
             }
@@ -383,7 +383,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                         // them: all its S' take one select on a per-lane flag (a select, not arithmetic: S' of
                         // such a pair may be anything, a NaN included); lower limits are compared element by element
                         // only on the step in which some row's document starts.
-                        if (SP_UNLIKELY(step_no >= mask_from)) {
+                        if (SP_RARE(VARLEN, step_no >= mask_from)) {
                             if (step_no >= dead_from) {
                                 asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
