@@ -6,8 +6,8 @@
 // Three stages, no atomics (bitwise reproducible):
 //   delta : Delta_i = dO_i . O_i and the per-row seeds -LSE_i/scale, -Delta_i
 //           (this file; HBM-bound, fp32 out)
-//   dkdv  : attn_bwd_dkdv.h, and the sum of its partial results here
-//   dq    : attn_bwd_dq.h
+//   dkdv  : attn_bwd_dkdv.h (long launches: attn_bwd_dkdv16.h), and the sum of its partial results here
+//   dq    : attn_bwd_dq.h (attn_bwd_dq16.h)
 // The last two are launched together (attn_bwd_matrix.h).
 // P is rebuilt from the saved LSE: P_ij = exp(scale*s_ij - LSE_i); S and dP
 // are evaluated in both matrix kernels.
@@ -17,6 +17,11 @@ namespace {
 
 using namespace sp;
 
+#ifdef SP_BWD_ALWAYS_LONG  // a build for tests: small shapes reach the edges of the long launches' programs
+constexpr bool kAlwaysLong = true;
+#else
+constexpr bool kAlwaysLong = false;
+#endif
 
 // ------------------------------------------------------------------ delta
 // One 16-byte vector of O and dO per lane, D/8 lanes per (row, head).  The grid covers the padded row range
@@ -123,7 +128,9 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
         if (hipGetLastError() != hipSuccess) return SP_ERR_LAUNCH;
     }
     if (a.stages & (SP_BWD_STAGE_DKDV | SP_BWD_STAGE_DQ)) {
-        const sp_status r = D == 64 ? launch_attn_bwd_matrix_d64(a, st) : launch_attn_bwd_matrix_d128(a, st);
+        const bool long_launch = kAlwaysLong || bwd_long_launch(a.B, a.S, a.Skv, a.off, a.Hq, a.D, a.row_lo ? a.n_docs : 0);
+        const sp_status r = D == 64 ? (long_launch ? launch_attn_bwd_matrix_long_d64(a, st) : launch_attn_bwd_matrix_d64(a, st))
+                                    : (long_launch ? launch_attn_bwd_matrix_long_d128(a, st) : launch_attn_bwd_matrix_d128(a, st));
         if (r != SP_OK) return r;
     }
     if ((a.stages & SP_BWD_STAGE_DKDV) && a.chunks.nsplit > 1) {

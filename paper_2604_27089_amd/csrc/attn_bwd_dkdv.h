@@ -6,10 +6,10 @@
 //   dK_j = scale * sum_{a in group} sum_{i>=j} dS_ij q_i,   dS_ij = P_ij (dO_i.v_j - Delta_i)
 //
 // One workgroup = 4 waves = 256 keys of one KV head, one wave per SIMD; a wave
-// owns 64 keys (four 16-key blocks): their K stays in registers as MFMA B operand,
-// their V sits in LDS for the whole kernel (D = 64: in registers too), and their
-// dK, dV live in accumulation registers that only MFMAs touch.  A streamed operand
-// fetched from LDS feeds four MFMAs (one per key block).
+// owns 64 keys (two 32-key blocks): their K stays in registers as MFMA B operand,
+// their V sits in LDS for the whole kernel, and their dK, dV live in 256
+// accumulation registers that only MFMAs touch.  A streamed operand fetched from
+// LDS feeds two MFMAs (one per key block).
 //
 // The Q/dO rows of the G query heads of the group stream through a ring of four
 // 32-row LDS tiles (direct global->LDS loads issued two steps ahead,
@@ -23,21 +23,15 @@
 //        already valid A operands; dO^T and Q^T come from transposing LDS reads)
 //
 // A lone wave issues in order, so the vector-ALU work is interleaved by hand
-// into the MFMA stream, a little behind every MFMA.  One loop body runs four phases
-// of D/16 operand slots (four MFMAs per slot):
+// into the MFMA stream.  One loop body runs four phases of D/16 operand slots
+// (two MFMAs per slot):
 //   S(u) | dK(u-1) + first half of exp | dP(u) + second half of exp | dV(u) + dS products
 // i.e. the dK contraction of a step is deferred into the next body, where it
 // and the dP contraction give the exponentials of the new step something to
 // hide behind.  The body is straight-line code: every LDS operand read is
-// asynchronous, issued three or four slots ahead with exact partial waits, the tile loads
+// asynchronous, issued two slots ahead with exact partial waits, the tile loads
 // of step u+2 are spread over the S phase, and the body is instantiated once per
 // ring position so that all LDS addresses are immediates.
-//
-// What bounds it: power.  With 32x32x16 MFMAs a step took 2660 cycles at 1.80 GHz, with 16x16x32
-// 3000 at 2.12 (pipe time 2048): 32768 rows, 4 heads, D = 128, 1683 -> 1595 us, 16 x 4096
-// rows 465 -> 446; D = 64 979 -> 908 and 270 -> 254 us (V in registers included; at 2.3 GHz).
-// Left out one at a time in the 32x32x16 kernel: vector ALU -16 % of the time, LDS reads
-// -10 %, tile loads -5 %, V reads alone -3 %; moving them about inside a slot changed nothing.
 //
 // This file holds the workgroup's program; attn_bwd_matrix.h has the kernel that
 // runs it, beside the one of attn_bwd_dq.h.
@@ -86,11 +80,19 @@ __device__ __forceinline__ size_t part_offset(int64_t bg, int nsplit, int Skv, i
     return ((size_t)bg * nsplit * Skv + (size_t)first * kOrderTile + (size_t)split * keys) * D;
 }
 
+// 16 accumulator registers from the four 16-byte per-row reads of one lane
+__device__ __forceinline__ void seeds_to_acc(f32x16& acc, const u32x4 (&s)[4]) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const uint32_t u = s[r / 4][r % 4];  // (through a scalar: bit-casting a vector element expression directly is not reliable)
+        acc[r] = __uint_as_float(u);
+    }
+}
+
 template <int D>
 struct Lds {
     static constexpr int TILE_B = BMQ * D * 2;
-    static constexpr bool kVRegs = D == 64;  // V operands resident in registers (at D = 128 there is no room for them)
-    static constexpr int QS = 0, DOS = NBUF * TILE_B, VS = 2 * NBUF * TILE_B, VW_B = kVRegs ? 0 : KPW * D * 2;
+    static constexpr int QS = 0, DOS = NBUF * TILE_B, VS = 2 * NBUF * TILE_B, VW_B = KPW * D * 2;
     static constexpr int AUX = VS + kWaves * VW_B, AUX_SLOT = 1024, AUX_W = NBUF * AUX_SLOT;
     static constexpr int BYTES = AUX + kWaves * AUX_W;
 };
@@ -98,16 +100,15 @@ struct Lds {
 // The work of workgroup `wg` of n_chunks * Hkv * B; smem holds Lds<D>::BYTES, 1 KB aligned.
 template <int D, bool VARLEN, bool SPLIT>
 __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem) {
-    constexpr int NS = D / 16;   // operand slots per phase: (16-row block, contraction step), resp. 16-wide blocks of the head dim
-    constexpr int NK = D / 32;   // contraction steps over the head dim
-    constexpr int KB = KPW / 16; // 16-key blocks of a wave
+    constexpr int NS = D / 16;   // operand slots per phase (contraction steps over the head dim)
+    constexpr int NDB = D / 32;  // 32-wide blocks of the head dim
     constexpr int HALF_B = 16 * D * 2;  // 16 rows of a tile
     using L = Lds<D>;
     constexpr int TILE_B = L::TILE_B, QS = L::QS, DOS = L::DOS, VS = L::VS, VW_B = L::VW_B;
     constexpr int AUX = L::AUX, AUX_SLOT = L::AUX_SLOT, AUX_W = L::AUX_W;
     static_assert(DOS + (NBUF - 1) * TILE_B + HALF_B < 65536, "immediate LDS offsets must fit 16 bits");
 
-    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, g4 = 4 * (lane >> 4);
+    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Earliest key tiles (most rows to visit) first, the chunks of a tile behind each other; KV heads and batch entries vary
     // fastest, so that everybody's longest key tiles are dispatched before anybody's short ones (one after the other, the
@@ -147,49 +148,53 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     const int j0 = jt * BNK;
     const int wkey0 = j0 + KPW * wave;  // first key of this wave
 
-    // resident B operands: K^T (and V^T) columns of this lane's keys
-    bf16x8 kreg[KB][NK], vreg[L::kVRegs ? KB : 1][NK];
+    // resident B operand: K^T columns of this lane's two keys
+    bf16x8 kreg[2][NS];
 #pragma unroll
-    for (int kb_ = 0; kb_ < KB; ++kb_) {
-        const int key = wkey0 + 16 * kb_ + lo;
+    for (int kbk = 0; kbk < 2; ++kbk) {
+        const int key = wkey0 + 32 * kbk + lo;
         const int key_c = key < Skv ? key : Skv - 1;
 #pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
-            kreg[kb_][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(kb + p.kvmap.off(key_c) + 32 * ks + 2 * g4));
-            if constexpr (L::kVRegs) vreg[kb_][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(vb + p.kvmap.off(key_c) + 32 * ks + 2 * g4));
+        for (int kk = 0; kk < NS; ++kk) {
+            kreg[kbk][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(kb + p.kvmap.off(key_c) + 16 * kk + 8 * hi));
         }
     }
     int wave_hi_min = S, wg_hi_max = S;
-    int khi_l[KB] = {};  // packed documents: one past the last row that may see this lane's keys (their document's end)
+    int khi_l[2] = {S, S};  // packed documents: one past the last row that may see this lane's keys (their document's end)
     if (VARLEN) {
         wave_hi_min = __builtin_amdgcn_readfirstlane(p.row_hi[(wkey0 < S ? wkey0 : S - 1)]);
         wg_hi_max = __builtin_amdgcn_readfirstlane(p.row_hi[(j0 + BNK - 1 < S ? j0 + BNK - 1 : S - 1)]);
 #pragma unroll
-        for (int k = 0; k < KB; ++k) {
-            const int key = wkey0 + 16 * k + lo;
-            khi_l[k] = p.row_hi[key < S ? key : S - 1];
+        for (int kbk = 0; kbk < 2; ++kbk) {
+            const int key = wkey0 + 32 * kbk + lo;
+            khi_l[kbk] = p.row_hi[key < S ? key : S - 1];
         }
     }
 
-    f32x4 dkacc[KB][NS], dvacc[KB][NS];
+    f32x16 dkacc[2][NDB], dvacc[2][NDB];
 #pragma unroll
-    for (int k = 0; k < KB; ++k)
+    for (int kbk = 0; kbk < 2; ++kbk)
 #pragma unroll
-        for (int db = 0; db < NS; ++db) dkacc[k][db] = dvacc[k][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { dkacc[kbk][db][r] = 0.f; dvacc[kbk][db][r] = 0.f; }
 
     // LDS addresses of this lane's operand reads; everything that changes per step is an immediate
     const uint32_t sm = lds_addr(smem);
-    uint32_t rb[NK];  // row-major operand (Q, dO rows): row lo (+16 per row block), chunk 4*ks + g
-    uint32_t vr[NK];  // the same chunk of this wave's V rows
+    uint32_t rb[NS];  // row-major operand (Q, dO rows): row lo, chunk 2*kk + hi
+    uint32_t vr[NS];  // the same chunk of this wave's V rows
 #pragma unroll
-    for (int ks = 0; ks < NK; ++ks) {
-        rb[ks] = sm + tile16_off_b128<D>(lo, 4 * ks + (lane >> 4));
-        vr[ks] = rb[ks] + VS + wave * VW_B;
+    for (int kk = 0; kk < NS; ++kk) {
+        rb[kk] = sm + tile_off_b128<D>(lo, 2 * kk + hi);
+        vr[kk] = rb[kk] + VS + wave * VW_B;
     }
-    uint32_t tb[NS];  // transposed operand (Q^T, dO^T): rows 4*g + (0..3) (+16), column 16*db + lo
+    uint32_t tb[2][NDB];  // transposed operand (Q^T, dO^T): rows 8*half + 4*hi + (0..3) (+16 per 16-row step), cols 32*db + ...
 #pragma unroll
-    for (int db = 0; db < NS; ++db) tb[db] = sm + tile16_off_tr<D>(16 * db, lane);
-    const uint32_t ab = sm + AUX + wave * AUX_W + 4 * g4;  // per-row scalars: rows 4*g .. +3 (+16 per row block)
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+            tb[half][db] = sm + tile_off_tr<D>(8 * half + 4 * hi, 32 * db + 16 * (lo >> 4), lo & 15);
+    const uint32_t ab = sm + AUX + wave * AUX_W + 16 * hi;  // per-row scalars: rows 8*g4 + 4*hi .. +3
 
     const int it_begin = (j0 > p.off ? j0 - p.off : 0) / BMQ;  // tile holding the first row that sees the first key
     const int it_end = (wg_hi_max + BMQ - 1) / BMQ;  // exclusive
@@ -216,7 +221,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     // `lim` (tile-relative) re-read row `lim` (they are never used unmasked)
     auto lane_off = [&](int K, int lim) __attribute__((always_inline)) {
         const int row = Dma::RPI * (wave + kWaves * K) + lane / Dma::CH;
-        const uint32_t chunk_b = (uint32_t)(((lane % Dma::CH) ^ swz16<D>(row)) * 16);
+        const uint32_t chunk_b = (uint32_t)(((lane % Dma::CH) ^ swz<D>(row)) * 16);
         return (uint32_t)(row < lim ? row : lim) * stride_b + chunk_b;
     };
     uint32_t voff[PW];
@@ -240,9 +245,9 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     }
     const size_t aux_jump_b = ((size_t)(p.S_pad / 32) + (size_t)(n_it - 1)) * 256;
     auto advance_load = [&]() __attribute__((always_inline)) {
-        if (SP_LIKELY(dc.left > 0)) {  // past the last step the cursor stays (the padding steps re-read the last tile)
+        if (dc.left > 0) {  // past the last step the cursor stays (the padding steps re-read the last tile)
             --dc.left;
-            if (SP_RARE(VARLEN, dc.it == it_begin)) {  // first tile of a head -> last tile of the next
+            if (dc.it == it_begin) {  // first tile of a head -> last tile of the next
                 dc.it = it_end - 1; q_head_b += (size_t)D * 2; dc.aux += aux_jump_b;
             } else {
                 dc.it -= 1; dc.aux -= 256;
@@ -259,7 +264,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
         } else {
             constexpr int KK = (K - 1) % PW;
             uint32_t off = voff[KK];
-            if (SP_RARE(VARLEN, dc.it == it_tail)) off = lane_off(KK, S - 1 - dc.it * BMQ);  // rare
+            if (dc.it == it_tail) off = lane_off(KK, S - 1 - dc.it * BMQ);  // rare
             const char* src = K <= PW ? dc.q : dc.dO;
             char* dst = smem + (K <= PW ? QS : DOS) + buf * TILE_B + (wave + kWaves * KK) * 1024;
             dma16(src + off, dst);
@@ -274,16 +279,10 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     const int last_hidden = wkey0 + KPW - 2 - p.off;  // last row that does not see all the wave's keys
     const int it_mask_lo = last_hidden >= 0 ? last_hidden / BMQ : -1;
     const int it_mask_hi = (wave_hi_min - 31 + BMQ - 1) / BMQ;
-    // ... there, the keys (their lanes) that no row of the tiles end_it + 1 .. dead_it sees: kept from step to step until a tile
-    // in which some key's document ends, or the next head's last tile
-    uint64_t dead[KB] = {};
-    int end_it = -1, dead_it = -1;
     {
-        if constexpr (!L::kVRegs) {
-            TileDma<D, BNK, kWaves, true> vdma;
-            vdma.init(wave, lane, p.kvmap.row_stride);
-            vdma.issue(vb + p.kvmap.off(j0), Skv - 1 - j0, reinterpret_cast<__bf16*>(smem + VS), wave);
-        }
+        TileDma<D, BNK, kWaves> vdma;
+        vdma.init(wave, lane, p.kvmap.row_stride);
+        vdma.issue(vb + p.kvmap.off(j0), Skv - 1 - j0, reinterpret_cast<__bf16*>(smem + VS), wave);
         static_for<1, PW + 1>([&](auto K) { issue_load(K, 3); });  // Q rows of step 0 again, as the stand-in
         static_for<0, GROUP>([&](auto K) { issue_load(K, 0); });
         advance_load();
@@ -293,21 +292,20 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
         __builtin_amdgcn_s_barrier();  // ... and everybody else's
     }
 
-    f32x4 sacc[2][KB], pacc[2][KB];  // [16-row block][key block]
-    u32x4 pp[KB], dsp[KB];  // bf16 A operands [key block]: P of the step, dS of the previous step
+    f32x16 sacc[2], pacc[2];
+    u32x4 pp[2][2], dsp[2][2];  // bf16 A operands [key block][16-row half]: P of the step, dS of the previous step
 #pragma unroll
-    for (int k = 0; k < KB; ++k) pp[k] = dsp[k] = u32x4{0, 0, 0, 0};
+    for (int kbk = 0; kbk < 2; ++kbk)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) { dsp[kbk][c] = u32x4{0, 0, 0, 0}; pp[kbk][c] = u32x4{0, 0, 0, 0}; }
 
     // The operand slots of a body, x = 0 .. 4*NS-1 in the phases S | dK | dP | dV.  Reads of slot x are issued
     // ahead(x) slots early, possibly from the previous body (slots x >= 4*NS name slots of the next body).
-    // Waits happen once per pair of slots, at the even one.  The dP phase takes both row blocks of a contraction step
-    // behind each other: the V operands are read with the first and serve both.
+    // Waits happen once per pair of slots, at the even one.
     constexpr int P4 = 4 * NS;
-    auto nreads = [](int x) constexpr {  // LDS reads of slot x (first slot of a row block: plus the per-row scalars)
+    auto nreads = [](int x) constexpr {  // LDS reads of slot x (first S and dP slots: plus the four per-row reads)
         const int s = x % P4;
-        if (s < NS) return s % NK == 0 ? 2 : 1;
-        if (s >= 2 * NS && s < 3 * NS) return 1 + (s < 2 * NS + 2 ? 1 : 0) + (s % 2 == 0 && !L::kVRegs ? KB : 0);
-        return 2;
+        return s == 0 ? 5 : s < NS ? 1 : s < 2 * NS ? 2 : s == 2 * NS ? 7 : s < 3 * NS ? 3 : 2;
     };
     auto ahead = [](int x) constexpr {
         const int s = x % P4;
@@ -324,33 +322,29 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     };
 
     // in-flight operands (asynchronous reads: see the rule in attn_common.h)
-    u32x4 aq[NS], ad[NS], bv[NK][KB], sds[2], sdp[2];
+    u32x4 aq[NS], ad[NS], bv0[NS], bv1[NS], sds[4], sdp[4];
     u32x2 bq0[NS], bq1[NS], bd0[NS], bd1[NS];
 
-    // reads of slot s (0 .. 4*NS-1) of the body at ring position BUF, in KB parts (one behind each MFMA of the slot that
-    // issues them)
-    auto issue_reads = [&](auto BUFC, auto SC, auto PARTC) __attribute__((always_inline)) {
-        constexpr int BUF = decltype(BUFC)::value, PBUF = (BUF + 3) % NBUF, s = decltype(SC)::value, part = decltype(PARTC)::value;
+    // reads of slot s (0 .. 4*NS-1) of the body at ring position BUF
+    auto issue_reads = [&](auto BUFC, auto SC) __attribute__((always_inline)) {
+        constexpr int BUF = decltype(BUFC)::value, PBUF = (BUF + 3) % NBUF, s = decltype(SC)::value;
         if constexpr (s < NS) {
-            if constexpr (part == 0) {
-                if constexpr (s % NK == 0) sds[s / NK] = lds_async_b128<BUF * AUX_SLOT + 64 * (s / NK)>(ab);
-                aq[s] = lds_async_b128<QS + BUF * TILE_B + (s / NK) * HALF_B>(rb[s % NK]);
-            }
+            if constexpr (s == 0) static_for<0, 4>([&](auto G4) { sds[G4] = lds_async_b128<BUF * AUX_SLOT + 32 * decltype(G4)::value>(ab); });
+            aq[s] = lds_async_b128<QS + BUF * TILE_B>(rb[s]);
         } else if constexpr (s < 2 * NS) {
-            constexpr int t = s - NS;
-            if constexpr (part == 0) bq0[t] = lds_async_tr16<QS + PBUF * TILE_B>(tb[t]);
-            if constexpr (part == 1) bq1[t] = lds_async_tr16<QS + PBUF * TILE_B + HALF_B>(tb[t]);
+            constexpr int t = s - NS, c = t / NDB, db = t % NDB;
+            bq0[t] = lds_async_tr16<QS + PBUF * TILE_B + c * HALF_B>(tb[0][db]);
+            bq1[t] = lds_async_tr16<QS + PBUF * TILE_B + c * HALF_B>(tb[1][db]);
         } else if constexpr (s < 3 * NS) {
-            constexpr int kk = s - 2 * NS, ks = kk / 2, r = kk % 2;
-            if constexpr (part == 0) {
-                if constexpr (kk < 2) sdp[r] = lds_async_b128<BUF * AUX_SLOT + 128 + 64 * r>(ab);
-                ad[kk] = lds_async_b128<DOS + BUF * TILE_B + r * HALF_B>(rb[ks]);
-            }
-            if constexpr (r == 0 && !L::kVRegs) bv[ks][part] = lds_async_b128<part * HALF_B>(vr[ks]);
+            constexpr int kk = s - 2 * NS;
+            if constexpr (kk == 0) static_for<0, 4>([&](auto G4) { sdp[G4] = lds_async_b128<BUF * AUX_SLOT + 128 + 32 * decltype(G4)::value>(ab); });
+            ad[kk] = lds_async_b128<DOS + BUF * TILE_B>(rb[kk]);
+            bv0[kk] = lds_async_b128<0>(vr[kk]);
+            bv1[kk] = lds_async_b128<32 * D * 2>(vr[kk]);
         } else {
-            constexpr int t = s - 3 * NS;
-            if constexpr (part == 0) bd0[t] = lds_async_tr16<DOS + BUF * TILE_B>(tb[t]);
-            if constexpr (part == 1) bd1[t] = lds_async_tr16<DOS + BUF * TILE_B + HALF_B>(tb[t]);
+            constexpr int t = s - 3 * NS, c = t / NDB, db = t % NDB;
+            bd0[t] = lds_async_tr16<DOS + BUF * TILE_B + c * HALF_B>(tb[0][db]);
+            bd1[t] = lds_async_tr16<DOS + BUF * TILE_B + c * HALF_B>(tb[1][db]);
         }
     };
 
@@ -362,51 +356,41 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
         constexpr int BUF = decltype(BUFC)::value, DBUF = (BUF + 2) % NBUF;
         constexpr bool FIRST = decltype(FIRSTC)::value, LAST = decltype(LASTC)::value;
         using NextBuf = std::integral_constant<int, (BUF + 1) % NBUF>;
-        // Where the vector-ALU work goes: behind the MFMAs of the dK, dP and dV phases, numbered 0 .. 3*G-1, evenly.  The
-        // exponentials begin behind the second MFMA of the dK phase (two have then issued since the last write of S') and
-        // end a slot before the dV phase; P is packed one place behind them (an operand is at least two instructions old
-        // when an MFMA reads it).  Eight other spreads (fewer in the dP phase with its many reads, none behind the MFMAs
-        // that a read follows) were the same or up to 1.5 % slower.
-        constexpr int G = NS * KB, N_EXP = 8 * KB, N_PAIR = 4 * KB, kExpL = 2 * G - KB - 1;
-        auto exps_done = [](int x) constexpr { return x < 1 ? 0 : x >= kExpL ? N_EXP : x * N_EXP / kExpL; };
-        auto packs_done = [=](int x) constexpr { return exps_done(x - 1) / 2; };
-        auto pairs_done = [](int x) constexpr { return x < 2 * G ? 0 : (x - 2 * G + 1) * N_PAIR / G; };
-        // The step's elements in the order in which the S phase finishes them: element i = row block i / (4*KB), then
-        // key block, then register.  P stays in the S' registers; arguments are computed one place ahead, so that no
-        // exponential waits for its own product.
-        float arg[N_EXP];
-        auto exp_args = [&](auto XC) __attribute__((always_inline)) {
-            constexpr int x = decltype(XC)::value;
-            static_for<exps_done(x - 1), exps_done(x)>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                arg[i] = sacc[i / (4 * KB)][i / 4 % KB][i % 4] * p.scale_log2;
+        constexpr int EPM = 32 / (4 * NS);  // exponentials per MFMA in the dK and dP phases (32 MFMAs, 32 elements)
+        constexpr int PPM = 16 / (2 * NS);  // dS pairs per MFMA in the dV phase
+
+        // Vector-ALU work of MFMA position m (0 .. 4*NS-1) of the dK and dP phases: the exponentials of
+        // accumulator elements m*EPM .. (element i = key block i/16, register i%16; P stays in the S'
+        // registers), and the bf16 packing of the pairs completed by the previous position (so that no
+        // pack directly follows the exponential it reads).
+        auto pack_pair = [&](auto JC) __attribute__((always_inline)) {
+            constexpr int j = decltype(JC)::value, kbk = j / 8, r = 2 * (j % 8);
+            pp[kbk][r / 8][(r % 8) / 2] = pack_bf16(sacc[kbk][r], sacc[kbk][r + 1]);
+        };
+        auto exp_chunk = [&](auto MC) __attribute__((always_inline)) {
+            constexpr int m = decltype(MC)::value;
+            float t[EPM];
+            static_for<0, EPM>([&](auto E) {
+                constexpr int i = m * EPM + decltype(E)::value;
+                t[decltype(E)::value] = sacc[i / 16][i % 16] * p.scale_log2;
+            });
+            if constexpr (m > 0) static_for<((m - 1) * EPM) / 2, (m * EPM) / 2>([&](auto J) { pack_pair(J); });
+            static_for<0, EPM>([&](auto E) {
+                constexpr int i = m * EPM + decltype(E)::value;
+                sacc[i / 16][i % 16] = __builtin_amdgcn_exp2f(t[decltype(E)::value]);
             });
         };
-        auto valu_at = [&](auto XC) __attribute__((always_inline)) {
-            constexpr int x = decltype(XC)::value;
-            if constexpr (x < 2 * G) {
-                static_for<packs_done(x - 1), packs_done(x)>([&](auto J) {
-                    constexpr int i = 2 * decltype(J)::value, r = i / (4 * KB), k = i / 4 % KB, e = i % 4;
-                    pp[k][2 * r + e / 2] = pack_bf16(sacc[r][k][e], sacc[r][k][e + 1]);
-                });
-                static_for<exps_done(x - 1), exps_done(x)>([&](auto I) {
-                    constexpr int i = decltype(I)::value;
-                    sacc[i / (4 * KB)][i / 4 % KB][i % 4] = __builtin_amdgcn_exp2f(arg[i]);
-                });
-                if constexpr (x >= 1) exp_args(Int<x + 1>{});
-            } else {
-                static_for<pairs_done(x - 1), pairs_done(x)>([&](auto J) {  // dS, for the dK of the next body
-                    constexpr int i = 2 * decltype(J)::value, r = i / (4 * KB), k = i / 4 % KB, e = i % 4;
-                    uint32_t w = pack_bf16(sacc[r][k][e] * pacc[r][k][e], sacc[r][k][e + 1] * pacc[r][k][e + 1]);
-                    asm volatile("" : "+v"(w));  // pins the arithmetic here: its only consumers are in the next body
-                    dsp[k][2 * r + e / 2] = w;
-                });
-            }
+        // dS of the pair j (0..15)
+        auto ds_pair = [&](auto JC) __attribute__((always_inline)) {
+            constexpr int j = decltype(JC)::value, kbk = j / 8, r = 2 * (j % 8);
+            uint32_t w = pack_bf16(sacc[kbk][r] * pacc[kbk][r], sacc[kbk][r + 1] * pacc[kbk][r + 1]);
+            asm volatile("" : "+v"(w));  // pins the arithmetic here: its only consumers are in the next body
+            dsp[kbk][r / 8][(r % 8) / 2] = w;
         };
 
         if constexpr (FIRST) {
             static_for<0, kMaxAhead>([&](auto XC) {
-                if constexpr (decltype(XC)::value - ahead(decltype(XC)::value) < 0) static_for<0, KB>([&](auto PART) { issue_reads(BUFC, XC, PART); });
+                if constexpr (decltype(XC)::value - ahead(decltype(XC)::value) < 0) issue_reads(BUFC, XC);
             });
         }
         static_for<0, P4>([&](auto SC) {
@@ -421,128 +405,145 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
                 vmem_wait<GROUP>();
                 __builtin_amdgcn_s_barrier();
             }
-            // the reads this slot issues go out behind its MFMAs
-            auto issue_slot = [&](auto PART) __attribute__((always_inline)) {
+            // the reads this slot issues go out behind its first MFMA (a read holds the wave's issue for
+            // about half an MFMA; in front of the MFMA that time would be lost)
+            auto issue_slot = [&]() __attribute__((always_inline)) {
                 static_for<1, kMaxAhead + 1>([&](auto AC) {
                     constexpr int x = s + decltype(AC)::value;
                     if constexpr (x - ahead(x) == s) {
-                        if constexpr (x < P4) issue_reads(BUFC, Int<x>{}, PART);
-                        else if constexpr (!LAST) issue_reads(NextBuf{}, Int<x - P4>{}, PART);
+                        if constexpr (x < P4) issue_reads(BUFC, std::integral_constant<int, x>{});
+                        else if constexpr (!LAST) issue_reads(NextBuf{}, std::integral_constant<int, x - P4>{});
                     }
                 });
                 __builtin_amdgcn_sched_barrier(0);
             };
-            // The slot's MFMAs, one per key block, each followed by its share of the other work: a lone wave that issues
-            // two MFMAs in a row stands still while the first one runs.
-            static_for<0, KB>([&](auto N) {
-                constexpr int n = decltype(N)::value, w = n == 0 ? W : -1;
-                if constexpr (s < NS) {
-                    // ---- S(u); the loads of step u+2 ----
-                    constexpr int r = s / NK, ks = s % NK;
-                    if constexpr (n == 0 && ks == 0) lds_wait<w>(sds[r]);
-                    if constexpr (ks == 0) mfma16_vc<n == 0 ? -1 : w>(sacc[r][n], aq[s], kreg[n][ks], __builtin_bit_cast(f32x4, sds[r]));
-                    else mfma16_v<w>(sacc[r][n], aq[s], kreg[n][ks]);
+            if constexpr (s < NS) {
+                // ---- S(u); the loads of step u+2 ----
+                if constexpr (s == 0) {
+                    lds_wait4<W>(sds[0], sds[1], sds[2], sds[3]);
+                    f32x16 seed;
+                    seeds_to_acc(seed, sds);
+                    mfma_vc(sacc[0], aq[s], kreg[0][s], seed);
                     __builtin_amdgcn_sched_barrier(0);
-                    issue_slot(N);
-                    if constexpr (n == 1 && s < GROUP) issue_load(SC, DBUF);
-                } else if constexpr (s < 2 * NS) {
-                    // ---- dK(u-1), exponentials ----
-                    // (key blocks forth in even slots, back in odd ones: each MFMA keeps an operand of the one before it)
-                    constexpr int t = s - NS, k = even ? n : KB - 1 - n;
-                    const u32x4 bqt = {bq0[t][0], bq0[t][1], bq1[t][0], bq1[t][1]};
-                    mfma16_a<w>(dkacc[k][t], dsp[k], bqt);
+                    issue_slot();
+                    issue_load(std::integral_constant<int, 0>{}, DBUF);
                     __builtin_amdgcn_sched_barrier(0);
-                    issue_slot(N);
-                    if constexpr (s == NS && n == 1) {  // two MFMAs have issued since the last write of S'
-                        // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  Register r of row
-                        // block b is row q0 + 4*g + 16*b + r, so "hidden" is one compare of a compile-time number
-                        // with a per-lane limit and one select.  A step none of whose rows sees any of
-                        // the wave's keys (above the wave's diagonal while the rest of the workgroup is still on
-                        // theirs, and padding) is overwritten outright: a wave is in that state for up to six of the
-                        // eight steps of a tile's diagonal, and the whole workgroup waits for it at each barrier.
-                        // With packed documents, a key whose document ends before the row tile is seen by none of
-                        // its rows: all its S' take one select on a per-lane flag (a select, not arithmetic: S'
-                        // of such a pair may be anything, a NaN included); upper limits are compared element by
-                        // element only on the row tile in which some key's document (dense: the sequence) ends.
-                        if (SP_RARE(VARLEN, cur_it <= it_mask_lo || step_no >= total)) {
-                            const int q0 = cur_it * BMQ;
-                            if (step_no >= total || q0 + BMQ - 1 + p.off < wkey0) {
-                                asm volatile("" ::: "memory");  // keeps this a branch
-#pragma unroll
-                                for (int k = 0; k < KB; ++k)
-#pragma unroll
-                                    for (int i = 0; i < 8; ++i) sacc[i / 4][k][i % 4] = -__builtin_inff();
-                            } else {
-                                asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
-#pragma unroll
-                                for (int k = 0; k < KB; ++k) {
-                                    const int key = wkey0 + 16 * k + (int)(__lane_id() & 15);
-                                    const int lim = key - p.off - q0 - 4 * (int)(__lane_id() >> 4);  // first row that sees the key
-#pragma unroll
-                                    for (int i = 0; i < 8; ++i) sacc[i / 4][k][i % 4] = 16 * (i / 4) + i % 4 >= lim ? sacc[i / 4][k][i % 4] : -__builtin_inff();
-                                }
-                            }
-                        }
-                        if (SP_RARE(VARLEN, cur_it >= it_mask_hi)) {  // rows at or past the end of the first key's document or of the sequence
-                            const int q0 = cur_it * BMQ;
-                            bool inside = !VARLEN;
-                            if (VARLEN && (cur_it <= end_it || cur_it > dead_it)) {
-                                dead_it = cur_it;
-                                bool ends = false;
-#pragma unroll
-                                for (int k = 0; k < KB; ++k) ends = ends || (khi_l[k] > q0 && khi_l[k] < q0 + BMQ);
-                                inside = __builtin_amdgcn_ballot_w64(ends) != 0;
-                                // keys ascend, and so do their documents' ends: the next one, going down, is that of the last hidden key
-                                end_it = inside ? cur_it : -1;
-#pragma unroll
-                                for (int k = 0; k < KB; ++k) {
-                                    dead[k] = inside ? 0 : __builtin_amdgcn_ballot_w64(khi_l[k] <= q0);
-                                    if (dead[k] != 0) end_it = (__builtin_amdgcn_readlane(khi_l[k], 63 - __builtin_clzll(dead[k])) - 1) / BMQ;
-                                }
-                            }
-                            if (inside) {
-                                asm volatile("" ::: "memory");  // keeps this a branch
-#pragma unroll
-                                for (int k = 0; k < KB; ++k) {
-                                    const int lim = (VARLEN ? khi_l[k] : S) - q0 - 4 * (int)(__lane_id() >> 4);
-#pragma unroll
-                                    for (int i = 0; i < 8; ++i) sacc[i / 4][k][i % 4] = 16 * (i / 4) + i % 4 < lim ? sacc[i / 4][k][i % 4] : -__builtin_inff();
-                                }
-                            } else {
-                                uint64_t any = 0;
-#pragma unroll
-                                for (int k = 0; k < KB; ++k) any |= dead[k];
-                                if (any != 0) {
-                                    asm volatile("" ::: "memory");  // keeps this a branch
-#pragma unroll
-                                    for (int k = 0; k < KB; ++k) hide_lanes(sacc[0][k], sacc[1][k], dead[k]);
-                                }
-                            }
-                        }
-                        exp_args(Int<1>{});
-                    }
-                    valu_at(Int<t * KB + n>{});
-                } else if constexpr (s < 3 * NS) {
-                    // ---- dP(u), exponentials ----
-                    constexpr int kk = s - 2 * NS, ks = kk / 2, r = kk % 2;
-                    const u32x4 bvk = [&]() { if constexpr (L::kVRegs) return as_u32x4(vreg[n][ks]); else return bv[ks][n]; }();
-                    if constexpr (n == 0 && kk == 0) lds_wait<w>(sdp[0]);
-                    if constexpr (ks == 0) mfma16_vc<(kk == 0 ? -1 : w)>(pacc[r][n], ad[kk], bvk, __builtin_bit_cast(f32x4, sdp[r]));
-                    else mfma16_v<w>(pacc[r][n], ad[kk], bvk);
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue_slot(N);
-                    valu_at(Int<G + kk * KB + n>{});
+                    mfma_vc(sacc[1], aq[s], kreg[1][s], seed);
                 } else {
-                    // ---- dV(u), dS products ----
-                    constexpr int t = s - 3 * NS, k = even ? n : KB - 1 - n;
-                    const u32x4 bdo = {bd0[t][0], bd0[t][1], bd1[t][0], bd1[t][1]};
-                    mfma16_a<w>(dvacc[k][t], pp[k], bdo);
+                    mfma_v<W>(sacc[0], aq[s], kreg[0][s]);
                     __builtin_amdgcn_sched_barrier(0);
-                    issue_slot(N);
-                    valu_at(Int<2 * G + t * KB + n>{});
+                    issue_slot();
+                    if constexpr (s < GROUP) issue_load(std::integral_constant<int, s>{}, DBUF);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_v<-1>(sacc[1], aq[s], kreg[1][s]);
+                }
+            } else if constexpr (s < 2 * NS) {
+                // ---- dK(u-1), exponentials of key block 0 ----
+                // Exponential chunk m runs behind MFMA m+1 of the dK and dP phases taken together (the last
+                // one behind the first MFMA of the dV phase): two MFMAs have then issued since the last write
+                // of S', which covers the wait states between an MFMA and a vector-ALU read of its result.
+                constexpr int t = s - NS, c = t / NDB, db = t % NDB;
+                const u32x4 bqt = {bq0[t][0], bq0[t][1], bq1[t][0], bq1[t][1]};
+                mfma_a_w<W>(dkacc[0][db], dsp[0][c], bqt);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_slot();
+                if constexpr (t > 0) exp_chunk(std::integral_constant<int, 2 * t - 1>{});
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_a(dkacc[1][db], dsp[1][c], bqt);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (t == 0) {
+                    // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  The element of register r
+                    // is row q0 + 4*hi + c_r with c_r = 8*(r/4) + r%4 known at compile time, so "hidden" is one
+                    // compare of c_r with a per-lane limit and one select.  A step none of whose rows sees any of
+                    // the wave's keys (above the wave's diagonal while the rest of the workgroup is still on
+                    // theirs, and padding) is overwritten outright: a wave is in that state for up to six of the
+                    // eight steps of a tile's diagonal, and the whole workgroup waits for it at each barrier.
+                    // With packed documents, a key whose document ends before the row tile is seen by none of
+                    // its rows: all 16 of its S' take one select on a per-lane flag (a select, not arithmetic: S'
+                    // of such a pair may be anything, a NaN included); upper limits are compared element by
+                    // element only on the row tile in which some key's document (dense: the sequence) ends.
+                    if (cur_it <= it_mask_lo || step_no >= total) {
+                        const int q0 = cur_it * BMQ;
+                        if (step_no >= total || q0 + BMQ - 1 + p.off < wkey0) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) { sacc[0][r] = -__builtin_inff(); sacc[1][r] = -__builtin_inff(); }
+                        } else {
+                            asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
+#pragma unroll
+                            for (int kbk = 0; kbk < 2; ++kbk) {
+                                const int key = wkey0 + 32 * kbk + (int)(__lane_id() & 31);
+                                const int lim = key - p.off - q0 - 4 * (int)(__lane_id() >> 5);  // first row that sees the key
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) sacc[kbk][r] = 8 * (r / 4) + r % 4 >= lim ? sacc[kbk][r] : -__builtin_inff();
+                            }
+                        }
+                    }
+                    if (cur_it >= it_mask_hi) {  // rows at or past the end of the first key's document or of the sequence
+                        const int q0 = cur_it * BMQ;
+                        const bool inside = !VARLEN || __builtin_amdgcn_ballot_w64((khi_l[0] > q0 && khi_l[0] < q0 + BMQ) ||
+                                                                                   (khi_l[1] > q0 && khi_l[1] < q0 + BMQ)) != 0;
+                        if (inside) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                            for (int kbk = 0; kbk < 2; ++kbk) {
+                                const int lim = (VARLEN ? khi_l[kbk] : S) - q0 - 4 * (int)(__lane_id() >> 5);
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) sacc[kbk][r] = 8 * (r / 4) + r % 4 < lim ? sacc[kbk][r] : -__builtin_inff();
+                            }
+                        } else {
+                            const uint64_t dead0 = __builtin_amdgcn_ballot_w64(khi_l[0] <= q0), dead1 = __builtin_amdgcn_ballot_w64(khi_l[1] <= q0);
+                            if ((dead0 | dead1) != 0) {
+                                asm volatile("" ::: "memory");  // keeps this a branch
+                                hide_lanes(sacc[0], dead0);
+                                hide_lanes(sacc[1], dead1);
+                            }
+                        }
+                    }
+                }
+                exp_chunk(std::integral_constant<int, 2 * t>{});
+            } else if constexpr (s < 3 * NS) {
+                // ---- dP(u), exponentials of key block 1 ----
+                constexpr int kk = s - 2 * NS;
+                if constexpr (kk == 0) {
+                    lds_wait4<W>(sdp[0], sdp[1], sdp[2], sdp[3]);
+                    f32x16 seed;
+                    seeds_to_acc(seed, sdp);
+                    mfma_vc(pacc[0], ad[kk], bv0[kk], seed);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue_slot();
+                    exp_chunk(std::integral_constant<int, 2 * (NS + kk) - 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_vc(pacc[1], ad[kk], bv1[kk], seed);
+                } else {
+                    mfma_v<W>(pacc[0], ad[kk], bv0[kk]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue_slot();
+                    exp_chunk(std::integral_constant<int, 2 * (NS + kk) - 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_v<-1>(pacc[1], ad[kk], bv1[kk]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-            });
+                exp_chunk(std::integral_constant<int, 2 * (NS + kk)>{});
+            } else {
+                // ---- dV(u), dS products (pair chunk m behind MFMA m+1 of the phase, as above) ----
+                constexpr int t = s - 3 * NS, c = t / NDB, db = t % NDB;
+                const u32x4 bdo = {bd0[t][0], bd0[t][1], bd1[t][0], bd1[t][1]};
+                mfma_a_w<W>(dvacc[0][db], pp[0][c], bdo);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_slot();
+                if constexpr (t == 0) {
+                    exp_chunk(std::integral_constant<int, 4 * NS - 1>{});
+                    static_for<((4 * NS - 1) * EPM) / 2, 16>([&](auto J) { pack_pair(J); });  // the last pair(s) of P
+                } else {
+                    static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (2 * t - 1) * PPM + decltype(J)::value>{}); });
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_a(dvacc[1][db], pp[1][c], bdo);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (2 * t) * PPM + decltype(J)::value>{}); });
+                if constexpr (t == NS - 1) static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (2 * t + 1) * PPM + decltype(J)::value>{}); });
+            }
         });
         __builtin_amdgcn_sched_barrier(0);
         ++step_no;
@@ -561,14 +562,15 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
 
     // ---- the deferred dK of the last step ----
     {
+        constexpr uint32_t qoff = QS + (NBUF - 1) * TILE_B;
         static_for<0, NS>([&](auto TC) {
-            constexpr int t = decltype(TC)::value;
-            u32x2 h0 = lds_async_tr16<QS + (NBUF - 1) * TILE_B>(tb[t]);
-            u32x2 h1 = lds_async_tr16<QS + (NBUF - 1) * TILE_B + HALF_B>(tb[t]);
+            constexpr int t = decltype(TC)::value, c = t / NDB, db = t % NDB;
+            u32x2 h0 = lds_async_tr16<c * HALF_B>(tb[0][db] + qoff);
+            u32x2 h1 = lds_async_tr16<c * HALF_B>(tb[1][db] + qoff);
             lds_wait<0>(h0, h1);
             const u32x4 bqt = {h0[0], h0[1], h1[0], h1[1]};
-#pragma unroll
-            for (int k = 0; k < KB; ++k) dkacc[k][t] = mfma16(as_bf16x8(dsp[k]), as_bf16x8(bqt), dkacc[k][t]);
+            dkacc[0][db] = mfma32(as_bf16x8(dsp[0][c]), as_bf16x8(bqt), dkacc[0][db]);
+            dkacc[1][db] = mfma32(as_bf16x8(dsp[1][c]), as_bf16x8(bqt), dkacc[1][db]);
         });
     }
     wait_vmem();  // no direct-to-LDS load may outlive the workgroup's LDS allocation
@@ -583,39 +585,41 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
         float* pk = p.part + part_offset((int64_t)b * p.Hkv + g, p.chunks.nsplit, Skv, first_chunk, split, keys, D);
         float* pv = pk + (size_t)p.B * p.Hkv * p.chunks.nsplit * Skv * D;
 #pragma unroll
-        for (int k = 0; k < KB; ++k) {
-            const int k0 = wkey0 - j0 + 16 * k + g4;  // first of the lane's four keys, in the tile
-            if (k0 + 4 <= keys) {
+        for (int kbk = 0; kbk < 2; ++kbk)
 #pragma unroll
-                for (int db = 0; db < NS; ++db) {
-                    const size_t at = (size_t)k0 * D + 4 * (16 * db + lo);
-                    *reinterpret_cast<f32x4*>(pk + at) = dkacc[k][db];
-                    *reinterpret_cast<f32x4*>(pv + at) = dvacc[k][db];
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const int k0 = wkey0 - j0 + 32 * kbk + 8 * g4 + 4 * hi;  // first of the lane's four keys, in the tile
+                if (k0 + 4 <= keys) {
+#pragma unroll
+                    for (int db = 0; db < NDB; ++db) {
+                        const size_t at = (size_t)k0 * D + 4 * (32 * db + lo);
+                        *reinterpret_cast<f32x4*>(pk + at) = f32x4{dkacc[kbk][db][4 * g4], dkacc[kbk][db][4 * g4 + 1], dkacc[kbk][db][4 * g4 + 2], dkacc[kbk][db][4 * g4 + 3]};
+                        *reinterpret_cast<f32x4*>(pv + at) = f32x4{dvacc[kbk][db][4 * g4], dvacc[kbk][db][4 * g4 + 1], dvacc[kbk][db][4 * g4 + 2], dvacc[kbk][db][4 * g4 + 3]};
+                    }
+                } else if (k0 < keys) {  // the last one to three keys
+#pragma unroll
+                    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                        for (int e = 0; e < 3; ++e)
+                            if (k0 + e < keys) {
+                                const size_t at = (size_t)k0 * D + (size_t)(keys - k0) * (32 * db + lo) + e;
+                                pk[at] = dkacc[kbk][db][4 * g4 + e];
+                                pv[at] = dvacc[kbk][db][4 * g4 + e];
+                            }
                 }
-            } else if (k0 < keys) {  // the last one to three keys
-#pragma unroll
-                for (int db = 0; db < NS; ++db)
-#pragma unroll
-                    for (int e = 0; e < 3; ++e)
-                        if (k0 + e < keys) {
-                            const size_t at = (size_t)k0 * D + (size_t)(keys - k0) * (16 * db + lo) + e;
-                            pk[at] = dkacc[k][db][e];
-                            pv[at] = dvacc[k][db][e];
-                        }
             }
-        }
     } else {
 #pragma unroll
-        for (int k = 0; k < KB; ++k)
+        for (int kbk = 0; kbk < 2; ++kbk)
 #pragma unroll
-            for (int db = 0; db < NS; ++db)
+            for (int db = 0; db < NDB; ++db)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int krow = wkey0 + 16 * k + g4 + e;
+                for (int r = 0; r < 16; ++r) {
+                    const int krow = wkey0 + 32 * kbk + 8 * (r / 4) + 4 * hi + (r % 4);
                     if (krow < Skv) {
-                        const size_t off = ((size_t)b * Skv * p.Hkv + g) * D + p.kvmap.off(krow) + 16 * db + lo;
-                        p.dk[off] = (__bf16)(dkacc[k][db][e] * p.scale);
-                        p.dv[off] = (__bf16)dvacc[k][db][e];
+                        const size_t off = ((size_t)b * Skv * p.Hkv + g) * D + p.kvmap.off(krow) + 32 * db + lo;
+                        p.dk[off] = (__bf16)(dkacc[kbk][db][r] * p.scale);
+                        p.dv[off] = (__bf16)dvacc[kbk][db][r];
                     }
                 }
     }

@@ -10,14 +10,14 @@
 // Section 4.1); the plain causal call is Skv = S, off = 0.
 //
 // One workgroup = 4 waves = 256 query rows of one query head, one wave per SIMD;
-// a wave owns 64 rows (NQ = two times 32; 32 in launches of few tiles, see
-// dq_row_blocks()), in blocks of 16: their Q and dO stay resident as MFMA
+// a wave owns 64 rows (NQ = two 32-row blocks; one in launches of few tiles, see
+// dq_row_blocks()): their Q and dO stay resident as MFMA
 // B operands (in accumulation registers), their dQ lives in accumulation
 // registers that only MFMAs touch, and -LSE/scale and -Delta of the lane's row
 // sit in register tiles that seed the S and dP accumulators through the MFMA C
 // operand.  K/V stream through rings of eight 32-key LDS tiles (direct
 // global->LDS loads issued six steps ahead, XOR-swizzled); every operand
-// fetched from LDS feeds 2*NQ MFMAs, one per row block.  Per 32-key step u:
+// fetched from LDS feeds NQ MFMAs, one per row block.  Per 32-key step u:
 //   S'^T = K.Q^T - LSE/scale, dP'^T = V.dO^T - Delta   (keys on the register axis,
 //        one query per lane)
 //   P = exp2(S' * scale*log2e), dS = P * dP'            (fp32 vector ALU, then bf16)
@@ -25,20 +25,14 @@
 //        the dS^T accumulator tile is already a valid B operand)
 //
 // A lone wave issues in order, so the vector-ALU work is interleaved by hand
-// into the MFMA stream, a little behind every MFMA.  One loop body runs three phases
-// of D/16 operand slots (an MFMA per row block in each):
-//   S(u) + the loads of step u+6 | dP(u) + exponentials | dQ(u-1) + the rest of them, dS products
+// into the MFMA stream.  One loop body runs three phases of D/16 operand slots
+// (an MFMA per row block in each):
+//   S(u) + the loads of step u+6 | dP(u) + exponentials | dQ(u-1) + dS products
 // i.e. the dQ contraction of a step is deferred into the next body.  The body is
-// straight-line code: LDS operand reads are asynchronous, issued sixteen MFMAs
+// straight-line code: LDS operand reads are asynchronous, issued eight MFMAs
 // ahead (across bodies) with one exact partial wait per pair of slots, and the
 // body is instantiated once per ring position so that LDS addresses are
 // immediates.
-//
-// What bounds it: power, then issue.  With 32x32x16 MFMAs a step took 1816 cycles at 1.73 GHz, with
-// 16x16x32 1950 at 1.99 (pipe time 1536): 32768 rows, 4 heads, D = 128, 1162 -> 1076 us, 16 x 4096 rows
-// 327 -> 311; D = 64 671 -> 647 and 193 -> 191.  Two MFMAs back to back with the other work
-// behind each pair, instead of some behind every one, took 2268 cycles; branches laid out so
-// that the usual path takes no jump gave 1 %, the load cursor's update outside the S phase cost 3 %.
 //
 // This file holds the workgroup's program; attn_bwd_matrix.h has the kernel that
 // runs it, beside the one of attn_bwd_dkdv.h.
@@ -78,14 +72,13 @@ struct Lds {
 template <int D, bool VARLEN, int NQ>
 __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) {
     constexpr int RPW = kRowsPerWave<NQ>, BM = kRows<NQ>;
-    constexpr int NS = D / 16;   // operand slots per phase: (16-key block, contraction step), resp. 16-wide blocks of the head dim
-    constexpr int NK = D / 32;   // contraction steps over the head dim
-    constexpr int RB = 2 * NQ;   // 16-row blocks of a wave
+    constexpr int NS = D / 16;   // operand slots per phase (contraction steps over the head dim)
+    constexpr int NDB = D / 32;  // 32-wide blocks of the head dim
     constexpr int TILE_B = Lds<D>::TILE_B, KS = Lds<D>::KS, VS = Lds<D>::VS;
     constexpr int HALF_B = 16 * D * 2;  // 16 rows of a tile
     static_assert(KS + (NBUF - 1) * TILE_B + HALF_B < 65536, "immediate LDS offsets must fit 16 bits");
 
-    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, g4 = 4 * (lane >> 4);
+    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // heads vary fastest (they share K/V tiles), then batch entries; query tiles from the last (longest) to the first
     const uint32_t n_heads = (uint32_t)p.Hq * (uint32_t)p.B;
@@ -108,52 +101,58 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     const int i0 = qt * BM;
     const int wrow0 = i0 + RPW * wave;  // first row of this wave
 
-    // resident B operands (Q^T, dO^T columns of this lane's rows) and accumulator seeds
-    bf16x8 qreg[RB][NK], doreg[RB][NK];
-    f32x4 seed_s[RB], seed_p[RB];
+    // resident B operands (Q^T, dO^T columns of this lane's two rows) and accumulator seeds
+    bf16x8 qreg[NQ][NS], doreg[NQ][NS];
+    f32x16 seed_s[NQ], seed_p[NQ];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const int row = wrow0 + 16 * rb + lo;
+    for (int qb = 0; qb < NQ; ++qb) {
+        const int row = wrow0 + 32 * qb + lo;
         const int rc = row < S ? row : S - 1;
 #pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
-            qreg[rb][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(qb_ + p.qmap.off(rc) + 32 * ks + 2 * g4));
-            doreg[rb][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(dob + p.qmap.off(rc) + 32 * ks + 2 * g4));
+        for (int kk = 0; kk < NS; ++kk) {
+            qreg[qb][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(qb_ + p.qmap.off(rc) + 16 * kk + 8 * hi));
+            doreg[qb][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(dob + p.qmap.off(rc) + 16 * kk + 8 * hi));
         }
         const float ls = -p.lse[((size_t)b * p.Hq + h) * S + rc] / p.scale;
         const float dl = -p.delta[((size_t)b * p.Hq + h) * S + rc];
-        seed_s[rb] = f32x4{ls, ls, ls, ls};
-        seed_p[rb] = f32x4{dl, dl, dl, dl};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { seed_s[qb][r] = ls; seed_p[qb][r] = dl; }
     }
     int wave_lo_max = 0, wg_lo_min = 0;
-    int rlo_l[RB] = {};  // packed documents: the first key this lane's rows may see (their document's start)
+    int rlo_l[2] = {0, 0};  // packed documents: the first key this lane's rows may see (their document's start)
     if (VARLEN) {
         wave_lo_max = __builtin_amdgcn_readfirstlane(p.row_lo[(wrow0 + RPW - 1 < S ? wrow0 + RPW - 1 : S - 1)]);
         wg_lo_min = __builtin_amdgcn_readfirstlane(p.row_lo[i0]);
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int row = wrow0 + 16 * rb + lo;
-            rlo_l[rb] = p.row_lo[row < S ? row : S - 1];
+        for (int qb = 0; qb < NQ; ++qb) {
+            const int row = wrow0 + 32 * qb + lo;
+            rlo_l[qb] = p.row_lo[row < S ? row : S - 1];
         }
+        if constexpr (NQ == 1) rlo_l[1] = rlo_l[0];
     }
 
-    f32x4 dqacc[RB][NS];
+    f32x16 dqacc[NQ][NDB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-        for (int db = 0; db < NS; ++db) dqacc[rb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dqacc[qb][db][r] = 0.f;
 
     // LDS addresses of this lane's operand reads; everything that changes per step is an immediate
     const uint32_t sm = lds_addr(smem);
-    uint32_t rk[NK], rv[NK];  // row-major operand (K, V rows): row lo (+16 per 16-key block), chunk 4*ks + g
+    uint32_t rk[NS], rv[NS];  // row-major operand (K, V rows): row lo, chunk 2*kk + hi
 #pragma unroll
-    for (int ks = 0; ks < NK; ++ks) {
-        rk[ks] = sm + tile16_off_b128<D>(lo, 4 * ks + (lane >> 4));
-        rv[ks] = rk[ks] + VS;
+    for (int kk = 0; kk < NS; ++kk) {
+        rk[kk] = sm + tile_off_b128<D>(lo, 2 * kk + hi);
+        rv[kk] = rk[kk] + VS;
     }
-    uint32_t tb[NS];  // K^T operand: rows 4*g + (0..3) (+16), column 16*db + lo
+    uint32_t tb[2][NDB];  // K^T operand: rows 8*half + 4*hi + (0..3) (+16 per 16-key half), cols 32*db + ...
 #pragma unroll
-    for (int db = 0; db < NS; ++db) tb[db] = sm + tile16_off_tr<D>(16 * db, lane);
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+            tb[half][db] = sm + tile_off_tr<D>(8 * half + 4 * hi, 32 * db + 16 * (lo >> 4), lo & 15);
 
     // the last key a row may see: i + off, at most the last key there is
     auto last_key = [&](int row) __attribute__((always_inline)) { return row + p.off < Skv - 1 ? row + p.off : Skv - 1; };
@@ -172,7 +171,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     // `lim` (tile-relative) re-read row `lim` (they are never used unmasked)
     auto lane_off = [&](int K, int lim) __attribute__((always_inline)) {
         const int row = Dma::RPI * (wave + kWaves * K) + lane / Dma::CH;
-        const uint32_t chunk_b = (uint32_t)(((lane % Dma::CH) ^ swz16<D>(row)) * 16);
+        const uint32_t chunk_b = (uint32_t)(((lane % Dma::CH) ^ swz<D>(row)) * 16);
         return (uint32_t)(row < lim ? row : lim) * stride_b + chunk_b;
     };
     uint32_t voff[PW];  // offsets of the tile the load cursor is on
@@ -191,7 +190,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     // The tail tile is the last one the cursor can reach, and the cursor stays on it: its clamped lane offsets
     // replace the regular ones for good.
     auto enter_tile = [&]() __attribute__((always_inline)) {
-        if (SP_RARE(VARLEN, dc.jt == jt_tail)) {  // rare
+        if (dc.jt == jt_tail) {  // rare
 #pragma unroll
             for (int K = 0; K < PW; ++K) voff[K] = lane_off(K, Skv - 1 - dc.jt * BN);
         }
@@ -205,10 +204,10 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         enter_tile();
     }
     auto advance_load = [&]() __attribute__((always_inline)) {
-        if (SP_LIKELY(dc.left > 0)) {  // past the last step the cursor stays (the padding steps re-read the last tile)
+        if (dc.left > 0) {  // past the last step the cursor stays (the padding steps re-read the last tile)
             --dc.left; dc.jt += 1;
             dc.k += tile_step_b; dc.v += tile_step_b;
-            if (SP_RARE(VARLEN, (dc.jt & tiles_per_chunk_mask) == 0)) {  // rare: the first tile of the next peer's chunk
+            if ((dc.jt & tiles_per_chunk_mask) == 0) {  // rare: the first tile of the next peer's chunk
                 const size_t off = p.kvmap.off(dc.jt * BN) * 2;
                 dc.k = k_head + off; dc.v = v_head + off;
             }
@@ -231,12 +230,6 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     const int mask_from = (last_key(wrow0) / BN - jt_begin) < total ? (last_key(wrow0) / BN - jt_begin) : total;
     const int dead_from = (last_key(wrow0 + RPW - 1) / BN + 1 - jt_begin) < total ? (last_key(wrow0 + RPW - 1) / BN + 1 - jt_begin) : total;
     const int mask_until = VARLEN ? (wave_lo_max + BN - 1) / BN - jt_begin : 0;
-    // ... there, the rows (their lanes) that see nothing of any step before start_step, in which the next row's document
-    // starts.  Kept from step to step: four blocks' compares in each of them cost a wave with a boundary among its rows
-    // more than the selects, and its workgroup waits for it (20000 rows in documents of 1024, 4 heads, D = 64, backward
-    // 198 us, 176 now, 160 with the 32x32x16 form of this stage).
-    uint64_t dead[RB] = {};
-    int start_step = 0;
     {
         static_for<0, PW>([&](auto K) { issue_load(K, NBUF - 1); });  // K rows of step 0 again, as the stand-in
         static_for<0, LEAD>([&](auto T) {
@@ -245,18 +238,20 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         });
     }
 
-    f32x4 sacc[2][RB], pacc[2][RB];  // [16-key block][row block]
-    u32x4 dsp[2][RB];  // bf16 B operands [parity of the step][row block]
+    f32x16 sacc[NQ], pacc[NQ];
+    u32x4 dsp[2][NQ][2];  // bf16 B operands [parity of the step][row block][16-key half]
 #pragma unroll
     for (int par = 0; par < 2; ++par)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) dsp[par][rb] = u32x4{0, 0, 0, 0};
+        for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) dsp[par][qb][c] = u32x4{0, 0, 0, 0};
 
     // The operand slots of a body, x = 0 .. 3*NS-1 in the phases S | dP | dQ.  Reads of slot x are issued
     // kAhead slots early (behind the first MFMA of the issuing slot), possibly from the previous body (slots
     // x >= 3*NS name slots of the next body).  Waits happen once per pair of slots, at the even one.
     constexpr int P3 = 3 * NS;
-    constexpr int kAhead = NQ == 2 ? 4 : 8;  // sixteen MFMAs
+    constexpr int kAhead = NQ == 2 ? 4 : 8;  // eight MFMAs
     auto nreads = [](int x) constexpr { return (x % P3) < 2 * NS ? 1 : 2; };
     // reads issued after those of slot s+1 by the time (even) slot s waits, which is before slot s issues
     // its own (none for the next body if `last`)
@@ -272,25 +267,17 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     u32x2 t0[NS], t1[NS];
 
     // reads of slot s (0 .. 3*NS-1) of the body at ring position BUF
-    auto issue_reads = [&](auto BUFC, auto SC, auto PART) __attribute__((always_inline)) {
+    auto issue_reads = [&](auto BUFC, auto SC) __attribute__((always_inline)) {
         constexpr int BUF = decltype(BUFC)::value, PBUF = (BUF + NBUF - 1) % NBUF, s = decltype(SC)::value;
-        if constexpr (decltype(PART)::value == 1) {  // the second transposing read
-            if constexpr (s >= 2 * NS) t1[s - 2 * NS] = lds_async_tr16<KS + PBUF * TILE_B + HALF_B>(tb[s - 2 * NS]);
-        } else if constexpr (s < NS) {
-            ak[s] = lds_async_b128<KS + BUF * TILE_B + (s / NK) * HALF_B>(rk[s % NK]);
+        if constexpr (s < NS) {
+            ak[s] = lds_async_b128<KS + BUF * TILE_B>(rk[s]);
         } else if constexpr (s < 2 * NS) {
-            av[s - NS] = lds_async_b128<BUF * TILE_B + ((s - NS) / NK) * HALF_B>(rv[s % NK]);
+            av[s - NS] = lds_async_b128<BUF * TILE_B>(rv[s - NS]);
         } else {
-            t0[s - 2 * NS] = lds_async_tr16<KS + PBUF * TILE_B>(tb[s - 2 * NS]);
+            constexpr int t = s - 2 * NS, c = t / NDB, db = t % NDB;
+            t0[t] = lds_async_tr16<KS + PBUF * TILE_B + c * HALF_B>(tb[0][db]);
+            t1[t] = lds_async_tr16<KS + PBUF * TILE_B + c * HALF_B>(tb[1][db]);
         }
-    };
-
-    // dS of pair j of a step (of its elements as numbered below), into the operands of parity PAR
-    auto ds_pair = [&](auto PARC, auto JC) __attribute__((always_inline)) {
-        constexpr int i = 2 * decltype(JC)::value, kb = i / (4 * RB), rb = i / 4 % RB, r = i % 4;
-        uint32_t w = pack_bf16(sacc[kb][rb][r] * pacc[kb][rb][r], sacc[kb][rb][r + 1] * pacc[kb][rb][r + 1]);
-        asm volatile("" : "+v"(w));  // pins the arithmetic here: its consumers are far behind
-        dsp[decltype(PARC)::value][rb][2 * kb + r / 2] = w;
     };
 
     // One body = step u at ring position BUF: (BUF-1)%8 holds step u-1 (its dQ is done here), (BUF+6)%8
@@ -301,31 +288,29 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         constexpr int BUF = decltype(BUFC)::value, DBUF = (BUF + LEAD) % NBUF, PAR = BUF % 2;
         constexpr bool FIRST = decltype(FIRSTC)::value, LAST = decltype(LASTC)::value;
         using NextBuf = std::integral_constant<int, (BUF + 1) % NBUF>;
-        // Where the vector-ALU work goes: behind the MFMAs of the dP and dQ phases, numbered 0 .. 2*G-1.
-        constexpr int G = NS * RB, N_EXP = 16 * NQ, N_PAIR = 8 * NQ;
-        constexpr int kExp0 = 1, kExpL = G + G / 2, kPair0 = G + G / 2, kPairL = G / 2;
-        auto exps_done = [](int x) constexpr { return x < kExp0 ? 0 : x - kExp0 + 1 >= kExpL ? N_EXP : (x - kExp0 + 1) * N_EXP / kExpL; };
-        auto pairs_done = [](int x) constexpr { return x < kPair0 ? 0 : x - kPair0 + 1 >= kPairL ? N_PAIR : (x - kPair0 + 1) * N_PAIR / kPairL; };
+        constexpr int EPM = 16 / NS;  // exponentials per MFMA in the dP phase (16 * NQ behind NS * NQ MFMAs)
+        constexpr int PPM = 8 / NS;   // dS pairs per MFMA in the dQ phase
 
-        // The step's elements in the order in which the S phase finishes them: element i = key block i / (4*RB), then
-        // row block, then register.  P stays in the S' registers; arguments are computed one place ahead, so that no
-        // exponential waits for its own product.
-        float arg[N_EXP];
-        auto exp_args = [&](auto XC) __attribute__((always_inline)) {
-            constexpr int x = decltype(XC)::value;
-            static_for<exps_done(x - 1), exps_done(x)>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                arg[i] = sacc[i / (4 * RB)][i / 4 % RB][i % 4] * p.scale_log2;
+        // exponentials of accumulator elements m*EPM .. of the step (element i = row block i/16, register
+        // i%16); P stays in the S' registers
+        auto exp_chunk = [&](auto MC) __attribute__((always_inline)) {
+            constexpr int m = decltype(MC)::value;
+            float t[EPM];
+            static_for<0, EPM>([&](auto E) {
+                constexpr int i = m * EPM + decltype(E)::value;
+                t[decltype(E)::value] = sacc[i / 16][i % 16] * p.scale_log2;
+            });
+            static_for<0, EPM>([&](auto E) {
+                constexpr int i = m * EPM + decltype(E)::value;
+                sacc[i / 16][i % 16] = __builtin_amdgcn_exp2f(t[decltype(E)::value]);
             });
         };
-        auto valu_at = [&](auto XC) __attribute__((always_inline)) {
-            constexpr int x = decltype(XC)::value;
-            static_for<exps_done(x - 1), exps_done(x)>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                sacc[i / (4 * RB)][i / 4 % RB][i % 4] = __builtin_amdgcn_exp2f(arg[i]);
-            });
-            if constexpr (x >= kExp0) exp_args(Int<x + 1>{});
-            static_for<pairs_done(x - 1), pairs_done(x)>([&](auto J) { ds_pair(Int<PAR>{}, J); });
+        // dS of the pair j (0..15), for the dQ of the next body
+        auto ds_pair = [&](auto JC) __attribute__((always_inline)) {
+            constexpr int j = decltype(JC)::value, qb = j / 8, r = 2 * (j % 8);
+            uint32_t w = pack_bf16(sacc[qb][r] * pacc[qb][r], sacc[qb][r + 1] * pacc[qb][r + 1]);
+            asm volatile("" : "+v"(w));  // pins the arithmetic here: its only consumers are in the next body
+            dsp[PAR][qb][r / 8][(r % 8) / 2] = w;
         };
 
         // Everybody is done with the previous body: nobody reads ring position (BUF+6)%8 = (BUF-2)%8 any
@@ -334,130 +319,132 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
         vmem_wait<(LEAD - 2) * GROUP>();
         __builtin_amdgcn_s_barrier();
 
-        if constexpr (FIRST) static_for<0, kAhead>([&](auto XC) {
-            issue_reads(BUFC, XC, Int<0>{});
-            issue_reads(BUFC, XC, Int<1>{});
-        });
+        if constexpr (FIRST) static_for<0, kAhead>([&](auto XC) { issue_reads(BUFC, XC); });
         static_for<0, P3>([&](auto SC) {
             constexpr int s = decltype(SC)::value;
             constexpr bool even = s % 2 == 0;
             constexpr int W = even ? young_reads(s, LAST) : -1;  // reads allowed to stay in flight at the pair's wait
             __builtin_amdgcn_sched_barrier(0);
-            // the reads this slot issues go out behind its first MFMA and (the second transposing one) its second
-            auto issue_slot = [&](auto PART) __attribute__((always_inline)) {
+            // the reads this slot issues go out behind its first MFMA
+            auto issue_slot = [&]() __attribute__((always_inline)) {
                 constexpr int x = s + kAhead;
-                if constexpr (x < P3) issue_reads(BUFC, Int<x>{}, PART);
-                else if constexpr (!LAST) issue_reads(NextBuf{}, Int<x - P3>{}, PART);
+                if constexpr (x < P3) issue_reads(BUFC, std::integral_constant<int, x>{});
+                else if constexpr (!LAST) issue_reads(NextBuf{}, std::integral_constant<int, x - P3>{});
                 __builtin_amdgcn_sched_barrier(0);
             };
-            // The slot's MFMAs, one per row block, each followed by its share of the other work: a lone wave that issues
-            // two MFMAs in a row stands still while the first one runs.
-            static_for<0, RB>([&](auto N) {
-                constexpr int n = decltype(N)::value, w = n == 0 ? W : -1;
-                if constexpr (s < NS) {
-                    // ---- S(u); the dS products of step u-1's second key block; the loads of step u+6 ----
-                    constexpr int kb = s / NK, ks = s % NK;
-                    if constexpr (ks == 0) mfma16_vc_ab<w>(sacc[kb][n], ak[s], qreg[n][ks], seed_s[n]);
-                    else mfma16_v_ab<w>(sacc[kb][n], ak[s], qreg[n][ks]);
+            if constexpr (s < NS) {
+                // ---- S(u); the loads of step u+6 ----
+                if constexpr (s == 0) mfma_vc_ab<W>(sacc[0], ak[s], qreg[0][s], seed_s[0]);
+                else mfma_v_ab<W>(sacc[0], ak[s], qreg[0][s]);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_slot();
+                if constexpr (s < GROUP) issue_load(SC, DBUF);
+                // the cursor moves on in the first slot without a load (scalar work between the slot's read and
+                // its second MFMA, where the compiler would otherwise put a wait state)
+                if constexpr (s == GROUP) advance_load();
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (NQ == 2) {
+                    if constexpr (s == 0) mfma_vc_ab<-1>(sacc[1], ak[s], qreg[1][s], seed_s[1]);
+                    else mfma_v_ab<-1>(sacc[1], ak[s], qreg[1][s]);
+                }
+            } else if constexpr (s < 2 * NS) {
+                // ---- dP(u), exponentials ----
+                // Exponential chunk m runs behind MFMA m+1 of the phase (the last one behind the first MFMA
+                // of the dQ phase): two MFMAs have then issued since the last write of S', which covers the
+                // wait states between an MFMA and a vector-ALU read of its result.
+                constexpr int kk = s - NS;
+                if constexpr (kk == 0) mfma_vc_ab<W>(pacc[0], av[kk], doreg[0][kk], seed_p[0]);
+                else mfma_v_ab<W>(pacc[0], av[kk], doreg[0][kk]);
+                __builtin_amdgcn_sched_barrier(0);
+                issue_slot();
+                if constexpr (NQ == 2) {
+                    if constexpr (kk > 0) exp_chunk(std::integral_constant<int, 2 * kk - 1>{});
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (n < 2) issue_slot(N);
-                    if constexpr (n == 1 && s == GROUP) advance_load();
-                    if constexpr (n == 1 && s < GROUP) issue_load(SC, DBUF);
-                } else if constexpr (s < 2 * NS) {
-                    // ---- dP(u), most of the exponentials ----
-                    constexpr int kk = s - NS, kb = kk / NK, ks = kk % NK;
-                    if constexpr (ks == 0) mfma16_vc_ab<w>(pacc[kb][n], av[kk], doreg[n][ks], seed_p[n]);
-                    else mfma16_v_ab<w>(pacc[kb][n], av[kk], doreg[n][ks]);
+                    if constexpr (kk == 0) mfma_vc_ab<-1>(pacc[1], av[kk], doreg[1][kk], seed_p[1]);
+                    else mfma_v_ab<-1>(pacc[1], av[kk], doreg[1][kk]);
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (n < 2) issue_slot(N);
-                    if constexpr (kk == 0 && n == 1) {  // two MFMAs have issued since the last write of S'
-                        // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  Register r of key block kb
-                        // is key j0 + 4*g + 16*kb + r, so "hidden" is one compare of a compile-time number with a per-lane
-                        // limit and one select.  A step none of whose keys the wave
-                        // sees (past its diagonal while the rest of the workgroup is still on theirs, and padding)
-                        // is overwritten outright: a wave is in that state for up to six of the eight steps of a
-                        // tile's diagonal, and every wave of the workgroup waits for it at each step's barrier
-                        // (diagonal block of 256 rows: 14.3 us with bounds compared index by index on all eight
-                        // steps, against 6.0 us for eight unmasked steps).
-                        // With packed documents, a row whose document starts after the step's keys sees none of
-                        // them: all its S' take one select on a per-lane flag (a select, not arithmetic: S' of
-                        // such a pair may be anything, a NaN included); lower limits are compared element by element
-                        // only on the step in which some row's document starts.
-                        if (SP_RARE(VARLEN, step_no >= mask_from)) {
-                            if (step_no >= dead_from) {
-                                asm volatile("" ::: "memory");  // keeps this a branch
+                }
+                if constexpr (kk == 2 - NQ) {  // behind the second MFMA of the phase
+                    // Causal / document mask: hidden positions get S' = -inf, i.e. P = 0.  The element of register r
+                    // is key j0 + 4*hi + c_r with c_r = 8*(r/4) + r%4 known at compile time, so "hidden" is one
+                    // compare of c_r with a per-lane limit and one select.  A step none of whose keys the wave
+                    // sees (past its diagonal while the rest of the workgroup is still on theirs, and padding)
+                    // is overwritten outright: a wave is in that state for up to six of the eight steps of a
+                    // tile's diagonal, and every wave of the workgroup waits for it at each step's barrier
+                    // (diagonal block of 256 rows: 14.3 us with bounds compared index by index on all eight
+                    // steps, against 6.0 us for eight unmasked steps).
+                    // With packed documents, a row whose document starts after the step's keys sees none of
+                    // them: all 16 of its S' take one select on a per-lane flag (a select, not arithmetic: S' of
+                    // such a pair may be anything, a NaN included); lower limits are compared element by element
+                    // only on the step in which some row's document starts.
+                    if (step_no >= mask_from) {
+                        if (step_no >= dead_from) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
 #pragma unroll
-                                for (int rb = 0; rb < RB; ++rb)
+                            for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-                                    for (int r = 0; r < 8; ++r) sacc[r / 4][rb][r % 4] = -__builtin_inff();
-                            } else {
-                                asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
+                                for (int r = 0; r < 16; ++r) sacc[qb][r] = -__builtin_inff();
+                        } else {
+                            asm volatile("" ::: "memory");  // keeps this a branch (not selects executed on every step)
 #pragma unroll
-                                for (int rb = 0; rb < RB; ++rb) {
-                                    const int row = wrow0 + 16 * rb + (int)(__lane_id() & 15);
-                                    const int rhi = row + p.off < p.Skv - 1 ? row + p.off : p.Skv - 1;  // last key it may see
-                                    const int lim = rhi - cur_jt * BN - 4 * (int)(__lane_id() >> 4);
+                            for (int qb = 0; qb < NQ; ++qb) {
+                                const int row = wrow0 + 32 * qb + (int)(__lane_id() & 31);
+                                const int rhi = row + p.off < p.Skv - 1 ? row + p.off : p.Skv - 1;  // last key it may see
+                                const int lim = rhi - cur_jt * BN - 4 * (int)(__lane_id() >> 5);
 #pragma unroll
-                                    for (int r = 0; r < 8; ++r) sacc[r / 4][rb][r % 4] = 16 * (r / 4) + r % 4 <= lim ? sacc[r / 4][rb][r % 4] : -__builtin_inff();
-                                }
-                            }
-                        }
-                        if (VARLEN && step_no < mask_until) {  // some row's document starts at or after this step's keys
-                            if (step_no >= start_step) {
-                                const int j0 = cur_jt * BN;
-                                bool starts = false;
-#pragma unroll
-                                for (int rb = 0; rb < RB; ++rb) starts = starts || (rlo_l[rb] > j0 && rlo_l[rb] < j0 + BN);
-                                if (__builtin_amdgcn_ballot_w64(starts) != 0) {
-                                    asm volatile("" ::: "memory");  // keeps this a branch
-                                    start_step = step_no + 1;
-#pragma unroll
-                                    for (int rb = 0; rb < RB; ++rb) dead[rb] = 0;
-#pragma unroll
-                                    for (int rb = 0; rb < RB; ++rb) {
-                                        const int lim = rlo_l[rb] - j0 - 4 * (int)(__lane_id() >> 4);
-#pragma unroll
-                                        for (int r = 0; r < 8; ++r) sacc[r / 4][rb][r % 4] = 16 * (r / 4) + r % 4 >= lim ? sacc[r / 4][rb][r % 4] : -__builtin_inff();
-                                    }
-                                } else {
-                                    // rows ascend, and so do their documents' starts: the next one is that of the first hidden row
-                                    start_step = total;
-#pragma unroll
-                                    for (int rb = RB - 1; rb >= 0; --rb) {
-                                        dead[rb] = __builtin_amdgcn_ballot_w64(rlo_l[rb] >= j0 + BN);
-                                        if (dead[rb] != 0) start_step = __builtin_amdgcn_readlane(rlo_l[rb], __builtin_ctzll(dead[rb])) / BN - jt_begin;
-                                    }
-                                }
-                            }
-                            uint64_t any = 0;
-#pragma unroll
-                            for (int rb = 0; rb < RB; ++rb) any |= dead[rb];
-                            if (any != 0) {
-                                asm volatile("" ::: "memory");  // keeps this a branch
-#pragma unroll
-                                for (int rb = 0; rb < RB; ++rb) hide_lanes(sacc[0][rb], sacc[1][rb], dead[rb]);
+                                for (int r = 0; r < 16; ++r) sacc[qb][r] = 8 * (r / 4) + r % 4 <= lim ? sacc[qb][r] : -__builtin_inff();
                             }
                         }
                     }
-                    if constexpr (kk * RB + n == kExp0) exp_args(Int<kExp0>{});
-                    valu_at(Int<kk * RB + n>{});
-                } else {
-                    // ---- dQ(u-1); with two row blocks the last quarter of the exponentials; the dS products of step u's
-                    // first key block ----
-                    // (row blocks forth in even slots, back in odd ones: each MFMA keeps an operand of the one before it)
-                    constexpr int t = s - 2 * NS, rb = even ? n : RB - 1 - n;
-                    const u32x4 kt = {t0[t][0], t0[t][1], t1[t][0], t1[t][1]};
-                    mfma16_a<w>(dqacc[rb][t], kt, dsp[1 - PAR][rb]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (n < 2) issue_slot(N);
-                    valu_at(Int<G + t * RB + n>{});
+                    if (VARLEN && step_no < mask_until) {  // some row's document starts at or after this step's keys
+                        const int j0 = cur_jt * BN;
+                        const bool inside = __builtin_amdgcn_ballot_w64((rlo_l[0] > j0 && rlo_l[0] < j0 + BN) ||
+                                                                        (rlo_l[1] > j0 && rlo_l[1] < j0 + BN)) != 0;
+                        if (inside) {
+                            asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                            for (int qb = 0; qb < NQ; ++qb) {
+                                const int lim = rlo_l[qb] - j0 - 4 * (int)(__lane_id() >> 5);
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) sacc[qb][r] = 8 * (r / 4) + r % 4 >= lim ? sacc[qb][r] : -__builtin_inff();
+                            }
+                        } else {
+                            uint64_t dead[NQ], any = 0;
+#pragma unroll
+                            for (int qb = 0; qb < NQ; ++qb) any |= dead[qb] = __builtin_amdgcn_ballot_w64(rlo_l[qb] >= j0 + BN);
+                            if (any != 0) {
+                                asm volatile("" ::: "memory");  // keeps this a branch
+#pragma unroll
+                                for (int qb = 0; qb < NQ; ++qb) hide_lanes(sacc[qb], dead[qb]);
+                            }
+                        }
+                    }
                 }
+                if constexpr (NQ == 2) exp_chunk(std::integral_constant<int, 2 * kk>{});
+                else if constexpr (kk > 0) exp_chunk(std::integral_constant<int, kk - 1>{});
+            } else {
+                // ---- dQ(u-1), dS products of step u (pair chunk m behind MFMA m+1, as above) ----
+                constexpr int t = s - 2 * NS, c = t / NDB, db = t % NDB;
+                const u32x4 kt = {t0[t][0], t0[t][1], t1[t][0], t1[t][1]};
+                mfma_a_w<W>(dqacc[0][db], kt, dsp[1 - PAR][0][c]);
                 __builtin_amdgcn_sched_barrier(0);
-            });
+                issue_slot();
+                constexpr int m = NQ * t;  // this slot's first MFMA of the phase
+                if constexpr (t == 0) exp_chunk(std::integral_constant<int, NQ * NS - 1>{});
+                else static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (m - 1) * PPM + decltype(J)::value>{}); });
+                if constexpr (NQ == 2) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_a(dqacc[1][db], kt, dsp[1 - PAR][1][c]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, m * PPM + decltype(J)::value>{}); });
+                }
+                if constexpr (t == NS - 1) static_for<0, PPM>([&](auto J) { ds_pair(std::integral_constant<int, (NQ * NS - 1) * PPM + decltype(J)::value>{}); });
+            }
         });
         __builtin_amdgcn_sched_barrier(0);
         ++step_no;
         if (step_no < total) cur_jt += 1;
+        if constexpr (GROUP >= NS) advance_load();
     };
 
     // Eight steps per iteration, one per ring position; the step count is rounded up to a multiple of
@@ -476,13 +463,13 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     // ---- the deferred dQ of the last step (ring position 7, dS of parity 1) ----
     {
         static_for<0, NS>([&](auto TC) {
-            constexpr int t = decltype(TC)::value;
-            u32x2 h0 = lds_async_tr16<KS + (NBUF - 1) * TILE_B>(tb[t]);
-            u32x2 h1 = lds_async_tr16<KS + (NBUF - 1) * TILE_B + HALF_B>(tb[t]);
+            constexpr int t = decltype(TC)::value, c = t / NDB, db = t % NDB;
+            u32x2 h0 = lds_async_tr16<KS + (NBUF - 1) * TILE_B + c * HALF_B>(tb[0][db]);
+            u32x2 h1 = lds_async_tr16<KS + (NBUF - 1) * TILE_B + c * HALF_B>(tb[1][db]);
             lds_wait<0>(h0, h1);
             const u32x4 kt = {h0[0], h0[1], h1[0], h1[1]};
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) dqacc[rb][t] = mfma16(as_bf16x8(kt), as_bf16x8(dsp[1][rb]), dqacc[rb][t]);
+            dqacc[0][db] = mfma32(as_bf16x8(kt), as_bf16x8(dsp[1][0][c]), dqacc[0][db]);
+            if constexpr (NQ == 2) dqacc[1][db] = mfma32(as_bf16x8(kt), as_bf16x8(dsp[1][1][c]), dqacc[1][db]);
         });
     }
     wait_vmem();  // no direct-to-LDS load may outlive the workgroup's LDS allocation, nor land in what is written next
@@ -493,7 +480,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         const int row0 = wrow0 + 32 * qb;
-        if (row0 < S) store_rows16<D>(dqacc[2 * qb], dqacc[2 * qb + 1], p.scale, smem + wave * (32 * D * 2), S - row0, [&](int row) __attribute__((always_inline)) { return out + p.qmap.off(row0 + row); });
+        if (row0 < S) store_rows<D>(dqacc[qb], p.scale, smem + wave * (32 * D * 2), S - row0, [&](int row) __attribute__((always_inline)) { return out + p.qmap.off(row0 + row); });
     }
 }
 

@@ -7,8 +7,8 @@
 // us, 4096 rows 218 -> 124, 8192 398 -> 267, 16384 890 -> 753, 32768 2.80 -> 2.77 ms, 16 x 4096 rows 857 -> 815 us.
 // Both programs keep a wave's whole register file, so sharing a kernel costs neither of them occupancy.
 #pragma once
-#include "attn_bwd_dkdv.h"
-#include "attn_bwd_dq.h"
+#include "attn_bwd_dkdv16.h"
+#include "attn_bwd_dq16.h"
 
 namespace {
 
@@ -24,10 +24,11 @@ struct MatrixParams {
     bool lead_is_q;
 };
 
-template <int D, bool VARLEN, bool SPLIT, int NQ>
+// LONG: the programs with 16x16x32 MFMAs (bwd_long_launch()).
+template <int D, bool VARLEN, bool SPLIT, int NQ, bool LONG>
 __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixParams p) {
     static_assert(dkdv::kThreads == dq::kThreads, "one block size");
-    constexpr int kLds = dkdv::Lds<D>::BYTES > dq::Lds<D>::BYTES ? dkdv::Lds<D>::BYTES : dq::Lds<D>::BYTES;
+    constexpr int kKv = LONG ? dkdv16::Lds<D>::BYTES : dkdv::Lds<D>::BYTES, kLds = kKv > dq::Lds<D>::BYTES ? kKv : dq::Lds<D>::BYTES;
     __shared__ __attribute__((aligned(1024))) char smem[kLds];
     const uint32_t i = p.base + blockIdx.x;
     bool is_q = p.lead_is_q;
@@ -44,8 +45,13 @@ __global__ __launch_bounds__(dkdv::kThreads) void attn_bwd_matrix_kernel(MatrixP
         wg = is_q ? q_before : r - q_before;
         if (is_q == p.lead_is_q) wg += p.n_lead;
     }
-    if (is_q) dq::run<D, VARLEN, NQ>(p.q, wg, smem);
-    else dkdv::run<D, VARLEN, SPLIT>(p.kv, wg, smem);
+    if constexpr (LONG) {
+        if (is_q) dq16::run<D, VARLEN, NQ>(p.q, wg, smem);
+        else dkdv16::run<D, VARLEN, SPLIT>(p.kv, wg, smem);
+    } else {
+        if (is_q) dq::run<D, VARLEN, NQ>(p.q, wg, smem);
+        else dkdv::run<D, VARLEN, SPLIT>(p.kv, wg, smem);
+    }
 }
 
 // In which order the workgroups of the two stages go out (speed only: every order gives the same bits).  Each stage
@@ -106,13 +112,13 @@ inline void dispatch_order(const AttnArgs& a, int64_t n_kv, int64_t n_q, MatrixP
     p.mix_kv = (uint32_t)(lead_q ? n_kv : n_kv - lead);
 }
 
-template <int D, bool VARLEN, int NQ>
+template <int D, bool VARLEN, int NQ, bool LONG>
 void launch_grid(const MatrixParams& p, unsigned n, hipStream_t st) {
-    if (p.kv.chunks.nsplit > 1) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, true, NQ>), dim3(n), dim3(dkdv::kThreads), 0, st, p);
-    else hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, false, NQ>), dim3(n), dim3(dkdv::kThreads), 0, st, p);
+    if (p.kv.chunks.nsplit > 1) hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, true, NQ, LONG>), dim3(n), dim3(dkdv::kThreads), 0, st, p);
+    else hipLaunchKernelGGL((attn_bwd_matrix_kernel<D, VARLEN, false, NQ, LONG>), dim3(n), dim3(dkdv::kThreads), 0, st, p);
 }
 
-template <int D, bool VARLEN>
+template <int D, bool VARLEN, bool LONG>
 sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
     MatrixParams p{};
     int nq;  // row blocks of a dQ wave
@@ -150,8 +156,8 @@ sp_status launch_matrix(const AttnArgs& a, hipStream_t st) {
     for (int64_t base = 0; base < n_kv + n_q; base += kMaxGrid) {
         const int64_t n = n_kv + n_q - base < kMaxGrid ? n_kv + n_q - base : kMaxGrid;
         p.base = (uint32_t)base;
-        if (nq == 1) launch_grid<D, VARLEN, 1>(p, (unsigned)n, st);
-        else launch_grid<D, VARLEN, 2>(p, (unsigned)n, st);
+        if (nq == 1) launch_grid<D, VARLEN, 1, LONG>(p, (unsigned)n, st);
+        else launch_grid<D, VARLEN, 2, LONG>(p, (unsigned)n, st);
         if (launch_status() != SP_OK) return SP_ERR_LAUNCH;
     }
     return SP_OK;

@@ -221,8 +221,9 @@ __device__ __forceinline__ void lds_wait(u32x2& x, u32x2& y) {
 //     before the MFMA (operands come from LDS reads, from earlier MFMAs, or from
 //     arithmetic done at least one operand slot earlier);
 //   - the vector ALU reads an MFMA's result only after enough later instructions
-//     have issued to cover the 4-pass MFMA's result latency (in the kernels: two
-//     independent MFMAs);
+//     have issued to cover the MFMA's result latency, 8 passes for 32x32x16 and 4
+//     for 16x16x32 (in the kernels: two independent MFMAs, or the vector-ALU chunk
+//     of an earlier step);
 //   - back-to-back MFMAs on the same accumulator are interlocked by hardware.
 // MFMAs ignore the EXEC mask: code that contains them must only be skipped by a
 // truly scalar branch, so every wave-uniform condition guarding such code has
@@ -230,10 +231,45 @@ __device__ __forceinline__ void lds_wait(u32x2& x, u32x2& y) {
 // Volatile assembly statements keep their order, which is what orders an MFMA
 // after the wait that covers its operands.  W >= 0: that wait rides in the same
 // statement.
-//   mfma16_v : accumulator in vector registers       mfma16_vc : ... starting from another tile
-//   mfma16_a : accumulator in accumulation registers
-//   *_ab     : the B operand lives in accumulation registers (resident operands)
+//   mfma_v  : accumulator in vector registers       mfma_vc : ... starting from another tile
+//   mfma_a  : accumulator in accumulation registers
+//   *_ab    : the B operand lives in accumulation registers (resident operands)
+// (32x32x16; the forms of 16x16x32 are further down)
 // ---------------------------------------------------------------------------
+template <int W>
+__device__ __forceinline__ void mfma_v(f32x16& acc, const u32x4& a, const bf16x8& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b));
+}
+template <int W>
+__device__ __forceinline__ void mfma_v(f32x16& acc, const u32x4& a, const u32x4& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_vc(f32x16& acc, const u32x4& a, const bf16x8& b, const f32x16& c) {
+    asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "v"(b), "v"(c));
+}
+__device__ __forceinline__ void mfma_vc(f32x16& acc, const u32x4& a, const u32x4& b, const f32x16& c) {
+    asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "v"(b), "v"(c));
+}
+__device__ __forceinline__ void mfma_a(f32x16& acc, const u32x4& a, const u32x4& b) {
+    asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b));
+}
+template <int W>
+__device__ __forceinline__ void mfma_a_w(f32x16& acc, const u32x4& a, const u32x4& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+a"(acc) : "v"(a), "v"(b));
+}
+template <int W>
+__device__ __forceinline__ void mfma_v_ab(f32x16& acc, const u32x4& a, const bf16x8& b) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "a"(b), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" SP_MFMA_POST : "+v"(acc) : "v"(a), "a"(b));
+}
+template <int W>
+__device__ __forceinline__ void mfma_vc_ab(f32x16& acc, const u32x4& a, const bf16x8& b, const f32x16& c) {
+    if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%4)\n\t" SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c), "n"(W));
+    else asm volatile(SP_MFMA_PRE "v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" SP_MFMA_POST : "=&v"(acc) : "v"(a), "a"(b), "v"(c));
+}
 // x = the lane's bit of `lanes` ? -inf : x.  One select per register as assembly: written in C++, a run of selects on one
 // flag becomes a branch around moves, and its copies of whole accumulator tiles took the dQ stage with one row block
 // (packed documents) from 241 to 256 vector registers and moves between the register files.  The compiler does not see
@@ -263,6 +299,12 @@ __device__ __forceinline__ void hide_lanes(TILE& x, TILE& y, uint64_t lanes) {  
 // at most N of this wave's global loads (register and LDS destinations) are still in flight
 template <int N>
 __device__ __forceinline__ void vmem_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// Waits that tie the values they cover: used where the awaited registers are then combined into wider
+// operands (the combination must not be scheduled before the wait).
+template <int N>
+__device__ __forceinline__ void lds_wait4(u32x4& a, u32x4& b, u32x4& c, u32x4& d) {
+    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(SP_LGKM(N)));
+}
 // ---------------------------------------------------------------------------
 // v_mfma_f32_16x16x32_bf16: C[16x16] += A[16x32] * B[32x16] per wave.  With lane l, lo = l % 16, g = l / 16:
 //   A operand: lane holds A[lo][8*g + e], e = 0..7;   B operand: lane holds B[8*g + e][lo]

@@ -174,6 +174,8 @@ sp_status launch_attn_fwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_matrix_d64(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_bwd_matrix_d128(const AttnArgs& a, hipStream_t st);
+sp_status launch_attn_bwd_matrix_long_d64(const AttnArgs& a, hipStream_t st);
+sp_status launch_attn_bwd_matrix_long_d128(const AttnArgs& a, hipStream_t st);
 sp_status launch_attn_merge(float* o_acc, float* lse_acc, const void* o_blk, const float* lse_blk, void* o_out,
                             int64_t B, int64_t S, int32_t Hq, int32_t D, hipStream_t st);
 
@@ -361,6 +363,30 @@ inline int32_t dkdv_full_splits(int64_t B, int64_t S, int64_t Skv, int32_t Hq, i
         if (n == 1 || end < best_end) { best = n; best_end = end; }
     }
     return best;
+}
+// Which MFMA shape the backward's matrix stages run with: 32x32x16 (false), or in long launches 16x16x32 (true).  Where the
+// chip is full for long enough the board's power sets the clock, and 16x16x32 takes less energy per product; elsewhere the
+// clock is at its limit and what counts is instructions, of which that shape has twice the MFMAs, masks for twice the
+// blocks and a quarter more code to fetch.  The two part at the matrix work per compute unit, in us by the costs above;
+// packed documents count as all of the mean length (the caller's longest may be anything).  Measured, backward, 4 query
+// heads and 1 KV head unless said otherwise, (work) 32x32x16 / 16x16x32, us:
+//   D = 128: 1024 rows (2) 35.3 / 37.4, of 8 heads (5) 50.7 / 56.0, 4096 rows of 8 heads (78) 178 / 185, 6000 rows (84) 153 /
+//     154, 8192 rows of 3 heads (118) 177 / 173, of 4 (157) 221 / 212, 16384 rows (627) 744 / 708, 32768 (2509) 2752 / 2608
+//   D = 64: 2048 rows (7) 37.4 / 38.9, 8192 rows (105) 137 / 139, 16384 rows of 2 heads (209) 249 / 253, 12288 rows (235) 264 /
+//     254, 32768 rows (1673) 1605 / 1525
+//   packed, D = 128: 5000 rows in documents of 600 (6) 75 / 84, 20000 in documents of 1024 (28) 177 / 189, 131072 in documents
+//     of 256 (83) 638 / 669, of 600 (175) 976 / 961, 65536 in documents of 4096 (446) 1346 / 1311
+//   packed, D = 64: 20000 rows in documents of 1024 (18) 121 / 132, 131072 in documents of 600 (117) 593 / 634, of 2000 (330)
+//     912 / 940, 40000 in 6 documents (415) 1210 / 1154
+// Of 528 shapes (300 to 32768 rows, batches, rings, packed) two were over 2 % slower than with 32x32x16 for all (by 1 and 2
+// us), against 262 with 16x16x32 for all.  Boxes differ: D = 64 gains from 120 and packed from 175 on one, from 235 and 415 on another.
+// A function of the extents only, and the same for one packed document as for a dense call: both give the same bits.
+constexpr double kLongLaunch[2][2] = {{220., 400.}, {100., 125.}};  // [D = 64, 128][dense, packed]
+inline bool bwd_long_launch(int64_t B, int64_t S, int64_t Skv, int64_t off, int32_t Hq, int32_t D, int64_t n_docs) {
+    const bool packed = n_docs > 1;
+    const double pairs = packed ? (double)S * ((double)S / (double)n_docs) / 2. : even_share(S, Skv, off) * (double)S * (double)Skv * (double)B;
+    const double work = step_share(D) * (kDkdvStep + dq_step(2 * 128)) * pairs * Hq / (32. * 256.) / (double)kComputeUnits;
+    return work >= kLongLaunch[D == 128][packed];
 }
 // The work split of a dense call.
 inline DkdvChunks dense_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t D) {
