@@ -61,6 +61,34 @@ def test_blocks_match_oracle(long_build, Sq, Skv, off, Hq, Hkv, D):
     check_grads([host_f64(t[0]) for t in got], refs, "block")
 
 
+# Lanes hidden by a document's end stay hidden from step to step, until a step in which the next one ends.  Several ends
+# inside one wave's 64 keys and rows, on and off the 32-row steps; documents that end with a tile; groups of heads, whose
+# later heads start the walk again at the top; chunks that start in the middle of a head (several per tile: 32 to 96 steps
+# of four to nine heads in up to eight chunks).  Two row blocks of dQ from 128 tiles on: 36 heads.
+PACKED = {
+    "many ends in a block": [5, 17, 10, 32, 64, 1, 31, 33, 96, 0, 128, 7, 9, 11, 200, 3, 3, 3, 60],
+    "ends on steps": [32, 32, 64, 32, 96, 32, 256, 32, 32, 160],
+    "ends one off a step": [33, 31, 65, 31, 95, 33, 255, 257, 1],
+    "short ones behind a long one": [700, 1, 2, 29, 32, 16, 48, 20],
+    "short ones before a long one": [20, 48, 16, 32, 29, 2, 1, 700],
+    "long, short, long": [400, 30, 34, 2, 62, 510],
+}
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(4, 1, 64), (4, 1, 128), (6, 2, 64), (9, 1, 128), (36, 9, 64), (36, 9, 128)])
+@pytest.mark.parametrize("name", sorted(PACKED))
+def test_packed_documents_match_oracle(long_build, name, Hq, Hkv, D):
+    lengths = PACKED[name]
+    print(f"{name}: {Hq}/{Hkv} D={D}", flush=True)
+    cu = synth.cu_seqlens_from_lengths(lengths)
+    T = int(cu[-1])
+    bits = synth.attn_inputs(T + Hq, T, Hq, Hkv, D)
+    q, k, v, do = (dev_bf16(t[0]) for t in bits)
+    got = run(long_build, q, k, v, do, torch.from_numpy(cu).cuda())[2:]
+    refs = rn.attn_varlen_bwd(*(rn.widen_bf16(t[0]) for t in bits), cu)[:3]
+    check_grads([host_f64(t) for t in got], refs, name)
+
+
 # Where the rule picks them: the regular library gives the bits of LIB_LONG (it runs these programs) and of the build with
 # every wait spelled out (no register read early, no operand late).  One and two row blocks of dQ, one and several chunks.
 def bits_of_three(q, k, v, do, cu, what):
