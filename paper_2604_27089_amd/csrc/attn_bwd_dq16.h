@@ -111,7 +111,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     using Dma = TileDma<D, BN, kWaves>;
     constexpr int PW = Dma::PER_WAVE;
     constexpr int GROUP = 2 * PW;
-    static_assert(GROUP <= NS, "one load per slot of the S phase");
+    static_assert(GROUP < NS, "one load per slot of the S phase, and the cursor moves on in the slot behind them");
     const uint32_t stride_b = p.kvmap.row_stride * 2;
     // byte offset, from the tile's first row, of the 16 bytes this lane fetches in its K-th load; rows past
     // `lim` (tile-relative) re-read row `lim` (they are never used unmasked)
