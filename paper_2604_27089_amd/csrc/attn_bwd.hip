@@ -128,7 +128,7 @@ sp_status launch(const AttnArgs& a, hipStream_t st) {
         if (hipGetLastError() != hipSuccess) return SP_ERR_LAUNCH;
     }
     if (a.stages & (SP_BWD_STAGE_DKDV | SP_BWD_STAGE_DQ)) {
-        const bool long_launch = kAlwaysLong || bwd_long_launch(a.B, a.S, a.Skv, a.off, a.Hq, a.D, a.row_lo ? a.n_docs : 0);
+        const bool long_launch = kAlwaysLong || bwd_long_launch(a.B, a.S, a.Skv, a.off, a.Hq, a.Hkv, a.D, a.row_lo ? a.n_docs : 0);
         const sp_status r = D == 64 ? (long_launch ? launch_attn_bwd_matrix_long_d64(a, st) : launch_attn_bwd_matrix_d64(a, st))
                                     : (long_launch ? launch_attn_bwd_matrix_long_d128(a, st) : launch_attn_bwd_matrix_d128(a, st));
         if (r != SP_OK) return r;

@@ -364,30 +364,6 @@ inline int32_t dkdv_full_splits(int64_t B, int64_t S, int64_t Skv, int32_t Hq, i
     }
     return best;
 }
-// Which MFMA shape the backward's matrix stages run with: 32x32x16 (false), or in long launches 16x16x32 (true).  Where the
-// chip is full for long enough the board's power sets the clock, and 16x16x32 takes less energy per product; elsewhere the
-// clock is at its limit and what counts is instructions, of which that shape has twice the MFMAs, masks for twice the
-// blocks and a quarter more code to fetch.  The two part at the matrix work per compute unit, in us by the costs above;
-// packed documents count as all of the mean length (the caller's longest may be anything).  Measured, backward, 4 query
-// heads and 1 KV head unless said otherwise, (work) 32x32x16 / 16x16x32, us:
-//   D = 128: 1024 rows (2) 35.3 / 37.4, of 8 heads (5) 50.7 / 56.0, 4096 rows of 8 heads (78) 178 / 185, 6000 rows (84) 153 /
-//     154, 8192 rows of 3 heads (118) 177 / 173, of 4 (157) 221 / 212, 16384 rows (627) 744 / 708, 32768 (2509) 2752 / 2608
-//   D = 64: 2048 rows (7) 37.4 / 38.9, 8192 rows (105) 137 / 139, 16384 rows of 2 heads (209) 249 / 253, 12288 rows (235) 264 /
-//     254, 32768 rows (1673) 1605 / 1525
-//   packed, D = 128: 5000 rows in documents of 600 (6) 75 / 84, 20000 in documents of 1024 (28) 177 / 189, 131072 in documents
-//     of 256 (83) 638 / 669, of 600 (175) 976 / 961, 65536 in documents of 4096 (446) 1346 / 1311
-//   packed, D = 64: 20000 rows in documents of 1024 (18) 121 / 132, 131072 in documents of 600 (117) 593 / 634, of 2000 (330)
-//     912 / 940, 40000 in 6 documents (415) 1210 / 1154
-// Of 528 shapes (300 to 32768 rows, batches, rings, packed) two were over 2 % slower than with 32x32x16 for all (by 1 and 2
-// us), against 262 with 16x16x32 for all.  Boxes differ: D = 64 gains from 120 and packed from 175 on one, from 235 and 415 on another.
-// A function of the extents only, and the same for one packed document as for a dense call: both give the same bits.
-constexpr double kLongLaunch[2][2] = {{220., 400.}, {100., 125.}};  // [D = 64, 128][dense, packed]
-inline bool bwd_long_launch(int64_t B, int64_t S, int64_t Skv, int64_t off, int32_t Hq, int32_t D, int64_t n_docs) {
-    const bool packed = n_docs > 1;
-    const double pairs = packed ? (double)S * ((double)S / (double)n_docs) / 2. : even_share(S, Skv, off) * (double)S * (double)Skv * (double)B;
-    const double work = step_share(D) * (kDkdvStep + dq_step(2 * 128)) * pairs * Hq / (32. * 256.) / (double)kComputeUnits;
-    return work >= kLongLaunch[D == 128][packed];
-}
 // The work split of a dense call.
 inline DkdvChunks dense_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, int32_t Hq, int32_t Hkv, int32_t D) {
     const int32_t most = dkdv_split_count(B, S, Skv, Hq, Hkv);
@@ -398,6 +374,40 @@ inline DkdvChunks dense_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, i
     }
     const int32_t n = dkdv_full_splits(B, S, Skv, Hq, Hkv, D, most, off);
     return DkdvChunks{n, 0, n * order_tiles(Skv)};
+}
+// Which MFMA shape the backward's matrix stages run with: 32x32x16 (false), or in long launches 16x16x32 (true).  Where the
+// chip is full for long enough the board's power sets the clock, and 16x16x32 takes less energy per product; elsewhere the
+// clock is at its limit and what counts is instructions, of which that shape has twice the MFMAs, masks for twice the
+// blocks and a quarter more code to fetch.  The two part at the matrix work per compute unit, in us by the costs above;
+// packed documents count as all of the mean length (the caller's longest may be anything).  Measured, backward, 4 query
+// heads and 1 KV head unless said otherwise, (work) 32x32x16 / 16x16x32, us:
+//   D = 128, from 90: 1024 rows (2) 35.3 / 37.4, of 8 heads (5) 50.7 / 56.0, 4096 rows of 8 heads (78) 178 / 185, 6000 rows (84)
+//     153 / 154, 8192 rows of 3 heads (118) 177 / 173, of 4 (157) 221 / 212, 16384 rows (627) 744 / 708, 32768 (2509) 2752 / 2608
+//   D = 64, from 125: 2048 rows (7) 37.4 / 38.9, 8192 rows (105) 137 / 139, 4 x 5207 rows (169) 216 / 211, 16384 rows of 2 heads
+//     (209) 249 / 253 and 258 / 257 on two boxes, 11332 rows (200) 238 / 227, 32768 rows (1673) 1605 / 1525
+//   rows that see every key, 8 KV heads, from 70 and 90: D = 128, 24 heads, 1470 rows (61) 115 / 118, 1660 rows (77) 134 / 131,
+//     32 heads, 4096 rows (627) 696 / 659; D = 64, 32 heads, 1563 rows (61) 100 / 101, 2048 rows (105) 125 / 120
+//   packed, D = 128, from 100: 5000 rows in documents of 600 (6) 75 / 84, 20000 in documents of 1024 (28) 177 / 189, 131072 in
+//     documents of 256 (83) 638 / 669, of 600 (175) 976 / 961, 65536 in documents of 4096 (446) 1346 / 1311
+//   packed, D = 64, from 400: 20000 rows in documents of 1024 (18) 121 / 132, 131072 in documents of 600 (117) 593 / 634, of 2000
+//     (330) 912 / 940, 40000 in 6 documents (415) 1210 / 1154
+// At D = 128 the chip is also full in a launch whose workgroups all run at once and end together: from work of 0.475 of its
+// longest workgroup on (4096 rows, 39 of 74 us: 84.5 / 82.0 and 81.7 / 80.8 on two boxes; 158 shapes below that 0.98 to 1.10
+// of the time of 32x32x16, 24 from there on 0.975 to 0.99; D = 64 1.04 to 1.10 throughout).
+// A function of the extents only, and the same for one packed document as for a dense call: both give the same bits.
+constexpr double kLongLaunch[2][3] = {{125., 90., 400.}, {90., 70., 100.}};  // [D = 64, 128][dense, every key seen, packed]
+inline bool bwd_long_launch(int64_t B, int64_t S, int64_t Skv, int64_t off, int32_t Hq, int32_t Hkv, int32_t D, int64_t n_docs) {
+    const bool packed = n_docs > 1;
+    const double pairs = packed ? (double)S * ((double)S / (double)n_docs) / 2. : even_share(S, Skv, off) * (double)S * (double)Skv * (double)B;
+    const double work = step_share(D) * (kDkdvStep + dq_step(2 * 128)) * pairs * Hq / (32. * 256.) / (double)kComputeUnits;
+    if (work >= kLongLaunch[D == 128][packed ? 2 : off >= Skv]) return true;
+    if (packed || D != 128 || off != 0 || Skv != S || work < 30.) return false;
+    const DkdvChunks c = dense_chunks(B, (int32_t)S, (int32_t)S, 0, Hq, Hkv, D);
+    const int64_t q_rows = 128 * dq_row_blocks(B, S, Hq), n_q = (S + q_rows - 1) / q_rows * Hq * B;
+    if ((int64_t)c.n_chunks * Hkv * B + n_q > kComputeUnits) return false;
+    const double steps = c.len > 0 ? (double)c.len : (double)dkdv_tile_steps(0, (int32_t)S, 0, Hq / Hkv) / c.nsplit;
+    const double t_kv = kDkdvStep * steps + kDkdvFixed, t_q = dq_step(q_rows) * (double)((S + 31) / 32) + kDqFixed;
+    return work >= 0.475 * (t_kv > t_q ? t_kv : t_q);
 }
 inline size_t dkdv_part_bytes(int64_t B, int64_t Skv, int32_t Hkv, int32_t D, int32_t nsplit) {
     return nsplit > 1 ? (size_t)2 * nsplit * B * Skv * Hkv * D * sizeof(float) : 0;

@@ -98,7 +98,7 @@ def bits_of_three(q, k, v, do, cu, what):
     return fast
 
 
-@pytest.mark.parametrize("B,S,Hq,Hkv,D", [(1, 8190, 4, 1, 128), (1, 10300, 4, 1, 128), (40, 1100, 9, 9, 128), (1, 20001, 2, 1, 64), (1, 32700, 1, 1, 64), (3, 9001, 6, 2, 64)])
+@pytest.mark.parametrize("B,S,Hq,Hkv,D", [(1, 4096, 4, 1, 128), (1, 8190, 4, 1, 128), (1, 10300, 4, 1, 128), (40, 1100, 9, 9, 128), (1, 20001, 2, 1, 64), (1, 32700, 1, 1, 64), (3, 9001, 6, 2, 64)])
 def test_rule_picks_these_programs_dense(B, S, Hq, Hkv, D):
     q, k, v, do = (dev_bf16(t) for t in synth.attn_inputs(S + D, S, Hq, Hkv, D, B))
     bits_of_three(q, k, v, do, None, f"B={B} S={S} {Hq}/{Hkv} D={D}")
