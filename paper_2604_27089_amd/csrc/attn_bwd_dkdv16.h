@@ -6,12 +6,13 @@
 // MFMAs (one per key block), the vector-ALU work is spread a little behind every MFMA, and reads are issued three or four
 // slots ahead.
 //
-// What bounds it: power.  With 32x32x16 MFMAs a step took 2660 cycles at 1.80 GHz, with 16x16x32
-// 3000 at 2.12 (pipe time 2048): 32768 rows, 4 heads, D = 128, 1683 -> 1595 us, 16 x 4096
-// rows 465 -> 446; D = 64 979 -> 908 and 270 -> 254 us (V in registers included; at 2.3 GHz).
-// Left out one at a time in the 32x32x16 kernel: vector ALU -16 % of the time, LDS reads
-// -10 %, tile loads -5 %, V reads alone -3 %; moving them about inside a slot changed nothing.
-//
+// What bounds it: the clock that the board's power leaves, and the instructions a lone wave issues beside its MFMAs.  131072
+// rows, 4 heads, D = 128, everything included: with 32x32x16 a step takes 2590 cycles at 1.69 GHz, the matrix pipe busy 79 %
+// of them, with 16x16x32 2890 at 1.95 GHz, busy 71 % (pipe time 2048): 12 % more cycles at a clock 15 % higher, 25.2 -> 24.3
+// ms; 32768 rows 1.63 -> 1.54 ms, 16 x 4096 rows 441 -> 419 us.  D = 64 (V in registers included), 32768 rows: 1.96 -> 2.20
+// GHz, busy 57 -> 54 %, 956 -> 887 us; at 2.2 of 2.4 GHz it is the instructions that are left.
+// Left out one at a time in the 32x32x16 kernel: vector ALU -16 % of the time, LDS reads -10 %, tile loads -5 %, V reads
+// alone -3 %; moving them about inside a slot changed nothing.
 #pragma once
 #include "attn_bwd_dkdv.h"
 
@@ -511,7 +512,7 @@ __device__ __forceinline__ void run(const DkdvParams& p, uint32_t wg, char* smem
     if constexpr (SPLIT) {
         // fp32 partial sums of this chunk (dK unscaled); the reduction kernel adds the chunks in a fixed order.  A
         // lane holds four consecutive keys of one column in four registers, and the sums are laid out like that, so a
-        // store is 16 bytes per lane and 512 contiguous bytes per half wave: 64 stores per wave where key-major sums
+        // store is 16 bytes per lane and 256 contiguous bytes per 16 lanes: 64 stores per wave where key-major sums
         // took 256 of 4 bytes per lane (5.5 us per workgroup).
         const int keys = Skv - j0 < BNK ? Skv - j0 : BNK;
         float* pk = p.part + part_offset((int64_t)b * p.Hkv + g, p.chunks.nsplit, Skv, first_chunk, split, keys, D);

@@ -5,12 +5,12 @@
 // reads are issued sixteen MFMAs ahead.  The phases of a body:
 //   S(u) + the loads of step u+6 | dP(u) + exponentials | dQ(u-1) + the rest of them, dS products
 //
-// What bounds it: power, then issue.  With 32x32x16 MFMAs a step took 1816 cycles at 1.73 GHz, with
-// 16x16x32 1950 at 1.99 (pipe time 1536): 32768 rows, 4 heads, D = 128, 1162 -> 1076 us, 16 x 4096 rows
-// 327 -> 311; D = 64 671 -> 647 and 193 -> 191.  Two MFMAs back to back with the other work
-// behind each pair, instead of some behind every one, took 2268 cycles; branches laid out so
-// that the usual path takes no jump gave 1 %, the load cursor's update outside the S phase cost 3 %.
-//
+// What bounds it: the clock that the board's power leaves, then issue.  131072 rows, 4 heads, D = 128, everything included:
+// with 32x32x16 a step takes 1780 cycles at 1.60 GHz, the matrix pipe busy 86 % of them, with 16x16x32 1910 at 1.86 GHz,
+// busy 80 % (pipe time 1536): 18.3 -> 16.9 ms; 32768 rows 1.17 -> 1.09 ms, 16 x 4096 rows 333 -> 312 us; D = 64, 32768 rows,
+// 1.85 -> 2.11 GHz, busy 63 -> 58 %, 678 -> 652 us.  Two MFMAs back to back with the other work behind each pair, instead of
+// some behind every one, took 16 % more cycles; branches laid out so that the usual path takes no jump gave 1 %, the load
+// cursor's update outside the S phase cost 3 %.
 #pragma once
 #include "attn_bwd_dq.h"
 
@@ -179,7 +179,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
     // ... there, the rows (their lanes) that see nothing of any step before start_step, in which the next row's document
     // starts.  Kept from step to step: four blocks' compares in each of them cost a wave with a boundary among its rows
     // more than the selects, and its workgroup waits for it (20000 rows in documents of 1024, 4 heads, D = 64, backward
-    // 198 us, 176 now, 160 with the 32x32x16 form of this stage).
+    // 198 us with the compares, 176 without).
     uint64_t dead[RB] = {};
     int start_step = 0;
     {
@@ -300,7 +300,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
             static_for<0, RB>([&](auto N) {
                 constexpr int n = decltype(N)::value, w = n == 0 ? W : -1;
                 if constexpr (s < NS) {
-                    // ---- S(u); the dS products of step u-1's second key block; the loads of step u+6 ----
+                    // ---- S(u); the loads of step u+6 ----
                     constexpr int kb = s / NK, ks = s % NK;
                     if constexpr (ks == 0) mfma16_vc_ab<w>(sacc[kb][n], ak[s], qreg[n][ks], seed_s[n]);
                     else mfma16_v_ab<w>(sacc[kb][n], ak[s], qreg[n][ks]);
@@ -309,7 +309,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                     if constexpr (n == 1 && s == GROUP) advance_load();
                     if constexpr (n == 1 && s < GROUP) issue_load(SC, DBUF);
                 } else if constexpr (s < 2 * NS) {
-                    // ---- dP(u), most of the exponentials ----
+                    // ---- dP(u), two thirds of the exponentials ----
                     constexpr int kk = s - NS, kb = kk / NK, ks = kk % NK;
                     if constexpr (ks == 0) mfma16_vc_ab<w>(pacc[kb][n], av[kk], doreg[n][ks], seed_p[n]);
                     else mfma16_v_ab<w>(pacc[kb][n], av[kk], doreg[n][ks]);
@@ -387,8 +387,7 @@ __device__ __forceinline__ void run(const DqParams& p, uint32_t wg, char* smem) 
                     if constexpr (kk * RB + n == kExp0) exp_args(Int<kExp0>{});
                     valu_at(Int<kk * RB + n>{});
                 } else {
-                    // ---- dQ(u-1); with two row blocks the last quarter of the exponentials; the dS products of step u's
-                    // first key block ----
+                    // ---- dQ(u-1); the last third of the exponentials, then the dS products of step u ----
                     // (row blocks forth in even slots, back in odd ones: each MFMA keeps an operand of the one before it)
                     constexpr int t = s - 2 * NS, rb = even ? n : RB - 1 - n;
                     const u32x4 kt = {t0[t][0], t0[t][1], t1[t][0], t1[t][1]};

@@ -163,7 +163,8 @@ inline int packed_key_groups(int64_t T, int64_t n_docs, int32_t Hq) {
 }
 // Row blocks of 32 query rows per wave of the dQ stage: 2 (256 rows per workgroup) unless the launch has few tiles
 // and is bound by the walk of the longest one.  With one block a wave's step takes 0.4 us instead of 0.75 and there are
-// twice the workgroups, but every K/V operand read from LDS feeds one MFMA instead of two.  Same bits.  Backward
+// twice the workgroups, but every K/V operand read from LDS feeds one MFMA instead of two (16x16x32: two
+// instead of four).  Same bits.  Backward
 // with 2 / 1 blocks, 4 heads of D = 128, us: 2048 rows (32 tiles of 256) 75 / 59, 4096 rows (64) 127 / 103, 8192 rows
 // (128) 280 / 246, 10007 rows of 3 heads (120) 330 / 277, 12288 rows (192) 483 / 509, 16384 rows (256) 835 / 855;
 // 8192 rows of 5 heads (160) 347 / 354; D = 64: 4096 rows 87 / 70, 8192 rows 173 / 150.
@@ -217,7 +218,9 @@ inline int32_t dkdv_split_count(int64_t B, int64_t S, int64_t Skv, int32_t Hq, i
 }
 // What the estimates take a workgroup of the two matrix stages to cost in a full chip, in us: per 32-row step of dK/dV, per
 // 32-key step of dQ with one or two row blocks (D = 128; D = 64 takes two thirds), and beyond the steps (resident operands
-// and first tiles, the pipeline's fill, the results).
+// and first tiles, the pipeline's fill, the results).  Fitted to the 32x32x16 programs, which run wherever a count or an
+// order is worth more than a few percent; the 16x16x32 ones of long launches take 4 to 7 % less for either stage (D = 64:
+// 0.58 of D = 128 for dK/dV, 0.61 for dQ), and what decides is the ratio of the two.
 constexpr double kDkdvStep = 1.5, kDkdvFixed = 20., kDqFixed = 10.;
 inline double dq_step(int64_t q_rows) { return q_rows == 128 ? 0.5 : 0.95; }
 inline double step_share(int32_t D) { return D == 64 ? 2. / 3. : 1.; }
