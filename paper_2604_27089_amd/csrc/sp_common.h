@@ -387,7 +387,7 @@ inline DkdvChunks dense_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, i
 //   D = 128, from 90: 1024 rows (2) 35.3 / 37.4, of 8 heads (5) 50.7 / 56.0, 4096 rows of 8 heads (78) 178 / 185, 6000 rows (84)
 //     153 / 154, 8192 rows of 3 heads (118) 177 / 173, of 4 (157) 221 / 212, 16384 rows (627) 744 / 708, 32768 (2509) 2752 / 2608
 //   D = 64, from 125: 2048 rows (7) 37.4 / 38.9, 8192 rows (105) 137 / 139, 4 x 5207 rows (169) 216 / 211, 16384 rows of 2 heads
-//     (209) 249 / 253 and 258 / 257 on two boxes, 11332 rows (200) 238 / 227, 32768 rows (1673) 1605 / 1525
+//     (209) 249 / 253 and 258 / 257 on two cards, 11332 rows (200) 238 / 227, 32768 rows (1673) 1605 / 1525
 //   rows that see every key, 8 KV heads, from 70 and 90: D = 128, 24 heads, 1470 rows (61) 115 / 118, 1660 rows (77) 134 / 131,
 //     32 heads, 4096 rows (627) 696 / 659; D = 64, 32 heads, 1563 rows (61) 100 / 101, 2048 rows (105) 125 / 120
 //   packed, D = 128, from 100: 5000 rows in documents of 600 (6) 75 / 84, 20000 in documents of 1024 (28) 177 / 189, 131072 in
@@ -395,7 +395,7 @@ inline DkdvChunks dense_chunks(int64_t B, int32_t S, int32_t Skv, int32_t off, i
 //   packed, D = 64, from 400: 20000 rows in documents of 1024 (18) 121 / 132, 131072 in documents of 600 (117) 593 / 634, of 2000
 //     (330) 912 / 940, 40000 in 6 documents (415) 1210 / 1154
 // At D = 128 the chip is also full in a launch whose workgroups all run at once and end together: from work of 0.475 of its
-// longest workgroup on (4096 rows, 39 of 74 us: 84.5 / 82.0 and 81.7 / 80.8 on two boxes; 158 shapes below that 0.98 to 1.10
+// longest workgroup on (4096 rows, 39 of 74 us: 84.5 / 82.0 and 81.7 / 80.8 on two cards; 158 shapes below that 0.98 to 1.10
 // of the time of 32x32x16, 24 from there on 0.975 to 0.99; D = 64 1.04 to 1.10 throughout).
 // A function of the extents only, and the same for one packed document as for a dense call: both give the same bits.
 constexpr double kLongLaunch[2][3] = {{125., 90., 400.}, {90., 70., 100.}};  // [D = 64, 128][dense, every key seen, packed]
